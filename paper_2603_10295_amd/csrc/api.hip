@@ -240,6 +240,21 @@ ephw_status ephw_system_load(ephw_ctx* ctx, const ephw_system_desc* d, ephw_syst
     return upload(dst, w, (size_t)n, &s->bytes, s->mem.get());
   };
   if ((st = weights(&s->w_e, d->w_e, d->ne)) != EPHW_OK) return fail(st);
+  {
+    // packed phases keep every weight's leading 22 bits only within a range of
+    // 2^8 of the largest (smaller ones would lose bits to the FP16 range)
+    double big = 0.0, small = HUGE_VAL;
+    bool finite = true;
+    for (int64_t i = 0; i < d->ne; ++i) {
+      const double w = d->w_e ? fabs(d->w_e[i]) : 1.0;
+      finite = finite && std::isfinite(w);
+      big = fmax(big, w);
+      if (w > 0.0) small = fmin(small, w);
+    }
+    int ex = 0;
+    if (finite && big > 0.0 && big <= 256.0 * small) (void)frexp(big, &ex);   // big <= 2^ex
+    if (finite && big > 0.0 && big <= 256.0 * small && ex > -60 && ex < 60) s->pack_scale = (float)ldexp(1.0, 14 - ex);
+  }
   if ((st = weights(&s->w_p, d->w_p, d->np)) != EPHW_OK) return fail(st);
   if ((st = weights(&s->w_h, d->w_h, d->nh)) != EPHW_OK) return fail(st);
   if ((st = weights(&s->w_c, d->w_c, d->nc)) != EPHW_OK) return fail(st);
@@ -456,6 +471,7 @@ ephw_status ephw_phase_sum_rp(ephw_system* s, const double* q, int64_t nq, int32
   p.K = s->np;
   p.A = wsp(s, WS_PQ);
   p.compensated = prec == EPHW_FP32_COMP;
+  p.split = kind == 1;
   p.lda = s->np;
   p.B = s->g;
   p.ldb = p.N;
@@ -470,7 +486,7 @@ ephw_status ephw_phase_sum_rp(ephw_system* s, const double* q, int64_t nq, int32
 ephw_status ephw_kset_free(ephw_kset* ks) {
   if (!ks) return EPHW_OK;
   (void)hipDeviceSynchronize();
-  void* ptrs[] = {ks->k, ks->pk, ks->pkh, ks->eps, ks->v64, ks->vt, ks->dv64, ks->dpk,
+  void* ptrs[] = {ks->k, ks->pk, ks->pkp, ks->pkh, ks->eps, ks->v64, ks->vt, ks->dv64, ks->dpk,
                   ks->dv != ks->dv64 ? ks->dv : nullptr};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -532,6 +548,11 @@ ephw_status ephw_kset_create(ephw_system* s, const double* k, int64_t nk, int32_
     if ((e = phase_matrix(0, ks->k, nk, s->r_h, s->w_h, s->nh, ks->pkh, st)) != EPHW_OK)
       return fail(e);
   }
+  if (kind == 1 && nk >= kPackMinPoints && s->nw <= 32 && s->pack_scale > 0.f && cgemm_packable(nk, 128, s->ne) &&
+      alloc(&ks->pkp, (size_t)packed_bytes(nk, s->ne)) == EPHW_OK) {   // without memory for it: the set works unpacked
+    Stage sg_(s, EPHW_STAGE_PHASE, st);
+    if ((e = pack_phases(ks->k, nk, s->r_e, s->w_e, s->ne, s->pack_scale, ks->pkp, st)) != EPHW_OK) return fail(e);
+  }
   if ((e = interp_eigh(s, ks->pkh, nk, s->nh, s->h_r, s->nw, ks->eps, ks->v64, st)) != EPHW_OK)
     return fail(e);
   {
@@ -586,6 +607,8 @@ struct InterpReq {
   int32_t prec = 0, qb = 1;
   uint32_t flags = 0;
   bool need_g = false, need_kq_eig = false;
+  bool split = false;        // only complex64 values leave the phase sums (see GemmParams::split)
+  bool packed = false;       // the Re sum on packed operands
   bool fused = false;        // band rotations in the Re-sum GEMM's epilogue (no W buffer)
   bool lw = false;           // linewidth reduction of the rotated g (no g output)
   LwParams lwp;              // its kernel parameters, from the arguments below
@@ -602,6 +625,13 @@ bool interp_fusable(const ephw_system* s, const InterpReq& r) {
   const int64_t E = (int64_t)s->nm * s->nw * s->nw, tail = r.nq % r.qb;
   return cgemm_band_fusable(1, r.nk, r.qb * E, s->nw, s->ne, r.qb * E) &&
          (tail == 0 || cgemm_band_fusable(1, r.nk, tail * E, s->nw, s->ne, tail * E));
+}
+
+// Whether the call's Re sums run on packed operands: the set has its packed
+// phases and both the full and the last batch fit.
+bool interp_packable(const ephw_system* s, const ephw_kset* ks, const InterpReq& r) {
+  const int64_t E = (int64_t)s->nm * s->nw * s->nw;
+  return r.split && r.need_g && ks->pkp && r.prec == EPHW_FP32 && cgemm_packable(r.nk, r.qb * E, s->ne);
 }
 
 InterpWs interp_layout(const ephw_system* s, const InterpReq& r, char* base) {
@@ -627,7 +657,10 @@ InterpWs interp_layout(const ephw_system* s, const InterpReq& r, char* base) {
   if (jw > 0) w.jwork = takd((size_t)jw * 8);
   w.u = take((size_t)nq * nm * nm * cs);
   if (r.need_g) {
-    w.g = take((size_t)qb * s->ne * E * cs);
+    // once the modes are rotated g(Re,q) gives way to the packed operand
+    const size_t gb = (size_t)qb * s->ne * E * cs;
+    const size_t pb = r.packed ? (size_t)packed_bytes(qb * E, s->ne) + (size_t)qb * E * 4 : 0;
+    w.g = take(gb > pb ? gb : pb);
     w.gnu = take((size_t)qb * s->ne * E * cs);
     if (!r.fused) w.w = take((size_t)nk * qb * E * cs);
   }
@@ -693,6 +726,7 @@ ephw_status interp_validate(const char* who, ephw_kset* ks, const double* q, int
   r->flags = flags;
   r->need_g = (flags & (EPHW_OUT_G | EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) != 0;
   r->need_kq_eig = !kq_index && (!wannier || eps_kq);
+  r->split = prec_kind(prec) == 1 && (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   return EPHW_OK;
 }
 
@@ -779,6 +813,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     rp.K = s->np;
     rp.A = static_cast<const char*>(w.pq) + (size_t)q0 * s->np * cs;
     rp.compensated = comp;
+    rp.split = r.split;
     rp.lda = s->np;
     rp.B = s->g;
     rp.ldb = rp.N;
@@ -801,6 +836,21 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     re.K = s->ne;
     re.A = ks->pk;
     re.compensated = comp;
+    re.split = r.split;
+    if (r.packed) {
+      float* inv = reinterpret_cast<float*>(static_cast<char*>(w.g) + packed_bytes(re.N, re.K));
+      {
+        Stage sg_(s, EPHW_STAGE_MODE_ROT, st, stages);
+        EPHW_TRY(pack_columns(w.gnu, re.K, re.N, re.N, w.g, inv, st));
+      }
+      re.packed.on = true;
+      re.packed.A = ks->pkp;
+      re.packed.lda = packed_ld(nk);
+      re.packed.inv_a = 1.f / s->pack_scale;
+      re.packed.B = w.g;
+      re.packed.ldb = packed_ld(re.N);
+      re.packed.inv_b = inv;
+    }
     re.lda = s->ne;
     re.B = w.gnu;
     re.ldb = re.N;
@@ -923,6 +973,7 @@ ephw_status ephw_interpolate(ephw_kset* ks, const double* q, int64_t nq, const i
                              as_stream(stream));
   r.qb = pick_q_batch(s, ks->nk, nq, prec_kind(prec));
   r.fused = interp_fusable(s, r);
+  r.packed = interp_packable(s, ks, r);
   const size_t need = interp_layout(s, r, nullptr).bytes;
   EPHW_TRY(ws_need(s, WS_ARENA, need));
   const InterpWs w = interp_layout(s, r, static_cast<char*>(wsp(s, WS_ARENA)));
@@ -987,7 +1038,12 @@ ephw_status ephw_interpolate_noalloc(ephw_kset* ks, const double* q, int64_t nq,
   for (;;) {
     r.qb = qb;
     r.fused = interp_fusable(s, r);
+    r.packed = interp_packable(s, ks, r);
     if (interp_layout(s, r, nullptr).bytes <= kScratchBytes) break;
+    if (qb == 1 && r.packed) {   // the packed operand's padding alone may pass the scratch
+      r.packed = false;
+      if (interp_layout(s, r, nullptr).bytes <= kScratchBytes) break;
+    }
     if (qb == 1) {
       set_error("ephw_interpolate_noalloc: the call needs " + std::to_string(interp_layout(s, r, nullptr).bytes) +
                 " bytes of scratch at one q per batch, more than the " + std::to_string(kScratchBytes) +

@@ -59,6 +59,21 @@ struct BandEpilogue {
   uint32_t* status = nullptr;     // kStatusIndex for an index outside [0, nk)
 };
 
+// Packed operands of an FP32 product C = A B (pack.hip): rows of A and columns
+// of B scaled by powers of two and held as two binary16 values per real value.
+struct PackedOperands {
+  bool on = false;
+  const void* A = nullptr;
+  const void* B = nullptr;
+  int64_t lda = 0, ldb = 0;        // packed_ld of M and N
+  float inv_a = 1.f;               // 1 / the scale of A's values
+  const float* inv_b = nullptr;    // [N], 1 / the scale of each column
+};
+// rows a packed operand is padded to, its groups of eight k, its bytes
+inline int64_t packed_ld(int64_t rows) { return ceil_div(rows, 128) * 128; }
+inline int64_t packed_groups(int64_t K) { return ceil_div(K, 16) * 2; }
+inline int64_t packed_bytes(int64_t rows, int64_t K) { return packed_groups(K) * 4 * packed_ld(rows) * 16; }
+
 // All sizes, leading dimensions, strides and offsets count complex elements.
 // Operands are interleaved complex (T re, T im), T = double (prec 0) or float
 // (prec 1).  "trans" means the operand is stored transposed (A as [K][M],
@@ -82,6 +97,13 @@ struct GemmParams {
   // FP32 only: K-blocked accumulation (fresh accumulators every 32 k, block
   // sums added in FP32), the compensated form of EPHW_FP32_COMP
   bool compensated = false;
+  // FP32 only: the product may run on the 16-bit matrix cores with every value
+  // split into three bfloat16 (gemm_split.h): the error against 64 bits is no
+  // larger, the roundings are others.  Set where only complex64 values are
+  // returned; sums returned in double precision (band sums, losses,
+  // linewidths, gradients) keep the FP32 instructions and with them their
+  // digits beyond FP32's.
+  bool split = false;
   int64_t n1 = 1, n2 = 1;
   int64_t strideA1 = 0, strideA2 = 0, strideB1 = 0, strideB2 = 0, strideC1 = 0, strideC2 = 0;
   // tblock > 0: C is stored in blocks of tblock rows, each block transposed:
@@ -90,6 +112,7 @@ struct GemmParams {
   int64_t tblock = 0;
   LossEpilogue loss;
   BandEpilogue band;
+  PackedOperands packed;   // used in place of A and B where on
   int64_t batch_base = 0;  // internal: first batch index of this launch
 };
 // whether cgemm can run the fused band epilogue for this Re-sum shape (FP32,
@@ -101,6 +124,10 @@ int64_t cgemm_band_lw_groups(int nw, int nm, int64_t N);
 // workgroup tiles per batch entry of a GEMM (size of the loss partial block)
 int64_t cgemm_tiles(int prec, int64_t M, int64_t N);
 
+// whether an FP32 product of this shape runs on packed operands (both within
+// 32-bit byte offsets)
+bool cgemm_packable(int64_t M, int64_t N, int64_t K);
+
 // prec: 0 = complex128 on FP64 MFMA, 1 = complex64 on FP32 MFMA
 ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream);
 
@@ -108,7 +135,7 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream);
 // launch: `grid` workgroups take tiles of the concatenated tile lists from a
 // work queue (per-XCD ranges, then the others).  All
 // problems of one launch share a tile configuration `cfg` (0 = large,
-// 1 = small 64x64).
+// 1 = small 64x64; FP32 also 2 and 3, cgemm_grouped_split_cfg).
 struct GroupProblem {
   int64_t M = 0, N = 0, K = 0;
   const void* A = nullptr;
@@ -125,6 +152,10 @@ void cgemm_tile_shape(int prec, int cfg, int* bm, int* bn);
 // workgroups of the grouped kernel one CU holds at once (its persistent grid
 // is this times the CU count)
 int cgemm_grouped_blocks_per_cu(int prec, int cfg);
+// FP32 tile configuration of a grouped product that may be split (see
+// GemmParams::split; 2 = 128x128, 3 = 64x128 tiles) for problems of
+// start[i + 1] - start[i] rows and depth K, or -1 where they are not split
+int cgemm_grouped_split_cfg(int64_t K, int64_t lda, int64_t ldb, const int64_t* start, int64_t n);
 // whether the grouped kernel can address operands with these leading dimensions
 bool cgemm_grouped_fits(int prec, int64_t lda, int64_t ldb);
 // fills tiles_m/tiles_n/tile_base of every problem; returns the total tile count

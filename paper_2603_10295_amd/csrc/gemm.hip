@@ -23,6 +23,8 @@
 #include "gemm.h"
 #include "mfma.h"
 
+#include <type_traits>
+
 namespace ephw {
 namespace {
 
@@ -115,7 +117,8 @@ struct TileShape {
 // Wave (wm, wn) holds W for 64 k points (rows) and 64 columns, i.e. 64/Nw^2
 // whole (q, nu) blocks of Nw x Nw.  Its rows go through LDS in two halves of
 // 32 k points (the wave's own 32 x 65 complex region; the K loop's stages are
-// free by then).  Two lanes share a k point and split its 64/Nw rows (b, m')
+// free by then): put(h, wl, LDW) writes the wave's rows of half h to wl, in
+// the accumulator layout of the caller's K loop.  Two lanes share a k point and split its 64/Nw rows (b, m')
 // into four-row groups: Nw = 8, one block, rows 4s..4s+3; Nw = 4, blocks
 // 2s, 2s+1, all four rows (s = lane parity).  Per half:
 //   1. T_b[m'][:] = W_b[m'][:] V(k) for the lane's rows, written over them in
@@ -130,16 +133,14 @@ struct TileShape {
 //      the k point's rows and stored per wave column.
 // Sums run in a fixed order (shuffles and a fixed wave order), so the results
 // are deterministic.
-template <int NW>
+template <int NW, typename Put>
 __device__ __forceinline__ void band_epilogue(const TileJob<float>& j, const BandEpilogue& B, int64_t m0, int64_t n0,
-                                              typename Mfma<float>::v4 (&acc_r)[4][4],
-                                              typename Mfma<float>::v4 (&acc_i)[4][4], float* smem) {
+                                              Put put, float* smem) {
   static_assert(NW == 4 || NW == 8, "four-row groups of whole blocks");
   constexpr int TM = 64, TN = 64, HR = 32, LDW = TN + 1;
   constexpr int NW2 = NW * NW, NB = 8 / NW, MR = 4;   // blocks per lane, rows per block group
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % 2, wn = wave / 2;
-  const int lrow = lane >> 4, lcol = lane & 15;
   float* wl = smem + wave * (HR * LDW * 2);
   const int kl = lane >> 1, sb = lane & 1;               // k point within the half, lane of the pair
   const int64_t cw0 = n0 + wn * TN;                      // first column of the wave
@@ -179,17 +180,7 @@ __device__ __forceinline__ void band_epilogue(const TileJob<float>& j, const Ban
       __syncthreads();   // every wave is done with the K loop's LDS stages
     else
       wave_sync();       // this wave is done with the first half's rows
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = ii * 16 + Mfma<float>::row(lrow, v), col = jj * 16 + lcol;
-          const float re = h == 0 ? acc_r[ii][jj][v] : acc_r[2 + ii][jj][v];
-          const float im = h == 0 ? acc_i[ii][jj][v] : acc_i[2 + ii][jj][v];
-          *reinterpret_cast<float2*>(wl + 2 * (row * LDW + col)) = make_float2(re, im);
-        }
+    put(h, wl, LDW);
     wave_sync();
     const int64_t k = m0 + wm * TM + h * HR + kl;
     const bool kok = k < j.M;
@@ -420,14 +411,13 @@ __device__ __forceinline__ float fermi_fast(float x) {
   return x > 0.f ? z / (1.f + z) : 1.f / (1.f + z);
 }
 
+template <typename Put>
 __device__ __forceinline__ void band_epilogue_mfma8(const TileJob<float>& j, const BandEpilogue& B, int64_t m0,
-                                                    int64_t n0, typename Mfma<float>::v4 (&acc_r)[4][4],
-                                                    typename Mfma<float>::v4 (&acc_i)[4][4], float* smem) {
+                                                    int64_t n0, Put put, float* smem) {
   using V4 = typename Mfma<float>::v4;
   constexpr int TM = 64, TN = 64, HR = 32, LDW = TN + 1, KI = 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % 2, wn = wave / 2;
-  const int lrow = lane >> 4, lcol = lane & 15;
   const int g4 = lane >> 4, c16 = lane & 15, cc = c16 & 7;
   const bool c_lo = c16 < 8;
   const int64_t E = (int64_t)B.nm * 64;
@@ -456,17 +446,7 @@ __device__ __forceinline__ void band_epilogue_mfma8(const TileJob<float>& j, con
 #pragma unroll 1
   for (int h = 0; h < 2; ++h) {
     __syncthreads();   // the K loop's stages / the previous half's rows are done with
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = ii * 16 + Mfma<float>::row(lrow, v), col = jj * 16 + lcol;
-          const float re = h == 0 ? acc_r[ii][jj][v] : acc_r[2 + ii][jj][v];
-          const float im = h == 0 ? acc_i[ii][jj][v] : acc_i[2 + ii][jj][v];
-          *reinterpret_cast<float2*>(wl + 2 * (row * LDW + col)) = make_float2(re, im);
-        }
+    put(h, wl, LDW);
     __syncthreads();   // both modes' rows of every k point are staged
 #pragma unroll 1
     for (int it = 0; it < 16; it += KI) {
@@ -985,10 +965,28 @@ __device__ __forceinline__ void gemm_tile(const TileJob<T>& j, int64_t m0, int64
     static_assert(sizeof(T) == 4 && BM == 128 && BN == 128 && WM == 2 && WN == 2 && KBLK == 0,
                   "the band epilogue runs on the FP32 128x128 tile");
     // BANDNW: 4 or 8 the rotations on VALU; 16 the Nw = 8 rotations on MFMA
+    auto put_half = [&](auto half, float* wl, int ldw) {
+      constexpr int H = decltype(half)::value;
+#pragma unroll
+      for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            *reinterpret_cast<float2*>(wl + 2 * ((ii * 16 + Mfma<float>::row(lrow, v)) * ldw + jj * 16 + lcol)) =
+                make_float2(acc_r[2 * H + ii][jj][v], acc_i[2 * H + ii][jj][v]);
+    };
+    // (a select between the halves by h would put the accumulators in memory)
+    auto put = [&](int h, float* wl, int ldw) {
+      if (h == 0)
+        put_half(IntC<0>{}, wl, ldw);
+      else
+        put_half(IntC<1>{}, wl, ldw);
+    };
     if constexpr (BANDNW == 16)
-      band_epilogue_mfma8(j, *band, m0, n0, acc_r, acc_i, smem);
+      band_epilogue_mfma8(j, *band, m0, n0, put, smem);
     else
-      band_epilogue<BANDNW>(j, *band, m0, n0, acc_r, acc_i, smem);
+      band_epilogue<BANDNW>(j, *band, m0, n0, put, smem);
     return;
   }
   // --- epilogue: lane holds column lcol of every block, rows per Mfma<T>::row --
@@ -1217,6 +1215,8 @@ __device__ __forceinline__ TileJob<T> job_of(const GemmParams& p, int64_t b) {
   return j;
 }
 
+#include "gemm_split.h"
+
 // OCC: waves per SIMD the register allocation must leave room for
 template <typename T, int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, int KBLK, int OCC, int BANDNW = 0,
           bool FLAT = false>
@@ -1272,9 +1272,12 @@ template <typename T, int CFG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     cgemm_grouped_kernel(const GroupProblem* __restrict__ probs, int n, int64_t total, int* __restrict__ queue) {
   using G = GroupCfg<T>;
-  constexpr int BM = CFG == 0 ? G::LM : G::SM, BN = CFG == 0 ? G::LN : G::SN, BK = CFG == 0 ? G::LK : G::SK;
-  using Sh = TileShape<T, BM, BN, BK, 2, 2>;
-  __shared__ T smem[Sh::smem_elems];
+  constexpr bool kSplit = CFG >= 2;
+  using Sp = std::conditional_t<CFG == 3, Split64, Split128>;
+  constexpr int BM = kSplit ? Sp::BM : CFG == 0 ? G::LM : G::SM, BN = kSplit ? Sp::BN : CFG == 0 ? G::LN : G::SN;
+  constexpr int BK = CFG == 1 ? G::SK : G::LK;
+  using Sh = TileShape<T, kSplit ? G::LM : BM, kSplit ? G::LN : BN, BK, 2, 2>;
+  __shared__ __align__(16) T smem[kSplit ? Sp::stage_bytes / sizeof(T) : Sh::smem_elems];
   __shared__ int64_t s_next;
   int q = blockIdx.x % kXcds, tried = 0;   // used by thread 0 only
   if (threadIdx.x == 0) s_next = queue_grab(queue, total, q, tried);
@@ -1323,7 +1326,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     // condition as for a plain launch); the per-row-group buffer resources else
     constexpr int kCpc = Chunk<T>::CPC;
     constexpr bool kFlatTile = 256 % (BK / kCpc) == 0 && 256 % (BN / kCpc) == 0;
-    if (kFlatTile && P.flat)
+    if constexpr (kSplit)
+      split_tile<Sp, false, false, false, 0>(j, tm * BM, tn * BN, smem, nullptr);
+    else if (kFlatTile && P.flat)
       gemm_tile<T, BM, BN, BK, 2, 2, false, false, 0, 0, kFlatTile>(j, tm * BM, tn * BN, smem);
     else
       gemm_tile<T, BM, BN, BK, 2, 2, false, false, 0>(j, tm * BM, tn * BN, smem);
@@ -1542,6 +1547,19 @@ void plain_shape(int prec, int64_t M, int64_t N, int* bm, int* bn) {
   *bn = wide ? 224 : dn;
 }
 
+// Rows of the split tile for an FP32 output, or 0 where an FP32 tile takes
+// less time: padded work over the rate a full tile reaches (TFLOP/s of complex
+// GEMM work; the split tiles pad K to 16, the FP32 ones to 4).
+int split_rows(int64_t M, int64_t N, int64_t K) {
+  auto pad = [](int64_t n, int64_t b) { return (double)(ceil_div(n, b) * b); };
+  const double t128 = pad(M, 128) * pad(N, 128) * pad(K, 16) / 200, t64 = pad(M, 64) * pad(N, 128) * pad(K, 16) / 170;
+  int bm, bn;
+  plain_shape(1, M, N, &bm, &bn);
+  const double t32 = pad(M, bm) * pad(N, bn) * pad(K, 4) / (bm == 128 ? 130 : bn == 224 ? 110 : 85);
+  if (t32 <= t128 && t32 <= t64) return 0;
+  return t128 <= t64 ? 128 : 64;
+}
+
 int64_t cgemm_tiles(int prec, int64_t M, int64_t N) {
   int bm, bn;
   plain_shape(prec, M, N, &bm, &bn);
@@ -1549,6 +1567,11 @@ int64_t cgemm_tiles(int prec, int64_t M, int64_t N) {
 }
 
 void cgemm_tile_shape(int prec, int cfg, int* bm, int* bn) {
+  if (cfg >= 2) {
+    *bm = cfg == 3 ? Split64::BM : Split128::BM;
+    *bn = cfg == 3 ? Split64::BN : Split128::BN;
+    return;
+  }
   if (prec == 0) {
     *bm = cfg != 0 ? GroupCfg<double>::SM : GroupCfg<double>::LM;
     *bn = cfg != 0 ? GroupCfg<double>::SN : GroupCfg<double>::LN;
@@ -1565,12 +1588,27 @@ bool grouped_fits(int64_t lda, int64_t ldb) {
          lane_offsets_fit<T, G::SM, G::SN, G::SK, 2, 2, false, false>(lda, ldb);
 }
 
+int cgemm_grouped_split_cfg(int64_t K, int64_t lda, int64_t ldb, const int64_t* start, int64_t n) {
+  if (K < kSplitMinK || !split_fits(false, false, lda, ldb)) return -1;
+  // padded rows over the rate of each tile, as in split_rows
+  double r128 = 0, r64 = 0;
+  for (int64_t i = 0; i < n; ++i) {
+    const int64_t m = start[i + 1] - start[i];
+    r128 += (double)(ceil_div(m, 128) * 128);
+    r64 += (double)(ceil_div(m, 64) * 64);
+  }
+  return r128 / 200 <= r64 / 170 ? 2 : 3;
+}
+
 int cgemm_grouped_blocks_per_cu(int prec, int cfg) {
   int n = 0;
   hipError_t e;
   if (prec == 0)
     e = cfg == 0 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cgemm_grouped_kernel<double, 0>, 256, 0)
                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cgemm_grouped_kernel<double, 1>, 256, 0);
+  else if (cfg >= 2)
+    e = cfg == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cgemm_grouped_kernel<float, 2>, 256, 0)
+                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cgemm_grouped_kernel<float, 3>, 256, 0);
   else
     e = cfg == 0 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cgemm_grouped_kernel<float, 0>, 256, 0)
                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cgemm_grouped_kernel<float, 1>, 256, 0);
@@ -1614,7 +1652,13 @@ ephw_status cgemm_grouped(int prec, int cfg, const GroupProblem* d_probs, int n,
       hipLaunchKernelGGL((cgemm_grouped_kernel<double, 1>), dim3(grid), dim3(256), 0, stream, d_probs, n, total_tiles,
                          queue);
   } else {
-    if (cfg == 0)
+    if (cfg == 2)
+      hipLaunchKernelGGL((cgemm_grouped_kernel<float, 2>), dim3(grid), dim3(256), 0, stream, d_probs, n, total_tiles,
+                         queue);
+    else if (cfg == 3)
+      hipLaunchKernelGGL((cgemm_grouped_kernel<float, 3>), dim3(grid), dim3(256), 0, stream, d_probs, n, total_tiles,
+                         queue);
+    else if (cfg == 0)
       hipLaunchKernelGGL((cgemm_grouped_kernel<float, 0>), dim3(grid), dim3(256), 0, stream, d_probs, n, total_tiles,
                          queue);
     else
@@ -1649,6 +1693,11 @@ bool cgemm_band_fusable(int prec, int64_t M, int64_t N, int nw, int64_t lda, int
          lane_offsets_fit<float, 128, 128, 16, 2, 2, false, false>(lda, ldb);
 }
 
+bool cgemm_packable(int64_t M, int64_t N, int64_t K) {
+  constexpr int64_t lim = ((int64_t)1 << 32) - 65536;
+  return K >= kSplitMinK && packed_bytes(M, K) < lim && packed_bytes(N, K) < lim;
+}
+
 // the MFMA form (Nw = 8, even Nm) sums a tile's two modes into one group of
 // 128 columns; the VALU forms write one group per wave's 64 columns
 int64_t cgemm_band_lw_groups(int nw, int nm, int64_t N) {
@@ -1669,6 +1718,15 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
       set_error("cgemm: the fused band epilogue stores g in 16-byte chunks (g must be 16-byte aligned)");
       return EPHW_EINVAL;
     }
+    if (p.packed.on) {
+      if (b.nw == 8 && b.nm % 2 == 0) return launch_packed<16>(p, stream);
+      return b.nw == 8 ? launch_packed<8>(p, stream) : launch_packed<4>(p, stream);
+    }
+    if (p.split && p.K >= kSplitMinK && split_fits(false, false, p.lda, p.ldb)) {
+      if (b.nw == 8 && b.nm % 2 == 0) return launch_split<Split128, false, false, false, 16>(p, stream);
+      return b.nw == 8 ? launch_split<Split128, false, false, false, 8>(p, stream)
+                       : launch_split<Split128, false, false, false, 4>(p, stream);
+    }
     // Nw = 8 with an even mode count: every tile holds two whole modes of one
     // q, which the MFMA form of the rotations needs
     if (b.nw == 8 && b.nm % 2 == 0) return launch<float, 128, 128, 16, 2, 2, false, false, 0, 2, 16>(p, stream);
@@ -1679,6 +1737,15 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
     set_error("cgemm: K must be positive");
     return EPHW_EINVAL;
   }
+  if (p.packed.on) {
+    if (prec == 0 || p.batch != 1 || p.loss.on || !cgemm_packable(p.M, p.N, p.K)) {
+      set_error("cgemm: this product cannot take packed operands");
+      return EPHW_EUNSUPPORTED;
+    }
+    return launch_packed<0>(p, stream);
+  }
+  if (p.split && p.K >= kSplitMinK && p.compensated && prec != 0 && split_fits(p.transA, p.transB, p.lda, p.ldb))
+    return dispatch_split<Split64, true>(p, stream);   // its second accumulators fit the registers of 64x128
   if (p.compensated) {
     if (prec == 0) {
       set_error("cgemm: K-blocked accumulation is an FP32 form");
@@ -1694,6 +1761,11 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
       (prec == 0 || (p.ldb % 2 == 0 && p.strideB % 2 == 0 && p.strideB1 % 2 == 0 && p.strideB2 % 2 == 0 &&
                      !p.offB && reinterpret_cast<uintptr_t>(p.B) % 16 == 0)))
     return prec == 0 ? dispatch_skinny<double>(p, stream) : dispatch_skinny<float>(p, stream);
+  if (p.split && p.K >= kSplitMinK && prec != 0 && !p.loss.on && split_fits(p.transA, p.transB, p.lda, p.ldb)) {
+    const int rows = split_rows(p.M, p.N, p.K);
+    if (rows == 128) return dispatch_split<Split128, false>(p, stream);
+    if (rows == 64) return dispatch_split<Split64, false>(p, stream);
+  }
   int bm, bn;
   plain_shape(prec, p.M, p.N, &bm, &bn);
   // the 64x224 tile addresses a whole slab from one base; very long rows

@@ -74,6 +74,11 @@ inline ephw_status upload(X** dst, const X* src, size_t count, int64_t* owner_by
   return EPHW_OK;
 }
 
+// k points from which an FP32 set's Re sums run on packed operands: packing the
+// other operand costs about 24 bytes of traffic per value, the faster product
+// saves about 2e-14 s per value and k point, which breaks even near 270 points
+constexpr int64_t kPackMinPoints = 512;
+
 inline int prec_kind(int32_t prec) { return prec == EPHW_FP64 ? 0 : 1; }
 inline size_t csize(int kind) { return kind == 0 ? 16 : 8; }
 
@@ -150,6 +155,9 @@ struct ephw_system {
   double* c_scaled = nullptr; // c128 [nc][nm][nm] = C / sqrt(M M')
   double* ism = nullptr;      // [nm] 1/sqrt(M_kappa) per mode index
   void* g = nullptr;
+  // scale of the packed Re phases w_R e^{2 pi i k.R} (pack.hip), a power of two
+  // with |w_R| scale <= 2^14, or 0 where the weights do not allow packing
+  float pack_scale = 0.f;
   int32_t q_batch = 0;
   int32_t k_tile = 0;
   int64_t bytes = 0;
@@ -169,6 +177,7 @@ struct ephw_kset {
   int64_t bytes = 0;
   double* k = nullptr;      // [nk][3]
   void* pk = nullptr;       // T [nk][ne]
+  void* pkp = nullptr;      // packed copy of pk (FP32 sets of kPackMinPoints points or more), or NULL
   double* pkh = nullptr;    // c128 [nk][nh]
   double* eps = nullptr;    // [nk][nw]
   double* v64 = nullptr;    // c128 [nk][nw][nw]

@@ -1,0 +1,128 @@
+"""The FP32 phase sums on the 16-bit matrix cores (calls that return complex64
+values alone): the BF16 form that splits as it loads and the packed FP16 form,
+at the edges of their tiles, slabs and dispatch, against NumPy in 64 bits.
+
+Bound of an element, from the format alone: every rounding of the running sum
+is at most 2^-24 of sum |a b| (three accumulations per 16 terms in the packed
+form, six in the BF16 form, and two roundings of the inputs to complex64), and
+the parts a split leaves out are at most 2^-21 of it; a complex product has two
+real ones per part."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def bound(K, steps):
+    return 2 * ((steps * ((K + 15) // 16) + 4) * 2.0 ** -24 + 2.0 ** -21)
+
+
+@pytest.fixture(scope="module")
+def run():
+    from gpu_run import Runner
+    return Runner()
+
+
+def system(box, nw, na, seed, ws=False, rp=((0, 0, 0),)):
+    s = synth.make_system(nw, na, synth.box(box), np.asarray(rp, dtype=np.int32), [seed, 31], g_dtype=np.complex64)
+    if ws:
+        s = dataclasses.replace(s, w_e=1.0 / np.random.default_rng(seed).choice([1, 2, 3, 12], len(s.r_e)))
+    return s
+
+
+def re_sums(s, k):
+    """sum_Re w e^{ik.Re} g(Re) in 64 bits and the sum of the terms' magnitudes, [k][ka][m'][n']"""
+    ph, g = oracle.phases(k, s.r_e, s.w_e), s.g[0].reshape(len(s.r_e), -1).astype(np.complex128)
+    shape = (len(k),) + s.g.shape[2:]
+    return (ph @ g).reshape(shape), (np.abs(ph) @ (np.abs(g.real) + np.abs(g.imag))).reshape(shape)
+
+
+def wannier(run, s, k, q, prec):
+    from paper_2603_10295_amd import ephw
+    return run.interpolate(run.system(s), k, q, prec, flags=ephw.OUT_G | ephw.OUT_WANNIER, want_eps_kq=False)["g"]
+
+
+@pytest.mark.parametrize("prec", [1, 2])
+@pytest.mark.parametrize("nk,box,nw,na,ws", [
+    (40, (4, 4, 4), 5, 1, False),      # K = 64, the first that is split; 64-row tile
+    (130, (5, 13, 1), 6, 2, True),     # K = 65, weights; two row tiles, the last of two rows
+    (511, (5, 4, 4), 3, 1, False),     # K = 80, below the packed sets
+    (512, (4, 4, 4), 5, 1, False),     # the first packed set
+    (515, (5, 13, 1), 7, 2, True),     # packed: K, rows and columns ragged
+    (640, (7, 6, 5), 8, 2, False),     # packed: whole tiles
+])
+def test_re_sum(run, prec, nk, box, nw, na, ws):
+    s = system(box, nw, na, 3, ws)
+    rng = np.random.default_rng(nk)
+    k, q = rng.random((nk, 3)), np.array([[0.1, 0.2, 0.3], [0.7, 0.0, 0.4]])
+    ref, mag = re_sums(s, k)
+    got = wannier(run, s, k, q, prec)
+    for j in range(len(q)):
+        assert np.all(np.abs(got[j] - ref) <= bound(len(s.r_e), 6) * mag)
+
+
+def test_packed_columns_of_any_scale(run):
+    """Columns between 2^-100 and 2^100 keep their own relative accuracy; zero
+    columns are zero, and a column that holds an infinity or a NaN is the only
+    one that is not finite."""
+    s = system((5, 13, 1), 6, 2, 5)
+    g = s.g.copy()
+    rng = np.random.default_rng(9)
+    g *= (2.0 ** rng.integers(-100, 100, g.shape[2:])).astype(np.float32)
+    g[0, :, 1, 2, 3] = 0
+    g[0, 7, 2, 0, 1] = np.inf
+    g[0, 9, 3, 4, 4] = np.nan
+    s = dataclasses.replace(s, g=g)
+    k, q = rng.random((600, 3)), np.zeros((1, 3))
+    got = wannier(run, s, k, q, 1)[0]
+    fine = np.ones(g.shape[2:], dtype=bool)
+    fine[2, 0, 1] = fine[3, 4, 4] = False
+    clean = dataclasses.replace(s, g=np.where(np.isfinite(g), g, 0).astype(np.complex64))
+    ref, mag = re_sums(clean, k)
+    assert np.all(np.abs(got - ref)[:, fine] <= bound(65, 6) * mag[:, fine])
+    assert not np.any(got[:, 1, 2, 3])
+    assert not np.any(np.isfinite(got[:, ~fine]))
+
+
+def test_weights_beyond_the_packed_range(run):
+    """Weights spread over more than 2^8 keep the set unpacked."""
+    s = system((5, 13, 1), 4, 1, 6)
+    w = np.ones(65)
+    w[::2] = 1e-4
+    s = dataclasses.replace(s, w_e=w, g=(s.g / w[None, :, None, None, None]).astype(np.complex64))
+    k, q = np.random.default_rng(1).random((530, 3)), np.zeros((1, 3))
+    ref, mag = re_sums(s, k)
+    assert np.all(np.abs(wannier(run, s, k, q, 1)[0] - ref) <= bound(65, 6) * mag)
+
+
+@pytest.mark.parametrize("nq", [17, 64, 65, 130])
+@pytest.mark.parametrize("prec", [1, 2])
+def test_rp_sum(run, prec, nq):
+    rp = synth.box((5, 13, 1))
+    s = system((2, 1, 1), 5, 1, 8, rp=rp)
+    q = np.random.default_rng(nq).random((nq, 3))
+    ph, g = oracle.phases(q, rp), s.g.reshape(65, -1).astype(np.complex128)
+    ref, mag = ph @ g, np.abs(ph) @ (np.abs(g.real) + np.abs(g.imag))
+    got = run.phase_sum_rp(run.system(s), q, prec).reshape(nq, -1)
+    assert np.all(np.abs(got - ref) <= bound(65, 6) * mag)
+
+
+@pytest.mark.parametrize("nk", [70, 520])
+@pytest.mark.parametrize("nw,na", [(8, 2), (8, 1), (4, 1), (12, 1)])
+def test_rotated_g_agrees_with_the_fp32_instructions(run, nk, nw, na):
+    """g alone (split, packed from 512 points on) against g of a call that also
+    returns the loss (FP32 instructions), in every fused rotation form: each
+    within 1e-5 of the largest element of the other."""
+    from paper_2603_10295_amd import ephw
+    s = system((4, 4, 4), nw, na, 11, rp=synth.box((4, 4, 4)))
+    rng = np.random.default_rng(2)
+    k, q = rng.random((nk, 3)), rng.random((5, 3))
+    h = run.system(s)
+    a = run.interpolate(h, k, q, 1, flags=ephw.OUT_G, want_eps_kq=False)["g"]
+    b = run.interpolate(h, k, q, 1, flags=ephw.OUT_G | ephw.OUT_LOSS, want_eps_kq=False)["g"]
+    assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max()
