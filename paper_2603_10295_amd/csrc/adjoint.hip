@@ -514,9 +514,9 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
     EPHW_TRY(cgemm(0, g, st));
     const int64_t jw = jacobi_work_doubles((int)nm, nq);
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
-    EPHW_TRY(jacobi_eigh(static_cast<const double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
+    EPHW_TRY(jacobi_eigh(static_cast<double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
                          static_cast<double*>(wsp(s, WS_E)), jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr,
-                         s->ctx->status, st));
+                         s->ctx->status, s->ctx->max_sweeps, st));
   }
   if (omega) EPHW_TRY(abs_sqrt(static_cast<const double*>(wsp(s, WS_LAM)), omega, nq * nm, st));
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
@@ -759,9 +759,9 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
     EPHW_TRY(cgemm(0, g, st));
     const int64_t jw = jacobi_work_doubles((int)nm, nq);
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
-    EPHW_TRY(jacobi_eigh(static_cast<const double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
+    EPHW_TRY(jacobi_eigh(static_cast<double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
                          static_cast<double*>(wsp(s, WS_E)), jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr,
-                         s->ctx->status, st));
+                         s->ctx->status, s->ctx->max_sweeps, st));
   }
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
   EPHW_TRY(mode_vectors(kind, static_cast<const double*>(wsp(s, WS_E)), nq, (int)nm, s->ism, wsp(s, WS_U), st));
@@ -1146,9 +1146,9 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
     EPHW_TRY(cgemm(0, g, st));
     const int64_t jw = jacobi_work_doubles((int)nm, nq);
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
-    EPHW_TRY(jacobi_eigh(static_cast<const double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
+    EPHW_TRY(jacobi_eigh(static_cast<double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
                          static_cast<double*>(wsp(s, WS_E)), jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr,
-                         s->ctx->status, st));
+                         s->ctx->status, s->ctx->max_sweeps, st));
   }
   EPHW_TRY(ws_need(s, WS_UINV, (size_t)nq * nm * nm * cs));
   {

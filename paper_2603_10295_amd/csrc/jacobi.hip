@@ -26,6 +26,13 @@ __device__ __forceinline__ int player_at(int pos, int round, int n2) {
   return pos == 0 ? 0 : 1 + ((pos - 1 + round) % (n2 - 1));
 }
 
+// the pair of a round that holds the missing player n2 - 1 of an odd order
+__device__ __forceinline__ int missing_pair(int round, int n2) {
+  // position of player n2 - 1: 1 + (n2 - 2 - round) mod (n2 - 1)
+  const int d = n2 - 2 - round, pos = 1 + (d < 0 ? d + n2 - 1 : d);
+  return pos < n2 - 1 - pos ? pos : n2 - 1 - pos;
+}
+
 template <int NT>
 __device__ double block_sum(double v, double* red) {
   // wave reduction then across waves through LDS
@@ -37,147 +44,6 @@ __device__ double block_sum(double v, double* red) {
   double tot = 0;
   for (int w = 0; w < NT / 64; ++w) tot += red[w];
   return tot;
-}
-
-// Core solver.  Ar/Ai/Vr/Vi: n*n row-major planes (LDS or global).
-// On exit the diagonal of A holds the eigenvalues and V the eigenvectors.
-template <int NT>
-__device__ bool jacobi_core(double* Ar, double* Ai, double* Vr, double* Vi, int n, double* rc,
-                            double* rs, double* rer, double* rei, int* rp, int* rq, double* red, int max_sweeps) {
-  const int tid = threadIdx.x;
-  const int n2 = n + (n & 1);
-  const int npairs = n2 / 2;
-  for (int e = tid; e < n * n; e += NT) {
-    Vr[e] = (e / n == e % n) ? 1.0 : 0.0;
-    Vi[e] = 0.0;
-  }
-  __syncthreads();
-  bool converged = (n <= 1);
-  for (int sweep = 0; sweep < max_sweeps && !converged; ++sweep) {
-    double off = 0.0, tot = 0.0;
-    for (int e = tid; e < n * n; e += NT) {
-      const double v = Ar[e] * Ar[e] + Ai[e] * Ai[e];
-      tot += v;
-      if (e / n != e % n) off += v;
-    }
-    off = block_sum<NT>(off, red);
-    tot = block_sum<NT>(tot, red);
-    if (off <= kOffTol2 * tot) {
-      converged = true;
-      break;
-    }
-    for (int round = 0; round < n2 - 1; ++round) {
-      if (tid < npairs) {
-        const int a = player_at(tid, round, n2), b = player_at(n2 - 1 - tid, round, n2);
-        const int p = a < b ? a : b, q = a < b ? b : a;
-        int pp = -1;
-        double c = 1.0, s = 0.0, er = 1.0, ei = 0.0;
-        if (q < n) {
-          const double br = Ar[p * n + q], bi = Ai[p * n + q];
-          const double bm = hypot(br, bi);
-          if (bm > 0.0) {
-            const double tau = (Ar[q * n + q] - Ar[p * n + p]) / (2.0 * bm);
-            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + t * t);
-            s = t * c;
-            er = br / bm;
-            ei = bi / bm;
-            pp = p;
-          }
-        }
-        rc[tid] = c;
-        rs[tid] = s;
-        rer[tid] = er;
-        rei[tid] = ei;
-        rp[tid] = pp;
-        rq[tid] = q;
-      }
-      __syncthreads();
-      // columns: A <- A J and V <- V J
-      for (int w = tid; w < n * npairs; w += NT) {
-        const int row = w / npairs, k = w % npairs;
-        const int p = rp[k];
-        if (p < 0) continue;
-        const int q = rq[k];
-        const double c = rc[k], s = rs[k], er = rer[k], ei = rei[k];
-        // x' = c x - s conj(e) y ; y' = s e x + c y
-        {
-          const double xr = Ar[row * n + p], xi = Ai[row * n + p];
-          const double yr = Ar[row * n + q], yi = Ai[row * n + q];
-          Ar[row * n + p] = c * xr - s * (er * yr + ei * yi);
-          Ai[row * n + p] = c * xi - s * (er * yi - ei * yr);
-          Ar[row * n + q] = s * (er * xr - ei * xi) + c * yr;
-          Ai[row * n + q] = s * (er * xi + ei * xr) + c * yi;
-        }
-        {
-          const double xr = Vr[row * n + p], xi = Vi[row * n + p];
-          const double yr = Vr[row * n + q], yi = Vi[row * n + q];
-          Vr[row * n + p] = c * xr - s * (er * yr + ei * yi);
-          Vi[row * n + p] = c * xi - s * (er * yi - ei * yr);
-          Vr[row * n + q] = s * (er * xr - ei * xi) + c * yr;
-          Vi[row * n + q] = s * (er * xi + ei * xr) + c * yi;
-        }
-      }
-      __syncthreads();
-      // rows: A <- J^H A ; x' = c x - s e y ; y' = s conj(e) x + c y
-      for (int w = tid; w < npairs * n; w += NT) {
-        const int k = w / n, col = w % n;
-        const int p = rp[k];
-        if (p < 0) continue;
-        const int q = rq[k];
-        const double c = rc[k], s = rs[k], er = rer[k], ei = rei[k];
-        const double xr = Ar[p * n + col], xi = Ai[p * n + col];
-        const double yr = Ar[q * n + col], yi = Ai[q * n + col];
-        Ar[p * n + col] = c * xr - s * (er * yr - ei * yi);
-        Ai[p * n + col] = c * xi - s * (er * yi + ei * yr);
-        Ar[q * n + col] = s * (er * xr + ei * xi) + c * yr;
-        Ai[q * n + col] = s * (er * xi - ei * xr) + c * yi;
-      }
-      __syncthreads();
-    }
-  }
-  return converged;
-}
-
-// Sort ascending, fix each column's phase, write eps and V (c128).
-template <int NT>
-__device__ void jacobi_finish(const double* Ar, const double* Vr, const double* Vi, int n, int* perm,
-                              double* phr, double* phi, double* eps_out, double* V_out) {
-  const int tid = threadIdx.x;
-  for (int i = tid; i < n; i += NT) {
-    const double li = Ar[i * n + i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const double lj = Ar[j * n + j];
-      rank += (lj < li) || (lj == li && j < i);
-    }
-    perm[rank] = i;
-  }
-  __syncthreads();
-  for (int c = tid; c < n; c += NT) {
-    const int src = perm[c];
-    eps_out[c] = Ar[src * n + src];
-    double best = -1.0, br = 1.0, bi = 0.0;
-    for (int r = 0; r < n; ++r) {
-      const double vr = Vr[r * n + src], vi = Vi[r * n + src];
-      const double m = vr * vr + vi * vi;
-      if (m > best) {
-        best = m;
-        br = vr;
-        bi = vi;
-      }
-    }
-    const double mag = sqrt(best);
-    phr[c] = mag > 0 ? br / mag : 1.0;   // multiply by conj(v_max)/|v_max|
-    phi[c] = mag > 0 ? -bi / mag : 0.0;
-  }
-  __syncthreads();
-  for (int e = tid; e < n * n; e += NT) {
-    const int r = e / n, c = e % n, src = perm[c];
-    const double vr = Vr[r * n + src], vi = Vi[r * n + src];
-    V_out[2 * e] = vr * phr[c] - vi * phi[c];
-    V_out[2 * e + 1] = vr * phi[c] + vi * phr[c];
-  }
 }
 
 constexpr int kSmallN = 32;
@@ -929,41 +795,269 @@ struct SmallTable {
 };
 using Small = SmallTable<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16>;
 
-// one workgroup of 16 waves per large matrix: the rounds stream A and V
-// through the caches (640 KB each at n = 200), so the more loads in flight
-// the better; the rotation parameters stay in LDS
+// ---------------------------------------------------------------------------
+// Large solves (n > 32).  A stays in the caches, V does not travel with it:
+// the rotations of a round depend on A alone, so one workgroup per matrix runs
+// the rounds on A and logs their parameters (jacobi_rounds_kernel), and the
+// rows of V, each independent of the others, replay the log on as many
+// wavefronts as there are rows to share out, in LDS (jacobi_replay_kernel).
+// The two kernels alternate, kLogSweeps sweeps at a time, until the sweep
+// limit; after convergence they return at once.
+//
+// Per round J_i^H A J_j touches only the 2x2 block (pair i, pair j), so a
+// thread loads a block's four elements, applies the column and then the row
+// rotation, and stores them: one pass and one barrier where columns and rows
+// of A would be two, and neighbouring lanes touch neighbouring elements (the
+// players of consecutive pairs are consecutive).  A block is 4 + 4 accesses of
+// 16 bytes, 720 KB a round at n = 150 through one CU's 64 bytes a cycle.
+// n = 150, 8 matrices: 44.4 ms with one workgroup per matrix doing both
+// passes on A and V (integer divisions per element, planes of re and im) ->
+// 12 ms, 10 of them the rounds (7.4 us each, 4.7 of it the traffic above).
+// ---------------------------------------------------------------------------
 constexpr int kLargeThreads = 1024;
+constexpr int kLogSweeps = 2;       // the log takes the 32 n^2 bytes per matrix of jacobi_work_doubles
+constexpr int kReplayRows = 4;      // rows of V per wavefront
 
+struct LargeRot {
+  double c, s, er, ei;
+};
+
+// The rotation of two complex values in place, every rounding written out:
+// complex64 results downstream (gradients) see the last bits of V, so both
+// kernels, and any later form of them, round alike.
+// columns: x' = c x - s conj(e) y ; y' = s e x + c y
+__device__ __forceinline__ void rotate_columns(const LargeRot& r, double2& x, double2& y) {
+  const double xr = x.x, xi = x.y, yr = y.x, yi = y.y;
+  x.x = fma(r.c, xr, -(r.s * fma(r.er, yr, r.ei * yi)));
+  x.y = fma(r.c, xi, -(r.s * fma(r.er, yi, -(r.ei * yr))));
+  y.x = fma(r.c, yr, r.s * fma(r.er, xr, -(r.ei * xi)));
+  y.y = fma(r.s, fma(r.ei, xr, r.er * xi), r.c * yi);
+}
+// rows: x' = c x - s e y ; y' = s conj(e) x + c y
+__device__ __forceinline__ void rotate_rows(const LargeRot& r, double2& x, double2& y) {
+  const double xr = x.x, xi = x.y, yr = y.x, yi = y.y;
+  x.x = fma(r.c, xr, -(r.s * fma(r.er, yr, -(r.ei * yi))));
+  x.y = fma(r.c, xi, -(r.s * fma(r.ei, yr, r.er * yi)));
+  y.x = fma(r.c, yr, r.s * fma(r.er, xr, r.ei * xi));
+  y.y = fma(r.s, fma(r.er, xi, -(r.ei * xr)), r.c * yi);
+}
+
+// number of pairs with two real players in a round, and the log's stride
+__host__ __device__ inline int large_pairs(int n) { return n / 2; }
+
+// state[0]: converged; state[1]: rounds in the log; state[2]: sweeps done
 __global__ void __launch_bounds__(kLargeThreads)
-    jacobi_large_kernel(const double* __restrict__ H, int n, double* __restrict__ eps,
-                        double* __restrict__ V, double* __restrict__ work, uint32_t* status) {
-  __shared__ double rc[128], rs[128], rer[128], rei[128], phr[256], phi[256], red[kLargeThreads / 64];
-  __shared__ int rp[128], rq[128], perm[256];
-  const int64_t b = blockIdx.x;
-  const int64_t nn = (int64_t)n * n;
-  double* Ar = work + 4 * nn * blockIdx.x;
-  double* Ai = Ar + nn;
-  double* Vr = Ai + nn;
-  double* Vi = Vr + nn;
-  const double* h = H + 2 * b * nn;
-  for (int64_t e = threadIdx.x; e < nn; e += kLargeThreads) {
-    Ar[e] = h[2 * e];
-    Ai[e] = h[2 * e + 1];
+    jacobi_rounds_kernel(double2* __restrict__ H, int n, LargeRot* __restrict__ log, int* __restrict__ state,
+                         const uint32_t* __restrict__ status, int phase) {
+  __shared__ LargeRot prm[128];
+  __shared__ int ip[128], iq[128];   // players of a pair, iq = -1 for the pair with the missing player
+  __shared__ double red[kLargeThreads / 64];
+  const int tid = threadIdx.x;
+  int* st = state + 3 * blockIdx.x;
+  if (phase > 0 && st[0]) {
+    if (tid == 0) st[1] = 0;
+    return;
+  }
+  double2* A = H + (int64_t)blockIdx.x * n * n;
+  const int n2 = n + (n & 1), np = n2 / 2, full = large_pairs(n);
+  LargeRot* lg = log + (int64_t)blockIdx.x * kLogSweeps * (n2 - 1) * full;
+  const int max_sweeps = sweep_limit(status);
+  int sweep = phase * kLogSweeps, rounds = 0;
+  bool converged = n <= 1;
+  for (int l = 0; l < kLogSweeps && sweep < max_sweeps && !converged; ++l, ++sweep) {
+    double off = 0.0, tot = 0.0;
+    for (int e = tid; e < n * n; e += kLargeThreads) {
+      const double2 a = A[e];
+      const double v = a.x * a.x + a.y * a.y;
+      tot += v;
+      if (e / n != e % n) off += v;
+    }
+    off = block_sum<kLargeThreads>(off, red);
+    tot = block_sum<kLargeThreads>(tot, red);
+    if (off <= kOffTol2 * tot) {
+      converged = true;
+      break;
+    }
+    for (int round = 0; round < n2 - 1; ++round) {
+      if (tid < np) {
+        const int a = player_at(tid, round, n2), b = player_at(n2 - 1 - tid, round, n2);
+        const int p = a < b ? a : b, q = a < b ? b : a;
+        LargeRot r = {1.0, 0.0, 1.0, 0.0};
+        if (q < n) {
+          const double br = A[p * n + q].x, bi = A[p * n + q].y;
+          const double bm = hypot(br, bi);
+          if (bm > 0.0) {
+            const double tau = (A[q * n + q].x - A[p * n + p].x) / (2.0 * bm);
+            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+            r.c = 1.0 / sqrt(1.0 + t * t);
+            r.s = t * r.c;
+            r.er = br / bm;
+            r.ei = bi / bm;
+          }
+        }
+        prm[tid] = r;
+        ip[tid] = p;
+        iq[tid] = q < n ? q : -1;
+        // odd n: pair 0 is always player 0's, so the pair of the missing player
+        // moves; its entry is left out (the pairs after it move up by one)
+        const int miss = n & 1 ? missing_pair(round, n2) : np;
+        if (tid != miss) lg[(int64_t)rounds * full + tid - (tid > miss ? 1 : 0)] = r;
+      }
+      __syncthreads();
+      int i = tid / np, j = tid - i * np;
+      const int di = kLargeThreads / np, dj = kLargeThreads - di * np;
+      while (i < np) {
+        const int pi = ip[i], qi = iq[i], pj = ip[j], qj = iq[j];
+        const bool hi = qi >= 0, hj = qj >= 0;
+        double2* rowp = A + pi * n;
+        double2* rowq = A + (hi ? qi : pi) * n;
+        const int cq = hj ? qj : pj;
+        double2 x[2] = {rowp[pj], rowq[pj]}, y[2] = {rowp[cq], rowq[cq]};
+        const LargeRot rj = prm[j], ri = prm[i];
+        rotate_columns(rj, x[0], y[0]);
+        rotate_columns(rj, x[1], y[1]);
+        rotate_rows(ri, x[0], x[1]);
+        rotate_rows(ri, y[0], y[1]);
+        rowp[pj] = x[0];
+        if (hj) rowp[qj] = y[0];
+        if (hi) rowq[pj] = x[1];
+        if (hi && hj) rowq[qj] = y[1];
+        i += di;
+        j += dj;
+        if (j >= np) {
+          j -= np;
+          ++i;
+        }
+      }
+      ++rounds;
+      __syncthreads();
+    }
+  }
+  if (tid == 0) {
+    st[0] = converged;
+    st[1] = rounds;
+    st[2] = sweep;
+  }
+}
+
+// V <- V J for the logged rounds: a wavefront owns kReplayRows rows of V in its
+// own LDS slice, its lanes share the pairs of a round, so rounds are separated
+// by wave-level waits only; the next round's parameters are loaded meanwhile.
+__global__ void __launch_bounds__(256)
+    jacobi_replay_kernel(double2* __restrict__ V, int n, const LargeRot* __restrict__ log,
+                         const int* __restrict__ state, int phase) {
+  extern __shared__ double2 replay_rows[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = blockIdx.y, row0 = (blockIdx.x * 4 + wave) * kReplayRows;
+  const int rounds = state[3 * b + 1];
+  if (row0 >= n || (rounds == 0 && phase > 0)) return;
+  const int n2 = n + (n & 1), full = large_pairs(n);
+  const LargeRot* lg = log + (int64_t)b * kLogSweeps * (n2 - 1) * full;
+  double2* vb = V + (int64_t)b * n * n;
+  double2* buf = replay_rows + wave * kReplayRows * n;
+  const int rows = n - row0 < kReplayRows ? n - row0 : kReplayRows;
+  for (int r = 0; r < kReplayRows; ++r)
+    for (int c = lane; c < n; c += 64)
+      buf[r * n + c] = phase > 0 && r < rows ? vb[(row0 + r) * n + c] : make_double2(row0 + r == c ? 1.0 : 0.0, 0.0);
+  wave_sync();
+  const LargeRot idle = {1.0, 0.0, 1.0, 0.0};
+  LargeRot next[2];
+  int round = 0;   // within the sweep
+  auto fetch = [&](int t, int rd, int u) {
+    const int k = lane + 64 * u;
+    const int miss = n & 1 ? missing_pair(rd, n2) : n2;
+    return t < rounds && k < n2 / 2 && k != miss ? lg[(int64_t)t * full + k - (k > miss ? 1 : 0)] : idle;
+  };
+#pragma unroll
+  for (int u = 0; u < 2; ++u) next[u] = fetch(0, 0, u);
+  for (int t = 0; t < rounds; ++t) {
+    const int rn = round + 1 == n2 - 1 ? 0 : round + 1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const LargeRot w = next[u];
+      next[u] = fetch(t + 1, rn, u);
+      const int k = lane + 64 * u;
+      if (k >= n2 / 2) continue;
+      const int pa = player_at(k, round, n2), pb = player_at(n2 - 1 - k, round, n2);
+      const int p = pa < pb ? pa : pb, q = pa < pb ? pb : pa;
+      if (q >= n) continue;
+#pragma unroll
+      for (int r = 0; r < kReplayRows; ++r) {
+        double2 x = buf[r * n + p], y = buf[r * n + q];
+        rotate_columns(w, x, y);
+        buf[r * n + p] = x;
+        buf[r * n + q] = y;
+      }
+    }
+    round = rn;
+    wave_sync();
+  }
+  for (int r = 0; r < rows; ++r)
+    for (int c = lane; c < n; c += 64) vb[(row0 + r) * n + c] = buf[r * n + c];
+}
+
+// Sort ascending, fix each column's phase: eps from the diagonal of A, the
+// columns of V permuted and scaled in place, a row at a time.
+__global__ void __launch_bounds__(kLargeThreads)
+    jacobi_finish_kernel(const double2* __restrict__ H, int n, double* __restrict__ eps, double2* __restrict__ V,
+                         const int* __restrict__ state, uint32_t* status) {
+  __shared__ int perm[256];
+  __shared__ double2 ph[256], row[kLargeThreads / 64][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double2* A = H + (int64_t)blockIdx.x * n * n;
+  double2* vb = V + (int64_t)blockIdx.x * n * n;
+  double* eo = eps + (int64_t)blockIdx.x * n;
+  if (tid == 0 && !state[3 * blockIdx.x]) atomicOr(status, kStatusNoConv);
+  for (int i = tid; i < n; i += kLargeThreads) {
+    const double li = A[i * n + i].x;
+    int rank = 0;
+    for (int j = 0; j < n; ++j) {
+      const double lj = A[j * n + j].x;
+      rank += (lj < li) || (lj == li && j < i);
+    }
+    perm[rank] = i;
   }
   __syncthreads();
-  const bool ok = jacobi_core<kLargeThreads>(Ar, Ai, Vr, Vi, n, rc, rs, rer, rei, rp, rq, red, sweep_limit(status));
-  if (!ok && threadIdx.x == 0) atomicOr(status, kStatusNoConv);
-  jacobi_finish<kLargeThreads>(Ar, Vr, Vi, n, perm, phr, phi, eps + b * n, V + 2 * b * nn);
+  for (int c = tid; c < n; c += kLargeThreads) {
+    const int src = perm[c];
+    eo[c] = A[src * n + src].x;
+    double best = -1.0, br = 1.0, bi = 0.0;
+    for (int r = 0; r < n; ++r) {
+      const double vr = vb[r * n + src].x, vi = vb[r * n + src].y;
+      const double m = vr * vr + vi * vi;
+      if (m > best) {
+        best = m;
+        br = vr;
+        bi = vi;
+      }
+    }
+    const double mag = sqrt(best);
+    ph[c] = mag > 0 ? make_double2(br / mag, -bi / mag) : make_double2(1.0, 0.0);   // conj(v_max)/|v_max|
+  }
+  __syncthreads();
+  for (int r = wave; r < n; r += kLargeThreads / 64) {
+    for (int c = lane; c < n; c += 64) row[wave][c] = vb[r * n + c];
+    wave_sync();
+    for (int c = lane; c < n; c += 64) {
+      const double vr = row[wave][perm[c]].x, vi = row[wave][perm[c]].y;
+      const double fr = ph[c].x, fi = ph[c].y;
+      vb[r * n + c] = make_double2(vr * fr - vi * fi, vr * fi + vi * fr);
+    }
+    wave_sync();
+  }
 }
 
 constexpr int64_t kLargeChunk = 1024;  // matrices per large-n launch (bounds the workspace)
+
+// doubles of one matrix's log: kLogSweeps sweeps of rounds of n / 2 rotations
+inline int64_t log_doubles(int n) { return (int64_t)4 * kLogSweeps * (n + (n & 1) - 1) * large_pairs(n); }
 
 }  // namespace
 
 int64_t jacobi_work_doubles(int n, int64_t batch) {
   if (n <= kSmallN) return 0;
   const int64_t chunk = batch < kLargeChunk ? batch : kLargeChunk;
-  return 4 * (int64_t)n * n * chunk;
+  return log_doubles(n) * chunk + (3 * chunk + 1) / 2;
 }
 
 ephw_status jacobi_eigh_grouped(const EighJob* d_jobs, int njobs, int64_t total, int max_n, uint32_t* status,
@@ -985,8 +1079,8 @@ ephw_status jacobi_eigh_grouped(const EighJob* d_jobs, int njobs, int64_t total,
   return EPHW_OK;
 }
 
-ephw_status jacobi_eigh(const double* H, int64_t batch, int n, double* eps, double* V, double* work,
-                        uint32_t* status, hipStream_t s, double off_tol2) {
+ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                        int max_sweeps, hipStream_t s, double off_tol2) {
   if (batch <= 0) return EPHW_OK;
   if (!(off_tol2 > 0.0) || off_tol2 < kOffTol2) off_tol2 = kOffTol2;
   if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
@@ -1013,11 +1107,24 @@ ephw_status jacobi_eigh(const double* H, int64_t batch, int n, double* eps, doub
     set_error("jacobi_eigh: large matrices need a workspace");
     return EPHW_EINVAL;
   }
+  const size_t rows_lds = (size_t)4 * kReplayRows * n * sizeof(double2);
   for (int64_t b0 = 0; b0 < batch; b0 += kLargeChunk) {
     const int64_t nb = (batch - b0) < kLargeChunk ? (batch - b0) : kLargeChunk;
-    hipLaunchKernelGGL(jacobi_large_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s,
-                       H + 2 * b0 * (int64_t)n * n, n, eps + b0 * n, V + 2 * b0 * (int64_t)n * n,
-                       work, status);
+    double2* h = reinterpret_cast<double2*>(H) + b0 * n * n;
+    double2* v = reinterpret_cast<double2*>(V) + b0 * n * n;
+    LargeRot* log = reinterpret_cast<LargeRot*>(work);
+    int* state = reinterpret_cast<int*>(work + log_doubles(n) * nb);
+    const int phases = max_sweeps > kLogSweeps ? (max_sweeps + kLogSweeps - 1) / kLogSweeps : 1;
+    for (int ph = 0; ph < phases; ++ph) {
+      hipLaunchKernelGGL(jacobi_rounds_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, log, state, status,
+                         ph);
+      EPHW_CHECK_LAUNCH();
+      hipLaunchKernelGGL(jacobi_replay_kernel, dim3((unsigned)ceil_div(n, 4 * kReplayRows), (unsigned)nb), dim3(256),
+                         rows_lds, s, v, n, log, state, ph);
+      EPHW_CHECK_LAUNCH();
+    }
+    hipLaunchKernelGGL(jacobi_finish_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, eps + b0 * n, v,
+                       state, status);
     EPHW_CHECK_LAUNCH();
   }
   return EPHW_OK;

@@ -17,8 +17,10 @@ ephw_status phase_matrix(int prec, const double* pts, int64_t n, const int32_t* 
 int64_t jacobi_work_doubles(int n, int64_t batch);
 // off_tol2: convergence when (off-diagonal norm / total norm)^2 <= off_tol2
 // (not below 1e-28, the FP64 default; n <= 32 only, larger orders keep 1e-28)
-ephw_status jacobi_eigh(const double* H, int64_t batch, int n, double* eps, double* V, double* work,
-                        uint32_t* status, hipStream_t s, double off_tol2 = 1e-28);
+// H is overwritten where n > 32.  max_sweeps: the sweep limit the status words
+// hold, from which the host counts the launches of the large solves.
+ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                        int max_sweeps, hipStream_t s, double off_tol2 = 1e-28);
 
 // many small (n <= 32) eigensolves of different orders in one launch;
 // matrix m of the launch belongs to the job with the largest block_base <= m
