@@ -798,11 +798,11 @@ using Small = SmallTable<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16>;
 // ---------------------------------------------------------------------------
 // Large solves (n > 32).  A stays in the caches, V does not travel with it:
 // the rotations of a round depend on A alone, so one workgroup per matrix runs
-// the rounds on A and logs their parameters (jacobi_rounds_kernel), and the
-// rows of V, each independent of the others, replay the log on as many
-// wavefronts as there are rows to share out, in LDS (jacobi_replay_kernel).
-// The two kernels alternate, kLogSweeps sweeps at a time, until the sweep
-// limit; after convergence they return at once.
+// a sweep of rounds on A and logs their parameters, and the rows of V, each
+// independent of the others, replay the log of the sweep before on as many
+// wavefronts as there are rows to share out, in LDS, on the CUs the first
+// workgroups leave idle.  One launch per sweep holds both (two logs in turn),
+// up to the sweep limit; after convergence the launches return at once.
 //
 // Per round J_i^H A J_j touches only the 2x2 block (pair i, pair j), so a
 // thread loads a block's four elements, applies the column and then the row
@@ -812,11 +812,11 @@ using Small = SmallTable<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16>;
 // 16 bytes, 720 KB a round at n = 150 through one CU's 64 bytes a cycle.
 // n = 150, 8 matrices: 44.4 ms with one workgroup per matrix doing both
 // passes on A and V (integer divisions per element, planes of re and im) ->
-// 12 ms, 10 of them the rounds (7.4 us each, 4.7 of it the traffic above).
+// 10 ms (7.2 us a round, 4.7 of it the traffic above).  Rows of A kept in LDS
+// (4 in 10 at n = 150) and parameters picked up from LDS instead of A: 10.7.
 // ---------------------------------------------------------------------------
 constexpr int kLargeThreads = 1024;
-constexpr int kLogSweeps = 2;       // the log takes the 32 n^2 bytes per matrix of jacobi_work_doubles
-constexpr int kReplayRows = 4;      // rows of V per wavefront
+constexpr int kReplayRows = 2;      // rows of V per wavefront
 
 struct LargeRot {
   double c, s, er, ei;
@@ -845,39 +845,37 @@ __device__ __forceinline__ void rotate_rows(const LargeRot& r, double2& x, doubl
 // number of pairs with two real players in a round, and the log's stride
 __host__ __device__ inline int large_pairs(int n) { return n / 2; }
 
-// state[0]: converged; state[1]: rounds in the log; state[2]: sweeps done
-__global__ void __launch_bounds__(kLargeThreads)
-    jacobi_rounds_kernel(double2* __restrict__ H, int n, LargeRot* __restrict__ log, int* __restrict__ state,
-                         const uint32_t* __restrict__ status, int phase) {
+// Per matrix, state[0]: converged; state[1 + parity]: rounds in the log that
+// the sweep of that parity wrote.  Sweep number `sweep` of matrix b.
+__device__ __forceinline__ void jacobi_sweep(double2* __restrict__ H, int n, LargeRot* __restrict__ log,
+                                             int* __restrict__ state, const uint32_t* __restrict__ status, int sweep,
+                                             int b) {
   __shared__ LargeRot prm[128];
   __shared__ int ip[128], iq[128];   // players of a pair, iq = -1 for the pair with the missing player
   __shared__ double red[kLargeThreads / 64];
   const int tid = threadIdx.x;
-  int* st = state + 3 * blockIdx.x;
-  if (phase > 0 && st[0]) {
-    if (tid == 0) st[1] = 0;
+  int* st = state + 3 * b;
+  if ((sweep > 0 && st[0]) || sweep >= sweep_limit(status)) {
+    if (tid == 0) {
+      if (sweep == 0) st[0] = 0;
+      st[1 + (sweep & 1)] = 0;
+    }
     return;
   }
-  double2* A = H + (int64_t)blockIdx.x * n * n;
+  double2* A = H + (int64_t)b * n * n;
   const int n2 = n + (n & 1), np = n2 / 2, full = large_pairs(n);
-  LargeRot* lg = log + (int64_t)blockIdx.x * kLogSweeps * (n2 - 1) * full;
-  const int max_sweeps = sweep_limit(status);
-  int sweep = phase * kLogSweeps, rounds = 0;
-  bool converged = n <= 1;
-  for (int l = 0; l < kLogSweeps && sweep < max_sweeps && !converged; ++l, ++sweep) {
-    double off = 0.0, tot = 0.0;
-    for (int e = tid; e < n * n; e += kLargeThreads) {
-      const double2 a = A[e];
-      const double v = a.x * a.x + a.y * a.y;
-      tot += v;
-      if (e / n != e % n) off += v;
-    }
-    off = block_sum<kLargeThreads>(off, red);
-    tot = block_sum<kLargeThreads>(tot, red);
-    if (off <= kOffTol2 * tot) {
-      converged = true;
-      break;
-    }
+  LargeRot* lg = log + ((int64_t)b * 2 + (sweep & 1)) * (n2 - 1) * full;
+  double off = 0.0, tot = 0.0;
+  for (int e = tid; e < n * n; e += kLargeThreads) {
+    const double2 a = A[e];
+    const double v = a.x * a.x + a.y * a.y;
+    tot += v;
+    if (e / n != e % n) off += v;
+  }
+  off = block_sum<kLargeThreads>(off, red);
+  tot = block_sum<kLargeThreads>(tot, red);
+  const bool converged = off <= kOffTol2 * tot;
+  if (!converged) {
     for (int round = 0; round < n2 - 1; ++round) {
       if (tid < np) {
         const int a = player_at(tid, round, n2), b = player_at(n2 - 1 - tid, round, n2);
@@ -901,7 +899,7 @@ __global__ void __launch_bounds__(kLargeThreads)
         // odd n: pair 0 is always player 0's, so the pair of the missing player
         // moves; its entry is left out (the pairs after it move up by one)
         const int miss = n & 1 ? missing_pair(round, n2) : np;
-        if (tid != miss) lg[(int64_t)rounds * full + tid - (tid > miss ? 1 : 0)] = r;
+        if (tid != miss) lg[(int64_t)round * full + tid - (tid > miss ? 1 : 0)] = r;
       }
       __syncthreads();
       int i = tid / np, j = tid - i * np;
@@ -929,56 +927,51 @@ __global__ void __launch_bounds__(kLargeThreads)
           ++i;
         }
       }
-      ++rounds;
       __syncthreads();
     }
   }
   if (tid == 0) {
     st[0] = converged;
-    st[1] = rounds;
-    st[2] = sweep;
+    st[1 + (sweep & 1)] = converged ? 0 : n2 - 1;
   }
 }
 
 // V <- V J for the logged rounds: a wavefront owns kReplayRows rows of V in its
 // own LDS slice, its lanes share the pairs of a round, so rounds are separated
 // by wave-level waits only; the next round's parameters are loaded meanwhile.
-__global__ void __launch_bounds__(256)
-    jacobi_replay_kernel(double2* __restrict__ V, int n, const LargeRot* __restrict__ log,
-                         const int* __restrict__ state, int phase) {
-  extern __shared__ double2 replay_rows[];
+__device__ __forceinline__ void jacobi_replay(double2* __restrict__ V, int n, const LargeRot* __restrict__ log,
+                                              const int* __restrict__ state, int sweep, int b, int part,
+                                              double2* replay_rows) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b = blockIdx.y, row0 = (blockIdx.x * 4 + wave) * kReplayRows;
-  const int rounds = state[3 * b + 1];
-  if (row0 >= n || (rounds == 0 && phase > 0)) return;
+  const int row0 = (part * (kLargeThreads / 64) + wave) * kReplayRows;
+  const int rounds = state[3 * b + 1 + (sweep & 1)];
+  if (row0 >= n || (rounds == 0 && sweep > 0)) return;
   const int n2 = n + (n & 1), full = large_pairs(n);
-  const LargeRot* lg = log + (int64_t)b * kLogSweeps * (n2 - 1) * full;
+  const LargeRot* lg = log + ((int64_t)b * 2 + (sweep & 1)) * (n2 - 1) * full;
   double2* vb = V + (int64_t)b * n * n;
   double2* buf = replay_rows + wave * kReplayRows * n;
   const int rows = n - row0 < kReplayRows ? n - row0 : kReplayRows;
   for (int r = 0; r < kReplayRows; ++r)
     for (int c = lane; c < n; c += 64)
-      buf[r * n + c] = phase > 0 && r < rows ? vb[(row0 + r) * n + c] : make_double2(row0 + r == c ? 1.0 : 0.0, 0.0);
+      buf[r * n + c] = sweep > 0 && r < rows ? vb[(row0 + r) * n + c] : make_double2(row0 + r == c ? 1.0 : 0.0, 0.0);
   wave_sync();
   const LargeRot idle = {1.0, 0.0, 1.0, 0.0};
   LargeRot next[2];
-  int round = 0;   // within the sweep
-  auto fetch = [&](int t, int rd, int u) {
+  auto fetch = [&](int t, int u) {
     const int k = lane + 64 * u;
-    const int miss = n & 1 ? missing_pair(rd, n2) : n2;
+    const int miss = n & 1 ? missing_pair(t, n2) : n2;
     return t < rounds && k < n2 / 2 && k != miss ? lg[(int64_t)t * full + k - (k > miss ? 1 : 0)] : idle;
   };
 #pragma unroll
-  for (int u = 0; u < 2; ++u) next[u] = fetch(0, 0, u);
+  for (int u = 0; u < 2; ++u) next[u] = fetch(0, u);
   for (int t = 0; t < rounds; ++t) {
-    const int rn = round + 1 == n2 - 1 ? 0 : round + 1;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const LargeRot w = next[u];
-      next[u] = fetch(t + 1, rn, u);
+      next[u] = fetch(t + 1, u);
       const int k = lane + 64 * u;
       if (k >= n2 / 2) continue;
-      const int pa = player_at(k, round, n2), pb = player_at(n2 - 1 - k, round, n2);
+      const int pa = player_at(k, t, n2), pb = player_at(n2 - 1 - k, t, n2);
       const int p = pa < pb ? pa : pb, q = pa < pb ? pb : pa;
       if (q >= n) continue;
 #pragma unroll
@@ -989,11 +982,24 @@ __global__ void __launch_bounds__(256)
         buf[r * n + q] = y;
       }
     }
-    round = rn;
     wave_sync();
   }
   for (int r = 0; r < rows; ++r)
     for (int c = lane; c < n; c += 64) vb[(row0 + r) * n + c] = buf[r * n + c];
+}
+
+// Workgroups 0 .. nb - 1 run sweep `sweep` on A, the others replay the sweep
+// before it, `parts` of them per matrix.
+__global__ void __launch_bounds__(kLargeThreads)
+    jacobi_sweep_kernel(double2* __restrict__ H, double2* __restrict__ V, int n, int nb, int parts,
+                        LargeRot* __restrict__ log, int* __restrict__ state, const uint32_t* __restrict__ status,
+                        int sweep) {
+  extern __shared__ double2 replay_rows[];
+  const int b = blockIdx.x;
+  if (b < nb)
+    jacobi_sweep(H, n, log, state, status, sweep, b);
+  else
+    jacobi_replay(V, n, log, state, sweep - 1, (b - nb) / parts, (b - nb) % parts, replay_rows);
 }
 
 // Sort ascending, fix each column's phase: eps from the diagonal of A, the
@@ -1049,8 +1055,8 @@ __global__ void __launch_bounds__(kLargeThreads)
 
 constexpr int64_t kLargeChunk = 1024;  // matrices per large-n launch (bounds the workspace)
 
-// doubles of one matrix's log: kLogSweeps sweeps of rounds of n / 2 rotations
-inline int64_t log_doubles(int n) { return (int64_t)4 * kLogSweeps * (n + (n & 1) - 1) * large_pairs(n); }
+// doubles of one matrix's two logs: n2 - 1 rounds of n / 2 rotations each
+inline int64_t log_doubles(int n) { return (int64_t)4 * 2 * (n + (n & 1) - 1) * large_pairs(n); }
 
 }  // namespace
 
@@ -1107,20 +1113,19 @@ ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V,
     set_error("jacobi_eigh: large matrices need a workspace");
     return EPHW_EINVAL;
   }
-  const size_t rows_lds = (size_t)4 * kReplayRows * n * sizeof(double2);
+  const size_t lds = (size_t)(kLargeThreads / 64) * kReplayRows * n * sizeof(double2);
+  const int parts = (int)ceil_div(n, (kLargeThreads / 64) * kReplayRows);
+  EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_sweep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   for (int64_t b0 = 0; b0 < batch; b0 += kLargeChunk) {
     const int64_t nb = (batch - b0) < kLargeChunk ? (batch - b0) : kLargeChunk;
     double2* h = reinterpret_cast<double2*>(H) + b0 * n * n;
     double2* v = reinterpret_cast<double2*>(V) + b0 * n * n;
     LargeRot* log = reinterpret_cast<LargeRot*>(work);
     int* state = reinterpret_cast<int*>(work + log_doubles(n) * nb);
-    const int phases = max_sweeps > kLogSweeps ? (max_sweeps + kLogSweeps - 1) / kLogSweeps : 1;
-    for (int ph = 0; ph < phases; ++ph) {
-      hipLaunchKernelGGL(jacobi_rounds_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, log, state, status,
-                         ph);
-      EPHW_CHECK_LAUNCH();
-      hipLaunchKernelGGL(jacobi_replay_kernel, dim3((unsigned)ceil_div(n, 4 * kReplayRows), (unsigned)nb), dim3(256),
-                         rows_lds, s, v, n, log, state, ph);
+    for (int sweep = 0; sweep <= (max_sweeps > 0 ? max_sweeps : 1); ++sweep) {
+      const int64_t grid = nb + (sweep > 0 ? nb * parts : 0);
+      hipLaunchKernelGGL(jacobi_sweep_kernel, dim3((unsigned)grid), dim3(kLargeThreads), lds, s, h, v, n, (int)nb,
+                         parts, log, state, status, sweep);
       EPHW_CHECK_LAUNCH();
     }
     hipLaunchKernelGGL(jacobi_finish_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, eps + b0 * n, v,
