@@ -522,8 +522,8 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
   EPHW_TRY(mode_vectors(kind, static_cast<const double*>(wsp(s, WS_E)), nq, (int)nm, s->ism, wsp(s, WS_U), st));
   const bool rot = (flags & (EPHW_OUT_G | EPHW_OUT_LOSS)) != 0;
-  // only complex64 values leave the products (see GemmParams::split)
-  const bool split = kind == 1 && (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
+  // see GemmParams
+  const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   const bool need_g = (flags & (EPHW_OUT_G | EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) != 0;
   const size_t gsz = (size_t)qb * ne * E * cs, wsz = (size_t)kt * qb * E * cs;
   const int64_t rot_tiles = cgemm_tiles(kind, nm * nw, nw);  // per pair
@@ -562,7 +562,7 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
     rp.ldc = rp.N;
     {
       Stage sg_(s, EPHW_STAGE_RP_GEMM, st);
-      rp.split = split;
+      rp.any_rounding = any_rounding;
       EPHW_TRY(cgemm(kind, rp, st));
     }
     {
@@ -588,7 +588,7 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
       mr.ldc = nw2;
       mr.strideC = E;
       mr.strideC2 = nb * E;
-      mr.split = split;
+      mr.any_rounding = any_rounding;
       EPHW_TRY(cgemm(kind, mr, st));
     }
     }
@@ -607,7 +607,7 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
       re.ldc = re.N;
       {
         Stage sg_(s, EPHW_STAGE_RE_GEMM, st);
-        re.split = split;
+        re.any_rounding = any_rounding;
         EPHW_TRY(cgemm(kind, re, st));
       }
       if (flags & EPHW_OUT_BAND_SUM) {
@@ -633,7 +633,7 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
       f4.C = Tm;
       f4.tblock = nw;
       f4.ldc = nw2;
-      f4.split = split;
+      f4.any_rounding = any_rounding;
       EPHW_TRY(cgemm(kind, f4, st));
       // g_nu[m'][n] = sum_m T'_nu[n][m] conj(V(k+q))[m][m']: rows (nu, n), columns m',
       // stored block-transposed, i.e. in the [nu][m'][n] order of g
@@ -665,7 +665,7 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
         f5.loss.k0 = k0;
         f5.loss.partial = lossp;
       }
-      f5.split = split;
+      f5.any_rounding = any_rounding;
       EPHW_TRY(cgemm(kind, f5, st));
       if (flags & EPHW_OUT_LOSS) EPHW_TRY(sum_into(lossp, kl * nb * rot_tiles, loss, st));
     }
@@ -1200,7 +1200,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
       r1.C = Tm;
       r1.tblock = nw;
       r1.ldc = nw2;
-      r1.split = kind == 1;
+      r1.any_rounding = true;
       EPHW_TRY(cgemm(kind, r1, st));
       // W_nu = V(k+q) g_nu V(k)^dagger: rows (nu, n') of T' times V(k+q)^T, stored
       // block-transposed into [pair][nu][m'][n']
@@ -1212,7 +1212,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
       r2.C = Wb;
       r2.tblock = nw;
       r2.ldc = nw2;
-      r2.split = kind == 1;
+      r2.any_rounding = true;
       EPHW_TRY(cgemm(kind, r2, st));
       // G_nu(Re, q) (+)= sum_k e^{-ik.Re} W_nu(k, q)
       GemmParams rk;
@@ -1228,7 +1228,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
       rk.C = Gnubar;
       rk.ldc = nb * E;
       rk.accumulate = k0 > 0;
-      rk.split = kind == 1;
+      rk.any_rounding = true;
       EPHW_TRY(cgemm(kind, rk, st));
     }
     // G[q][e][ka] = sum_nu u^-1_{nu,ka}(q) G_nu[e][q]
@@ -1249,7 +1249,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
     mi.ldc = nw2;
     mi.strideC = ne * E;
     mi.strideC2 = E;
-    mi.split = kind == 1;
+    mi.any_rounding = true;
     EPHW_TRY(cgemm(kind, mi, st));
     // g(Re, Rp) (+)= 1/(Ne Np) sum_q e^{-iq.Rp} G(Re, q)
     GemmParams rq;
@@ -1265,7 +1265,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
     rq.C = g_out;
     rq.ldc = ne * E;
     rq.accumulate = q0 > 0;
-    rq.split = kind == 1;
+    rq.any_rounding = true;
     EPHW_TRY(cgemm(kind, rq, st));
   }
   return EPHW_OK;

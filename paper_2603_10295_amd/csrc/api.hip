@@ -472,7 +472,7 @@ ephw_status ephw_phase_sum_rp(ephw_system* s, const double* q, int64_t nq, int32
   p.K = s->np;
   p.A = wsp(s, WS_PQ);
   p.compensated = prec == EPHW_FP32_COMP;
-  p.split = kind == 1;
+  p.any_rounding = true;
   p.lda = s->np;
   p.B = s->g;
   p.ldb = p.N;
@@ -608,7 +608,7 @@ struct InterpReq {
   int32_t prec = 0, qb = 1;
   uint32_t flags = 0;
   bool need_g = false, need_kq_eig = false;
-  bool split = false;        // only complex64 values leave the phase sums (see GemmParams::split)
+  bool any_rounding = false; // of the phase sums (see GemmParams)
   bool packed = false;       // the Re sum on packed operands
   bool fused = false;        // band rotations in the Re-sum GEMM's epilogue (no W buffer)
   bool lw = false;           // linewidth reduction of the rotated g (no g output)
@@ -632,7 +632,7 @@ bool interp_fusable(const ephw_system* s, const InterpReq& r) {
 // phases and both the full and the last batch fit.
 bool interp_packable(const ephw_system* s, const ephw_kset* ks, const InterpReq& r) {
   const int64_t E = (int64_t)s->nm * s->nw * s->nw;
-  return r.split && r.need_g && ks->pkp && r.prec == EPHW_FP32 && cgemm_packable(r.nk, r.qb * E, s->ne);
+  return r.any_rounding && r.need_g && ks->pkp && r.prec == EPHW_FP32 && cgemm_packable(r.nk, r.qb * E, s->ne);
 }
 
 InterpWs interp_layout(const ephw_system* s, const InterpReq& r, char* base) {
@@ -670,7 +670,7 @@ InterpWs interp_layout(const ephw_system* s, const InterpReq& r, char* base) {
     w.bq = takd((size_t)qb * s->nh * nw2 * 16);
     w.hkq = takd((size_t)qb * nk * nw2 * 16);
     w.vkq64 = takd((size_t)qb * nk * nw2 * 16);
-    w.vkq = take((size_t)qb * nk * nw2 * cs);
+    w.vkq = kind == 0 ? static_cast<void*>(w.vkq64) : take((size_t)qb * nk * nw2 * cs);
   }
   if (r.need_kq_eig || r.lw) w.ekq = takd((size_t)qb * nk * nw * 8);
   if (r.flags & EPHW_OUT_LOSS) {
@@ -727,7 +727,7 @@ ephw_status interp_validate(const char* who, ephw_kset* ks, const double* q, int
   r->flags = flags;
   r->need_g = (flags & (EPHW_OUT_G | EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) != 0;
   r->need_kq_eig = !kq_index && (!wannier || eps_kq);
-  r->split = prec_kind(prec) == 1 && (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
+  r->any_rounding = prec_kind(prec) == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   return EPHW_OK;
 }
 
@@ -797,7 +797,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
       // far below the complex64 rounding they are cast to); FP64 at 1e-14
       EPHW_TRY(jacobi_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, s->ctx->max_sweeps,
                            st, kind == 0 ? 1e-28 : 1e-20));
-      EPHW_TRY(cast_complex(kind, w.vkq64, w.vkq, (int64_t)nb * nk * nw2, st));
+      if (kind != 0) EPHW_TRY(cast_complex(kind, w.vkq64, w.vkq, (int64_t)nb * nk * nw2, st));
       ekq_b = ekq;
     } else if ((eps_kq || r.lw) && kq_index) {
       // k+q on the k grid: its bands are the k-set's bands at the indexed point
@@ -814,7 +814,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     rp.K = s->np;
     rp.A = static_cast<const char*>(w.pq) + (size_t)q0 * s->np * cs;
     rp.compensated = comp;
-    rp.split = r.split;
+    rp.any_rounding = r.any_rounding;
     rp.lda = s->np;
     rp.B = s->g;
     rp.ldb = rp.N;
@@ -837,7 +837,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     re.K = s->ne;
     re.A = ks->pk;
     re.compensated = comp;
-    re.split = r.split;
+    re.any_rounding = r.any_rounding;
     if (r.packed) {
       float* inv = reinterpret_cast<float*>(static_cast<char*>(w.g) + packed_bytes(re.N, re.K));
       {

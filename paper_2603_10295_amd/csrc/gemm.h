@@ -97,13 +97,14 @@ struct GemmParams {
   // FP32 only: K-blocked accumulation (fresh accumulators every 32 k, block
   // sums added in FP32), the compensated form of EPHW_FP32_COMP
   bool compensated = false;
-  // FP32 only: the product may run on the 16-bit matrix cores with every value
-  // split into three bfloat16 (gemm_split.h): the error against 64 bits is no
-  // larger, the roundings are others.  Set where only complex64 values are
-  // returned; sums returned in double precision (band sums, losses,
+  // the order of the sum and its roundings are free.  FP32: the product may run
+  // on the 16-bit matrix cores with every value split (gemm_split.h), its error
+  // against 64 bits no larger; FP64: on tiles that sum in another order.  Set
+  // for FP64 results, and for FP32 ones where only complex64 values are
+  // returned.  Sums returned in double precision (band sums, losses,
   // linewidths, gradients) keep the FP32 instructions and with them their
-  // digits beyond FP32's.
-  bool split = false;
+  // digits beyond FP32's, and so do the eigenproblems they depend on.
+  bool any_rounding = false;
   int64_t n1 = 1, n2 = 1;
   int64_t strideA1 = 0, strideA2 = 0, strideB1 = 0, strideB2 = 0, strideC1 = 0, strideC2 = 0;
   // tblock > 0: C is stored in blocks of tblock rows, each block transposed:
@@ -153,7 +154,7 @@ void cgemm_tile_shape(int prec, int cfg, int* bm, int* bn);
 // is this times the CU count)
 int cgemm_grouped_blocks_per_cu(int prec, int cfg);
 // FP32 tile configuration of a grouped product that may be split (see
-// GemmParams::split; 2 = 128x128, 3 = 64x128 tiles) for problems of
+// GemmParams::any_rounding; 2 = 128x128, 3 = 64x128 tiles) for problems of
 // start[i + 1] - start[i] rows and depth K, or -1 where they are not split
 int cgemm_grouped_split_cfg(int64_t K, int64_t lda, int64_t ldb, const int64_t* start, int64_t n);
 // whether the grouped kernel can address operands with these leading dimensions

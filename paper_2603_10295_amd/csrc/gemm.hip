@@ -1722,7 +1722,7 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
       if (b.nw == 8 && b.nm % 2 == 0) return launch_packed<16>(p, stream);
       return b.nw == 8 ? launch_packed<8>(p, stream) : launch_packed<4>(p, stream);
     }
-    if (p.split && p.K >= kSplitMinK && split_fits(false, false, p.lda, p.ldb)) {
+    if (p.any_rounding && p.K >= kSplitMinK && split_fits(false, false, p.lda, p.ldb)) {
       if (b.nw == 8 && b.nm % 2 == 0) return launch_split<Split128, false, false, false, 16>(p, stream);
       return b.nw == 8 ? launch_split<Split128, false, false, false, 8>(p, stream)
                        : launch_split<Split128, false, false, false, 4>(p, stream);
@@ -1744,7 +1744,7 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
     }
     return launch_packed<0>(p, stream);
   }
-  if (p.split && p.K >= kSplitMinK && p.compensated && prec != 0 && split_fits(p.transA, p.transB, p.lda, p.ldb))
+  if (p.any_rounding && p.K >= kSplitMinK && p.compensated && prec != 0 && split_fits(p.transA, p.transB, p.lda, p.ldb))
     return dispatch_split<Split64, true>(p, stream);   // its second accumulators fit the registers of 64x128
   if (p.compensated) {
     if (prec == 0) {
@@ -1759,9 +1759,16 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
   // (FP32 reads two complex values per 16-byte load: rows must start on 16 bytes)
   if (p.M <= 16 && p.N >= 16384 && !p.transB && !p.conjB && !p.loss.on && p.tblock == 0 &&
       (prec == 0 || (p.ldb % 2 == 0 && p.strideB % 2 == 0 && p.strideB1 % 2 == 0 && p.strideB2 % 2 == 0 &&
-                     !p.offB && reinterpret_cast<uintptr_t>(p.B) % 16 == 0)))
+                     !p.offB && reinterpret_cast<uintptr_t>(p.B) % 16 == 0))) {
+    // FP64: the 16-row tile's matrix work, padding included, takes less time than
+    // reading B, where a thread per column waits for its operands (M = 16, K = 125,
+    // N = 48000: 29 us against 61)
+    if (prec == 0 && p.any_rounding)
+      return p.transA ? launch<double, 16, 128, 16, 1, 4, true, false, 0, 2>(p, stream)
+                      : launch<double, 16, 128, 16, 1, 4, false, false, 0, 2>(p, stream);
     return prec == 0 ? dispatch_skinny<double>(p, stream) : dispatch_skinny<float>(p, stream);
-  if (p.split && p.K >= kSplitMinK && prec != 0 && !p.loss.on && split_fits(p.transA, p.transB, p.lda, p.ldb)) {
+  }
+  if (p.any_rounding && p.K >= kSplitMinK && prec != 0 && !p.loss.on && split_fits(p.transA, p.transB, p.lda, p.ldb)) {
     const int rows = split_rows(p.M, p.N, p.K);
     if (rows == 128) return dispatch_split<Split128, false>(p, stream);
     if (rows == 64) return dispatch_split<Split64, false>(p, stream);
@@ -1781,10 +1788,18 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
     set_error("cgemm: loss epilogue with leading dimensions too large for the 64x224 tile");
     return EPHW_EUNSUPPORTED;
   }
+  // 64x64 tiles on fewer workgroups than CUs: a quarter of the tile per
+  // workgroup (one 16x16 block per wave) takes a quarter of the time, which is
+  // that of its matrix instructions (FP64, K = 125: 24 -> 11 us), and slabs
+  // twice as deep, fewer loads in a row to wait for
+  const bool few = ceil_div(p.M, 64) * ceil_div(p.N, 64) * p.batch <= 256 && !p.loss.on;
   if (prec == 0) {
+    if (few && fits_any<double, 32, 32, 16, 2, 2>(p)) return dispatch_trans<double, 32, 32, 16, 2, 2, false, 2>(p, stream);
     if (wide) return dispatch_trans<double, 64, 224, 16, 2, 2, false, 1>(p, stream);
     return dispatch_trans<double, 64, 64, 8, 2, 2, false, 2>(p, stream);
   }
+  if (few && fits_any<float, 32, 32, 32, 2, 2>(p))
+    return dispatch_trans<float, 32, 32, 32, 2, 2, false, 2>(p, stream);
   if (wide) return dispatch_trans<float, 64, 224, 16, 4, 1, false, 2>(p, stream);
   if (small) return dispatch_trans<float, 64, 64, 16, 2, 2, false, 4>(p, stream);
   return dispatch_trans<float, 128, 128, 16, 2, 2, false, 2>(p, stream);

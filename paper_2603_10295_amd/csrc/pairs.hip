@@ -296,10 +296,10 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
 
   // one grouped-GEMM problem per group: by q, W_q = P_k[kept k] G_nu(q); by
   // k, W_k = P_q[kept q] G'(k); operand pointers relative to the chunk's buffers
-  // 64 x 64 tiles: the problems have tens of rows; split tiles where only
-  // complex64 values leave the sums (see GemmParams::split)
-  const bool split = kind == 1 && (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
-  const int cfg_split = split ? cgemm_grouped_split_cfg(by_k ? np : ne, lda_pair, ldb_pair, seg.data(), pl.na) : -1;
+  // 64 x 64 tiles: the problems have tens of rows; FP32 split tiles where the
+  // rounding is free (see GemmParams)
+  const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
+  const int cfg_split = kind == 1 && any_rounding ? cgemm_grouped_split_cfg(by_k ? np : ne, lda_pair, ldb_pair, seg.data(), pl.na) : -1;
   const int cfg = cfg_split > 0 ? cfg_split : 1;
   std::vector<GroupProblem> probs(pl.na);
   std::vector<int64_t> chunk_tiles(pl.nchunk);
@@ -383,7 +383,7 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
       rp.ldb = rp.N;
       rp.C = w.first;
       rp.ldc = rp.N;
-      rp.split = split;
+      rp.any_rounding = any_rounding;
       {
         Stage sg_(s, EPHW_STAGE_RP_GEMM, st);
         EPHW_TRY(cgemm(kind, rp, st));
@@ -418,7 +418,7 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
         re.C = w.big;
         re.ldc = np * E;
         re.strideC = E;
-        re.split = split;
+        re.any_rounding = any_rounding;
         EPHW_TRY(cgemm(kind, re, st));
       }
       // the Rp sum per k over its kept q, then the mode vectors per pair

@@ -126,3 +126,17 @@ def test_rotated_g_agrees_with_the_fp32_instructions(run, nk, nw, na):
     a = run.interpolate(h, k, q, 1, flags=ephw.OUT_G, want_eps_kq=False)["g"]
     b = run.interpolate(h, k, q, 1, flags=ephw.OUT_G | ephw.OUT_LOSS, want_eps_kq=False)["g"]
     assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("nq,box", [(1, (1, 1, 1)), (4, (4, 4, 1)), (15, (17, 1, 1)), (16, (5, 13, 1)), (17, (5, 13, 1))])
+def test_rp_sum_fp64_few_rows(run, nq, box):
+    """FP64 sums of up to 16 q over at least 16384 columns take a 16-row tile:
+    K below, at and past a slab, a ragged last column tile, and one row more."""
+    rp = synth.box(box)
+    s = synth.make_system(5, 1, synth.box((20, 11, 1)), rp, [nq, 32])
+    q = np.random.default_rng(nq).random((nq, 3))
+    K = len(rp)
+    ph, g = oracle.phases(q, rp), s.g.reshape(K, -1)
+    got = run.phase_sum_rp(run.system(s), q, 0).reshape(nq, -1)
+    mag = np.abs(ph) @ (np.abs(g.real) + np.abs(g.imag))
+    assert np.all(np.abs(got - ph @ g) <= 2 * (2 * K + 4) * 2.0 ** -53 * mag)
