@@ -64,16 +64,17 @@ __global__ void eig_mid_kernel(double* __restrict__ M, const double* __restrict_
 }
 
 // uinvT[q][a][v] = conj(e[q][a][v]) / ism[a]: the transpose of u^-1 for
-// u = diag(ism) e with e unitary (u^-1 = e^dagger diag(1/ism))
+// u = diag(ism) e with e unitary (u^-1 = e^dagger diag(1/ism)); plain: u^-1
+// itself, [q][v][a]
 template <typename T>
 __global__ void mode_inverse_kernel(const double* __restrict__ e, int64_t nq, int nm, const double* __restrict__ ism,
-                                    T* __restrict__ out) {
+                                    T* __restrict__ out, bool plain) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t per = (int64_t)nm * nm;
   if (i >= nq * per) return;
-  const int a = (int)((i % per) / nm);
-  out[2 * i] = (T)(e[2 * i] / ism[a]);
-  out[2 * i + 1] = (T)(-e[2 * i + 1] / ism[a]);
+  const int64_t q = i / per, a = (i % per) / nm, v = i % nm, o = plain ? q * per + v * nm + a : i;
+  out[2 * o] = (T)(e[2 * i] / ism[a]);
+  out[2 * o + 1] = (T)(-e[2 * i + 1] / ism[a]);
 }
 
 template <typename T>
@@ -182,6 +183,46 @@ __global__ void splitk_reduce_kernel(const T* __restrict__ part, int64_t batch, 
   }
   c[0] = re;
   c[1] = im;
+}
+
+// C[q] (+)= sum over e of (sum over chunks of part[q][e][chunk]), in order
+template <typename T>
+__global__ void ubar_reduce_kernel(const T* __restrict__ part, int64_t nq, int64_t ne, int chunks, int64_t mn,
+                                   T* __restrict__ C, int accumulate) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= nq * mn) return;
+  const int64_t q = idx / mn, i = idx % mn;
+  T re = accumulate ? C[2 * idx] : T(0), im = accumulate ? C[2 * idx + 1] : T(0);
+  for (int64_t e = 0; e < ne; ++e) {
+    T sr = 0, si = 0;
+    for (int c = 0; c < chunks; ++c) {
+      const T* p = part + 2 * (((q * ne + e) * chunks + c) * mn + i);
+      sr += p[0];
+      si += p[1];
+    }
+    re += sr;
+    im += si;
+  }
+  C[2 * idx] = re;
+  C[2 * idx + 1] = im;
+}
+
+// out[i][n][m] = conj(v[i][m][n])
+template <typename T>
+__global__ void conj_transpose_kernel(const T* __restrict__ v, int64_t count, int nw, T* __restrict__ out) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t nw2 = (int64_t)nw * nw;
+  if (idx >= count * nw2) return;
+  const int64_t i = idx / nw2, n = idx % nw2 / nw, m = idx % nw;
+  const T* src = v + 2 * (i * nw2 + m * nw + n);
+  out[2 * idx] = src[0];
+  out[2 * idx + 1] = -src[1];
+}
+
+// k index of every pair of a q-major pair list over all k
+__global__ void pair_k_kernel(int64_t n, int64_t nk, int32_t* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = (int32_t)(i % nk);
 }
 
 template <typename T>
@@ -432,12 +473,16 @@ namespace {
 // GEMM whose 128-row tiles want many k) and every k tile re-reads g(Re,q);
 // a larger q batch at the same pair budget would shorten the k tile, which
 // measured slower on the ribbon than the Eq. (9) GEMM it speeds up.
-void unit_shape(const ephw_system* s, int64_t nq, int64_t nk, int64_t E, size_t cs, int nbuf, int64_t* qb_out,
-                int64_t* kt_out) {
+void unit_shape(const ephw_system* s, int64_t nq, int64_t nk, int64_t E, size_t cs, int nbuf, bool forward,
+                int64_t* qb_out, int64_t* kt_out) {
   int64_t qb = s->q_batch;
   if (qb <= 0) {
     qb = (int64_t)(8.0e9 / (4.0 * (double)s->ne * E * cs));
     qb = std::max<int64_t>(1, std::min<int64_t>(qb, 8));
+    // the forward's two buffers may take 20 GB, one read of g(Re,Rp) for 8 q,
+    // while every k point still fits the pair budget
+    const int64_t qw = std::min<int64_t>(8, (int64_t)(20.0e9 / (2.0 * (double)s->ne * E * cs)));
+    if (forward && qw > qb && (double)nbuf * cs * std::min(qw, nq) * E * nk <= 48.0e9) qb = qw;
   }
   qb = std::min(qb, nq);
   int64_t kt = (int64_t)(48.0e9 / ((double)nbuf * cs * qb * E));
@@ -491,7 +536,7 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
   const size_t cs = csize(kind);
   const int64_t nw = s->nw, nm = s->nm, nw2 = nw * nw, E = nm * nw2, nk = ks->nk, ne = s->ne, np = s->np;
   int64_t qb, kt;
-  unit_shape(s, nq, nk, E, cs, 2, &qb, &kt);
+  unit_shape(s, nq, nk, E, cs, 2, true, &qb, &kt);
   // q side
   EPHW_TRY(ws_need(s, WS_PQ, (size_t)nq * np * cs));
   EPHW_TRY(phase_matrix(kind, q, nq, s->r_p, s->w_p, np, wsp(s, WS_PQ), st));
@@ -700,7 +745,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
   const int64_t nw = s->nw, nm = s->nm, nw2 = nw * nw, E = nm * nw2, nk = ks->nk, ne = s->ne, np = s->np;
   // unit shape: q batch and k tile within a workspace budget
   int64_t qb, kt;
-  unit_shape(s, nq, nk, E, cs, 7, &qb, &kt);
+  unit_shape(s, nq, nk, E, cs, 7, false, &qb, &kt);
 
   // ---- k side: eigenvector derivatives and scaled phases (cached in the k-set) ----
   if (!ks->dv) {
@@ -722,18 +767,6 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
                                 kind == 1 ? ks->dv : nullptr, kind, st));
     EPHW_TRY(scale_phase(kind, ks->pk, nk, s->r_e, ne, ks->dpk, st));
   }
-  // directions with a nonzero lattice component (the others have zero phase derivatives)
-  bool dir_e[3] = {false, false, false}, dir_p[3] = {false, false, false};
-  {
-    std::vector<int32_t> re(3 * ne), rp(3 * np);
-    EPHW_HIP(hipMemcpy(re.data(), s->r_e, re.size() * 4, hipMemcpyDeviceToHost));
-    EPHW_HIP(hipMemcpy(rp.data(), s->r_p, rp.size() * 4, hipMemcpyDeviceToHost));
-    for (int64_t i = 0; i < ne; ++i)
-      for (int d = 0; d < 3; ++d) dir_e[d] = dir_e[d] || re[3 * i + d] != 0;
-    for (int64_t i = 0; i < np; ++i)
-      for (int d = 0; d < 3; ++d) dir_p[d] = dir_p[d] || rp[3 * i + d] != 0;
-  }
-
   // ---- q side: phases, D(q) eigensolve, u, du/dq ----
   EPHW_TRY(ws_need(s, WS_PQ, (size_t)nq * np * cs));
   EPHW_TRY(phase_matrix(kind, q, nq, s->r_p, s->w_p, np, wsp(s, WS_PQ), st));
@@ -801,7 +834,10 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
   EPHW_TRY(ws_need(s, WS_LOSS, (size_t)kt * qb * rot_tiles * 8));
   EPHW_TRY(ws_need(s, WS_UBAR, (size_t)qb * nm * nm * cs));
   const int chunks_u = splitk_chunks(nw2, 16, 256);
-  EPHW_TRY(ws_need(s, WS_SPLIT, (size_t)std::max<int64_t>(qb * chunks_u * nm * nm, 1) * cs));
+  // Re per launch of the ubar products: all of them within 512 MB of partials
+  const int64_t ubar_each = qb * chunks_u * nm * nm * (int64_t)cs;
+  const int64_t ubar_group = std::max<int64_t>(1, std::min<int64_t>(ne, ((int64_t)512 << 20) / ubar_each));
+  EPHW_TRY(ws_need(s, WS_SPLIT, (size_t)(ubar_group * ubar_each)));
   // the per-pair Vbar GEMMs (Nw x Nw outputs, K = Nm Nw) split K until a unit
   // has about 1024 tiles
   const int64_t pair_out_tiles = cgemm_tiles(kind, nw, nw);
@@ -995,7 +1031,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
       EPHW_TRY(cgemm(kind, b6, st));
       // k through the Re phases: dk_d += Re <Wbar, W'_d>, W'_d = (2 pi i Re_d Pk) Gnu
       for (int d = 0; d < 3; ++d) {
-        if (!dir_e[d]) continue;
+        if (!s->dir_e[d]) continue;   // no lattice component: zero phase derivative
         GemmParams wd = re;
         wd.A = static_cast<const char*>(ks->dpk) + ((size_t)d * nk + k0) * ne * cs;
         wd.C = Z;  // Z is free now: reuse as W'_d
@@ -1023,26 +1059,45 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
     ma.strideC = ne * E;
     ma.strideC2 = E;
     EPHW_TRY(cgemm(kind, ma, st));
-    // ubar[q] = sum_e conj(G[q][e]) Gnubar[e][q]^T   (split-K over the band pairs)
-    for (int64_t e = 0; e < ne; ++e) {
+    // ubar[q] = sum_e conj(G[q][e]) Gnubar[e][q]^T: one product per (q, Re) and
+    // K chunk in a launch, then the sums in the order of Re
+    for (int64_t e0 = 0; e0 < ne; e0 += ubar_group) {
+      const int64_t eg = std::min(ubar_group, ne - e0);
       GemmParams ub;
       ub.M = nm;
       ub.N = nm;
-      ub.K = nw2;
-      ub.batch = nb;
-      ub.A = G + (size_t)e * E * cs;
+      ub.K = nw2 / chunks_u;
+      ub.batch = nb * eg * chunks_u;
+      ub.n1 = eg;
+      ub.n2 = chunks_u;
+      ub.A = G + (size_t)e0 * E * cs;
       ub.conjA = true;
       ub.lda = nw2;
       ub.strideA = ne * E;
-      ub.B = Gnubar + (size_t)e * nb * E * cs;
+      ub.strideA1 = E;
+      ub.strideA2 = ub.K;
+      ub.B = Gnubar + (size_t)e0 * nb * E * cs;
       ub.transB = true;
       ub.ldb = nw2;
       ub.strideB = E;
-      ub.C = ubar;
+      ub.strideB1 = nb * E;
+      ub.strideB2 = ub.K;
+      ub.C = wsp(s, WS_SPLIT);
       ub.ldc = nm;
-      ub.strideC = nm * nm;
-      ub.accumulate = e > 0;
-      EPHW_TRY(cgemm_splitk(kind, ub, chunks_u, wsp(s, WS_SPLIT), st));
+      ub.strideC = eg * chunks_u * nm * nm;
+      ub.strideC1 = chunks_u * nm * nm;
+      ub.strideC2 = nm * nm;
+      EPHW_TRY(cgemm(kind, ub, st));
+      const int64_t total = nb * nm * nm;
+      if (kind == 0)
+        hipLaunchKernelGGL(ubar_reduce_kernel<double>, dim3(grid1(total, 256)), dim3(256), 0, st,
+                           static_cast<const double*>(wsp(s, WS_SPLIT)), nb, eg, chunks_u, nm * nm,
+                           reinterpret_cast<double*>(ubar), e0 > 0 ? 1 : 0);
+      else
+        hipLaunchKernelGGL(ubar_reduce_kernel<float>, dim3(grid1(total, 256)), dim3(256), 0, st,
+                           static_cast<const float*>(wsp(s, WS_SPLIT)), nb, eg, chunks_u, nm * nm,
+                           reinterpret_cast<float*>(ubar), e0 > 0 ? 1 : 0);
+      EPHW_CHECK_LAUNCH();
     }
     // q through u: dq_d += Re <ubar[q], du_d[q]>
     for (int d = 0; d < 3; ++d)
@@ -1067,7 +1122,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
     }
     // q through the Rp phases: dq_d += Re <Gbar, G'_d>, G'_d = (2 pi i Rp_d Pq) g
     for (int d = 0; d < 3; ++d) {
-      if (!dir_p[d]) continue;
+      if (!s->dir_p[d]) continue;
       GemmParams gd = rp;
       gd.A = dpq + ((size_t)d * nq + q0) * np * cs;
       gd.C = Gnu;  // free after the k loop
@@ -1109,6 +1164,11 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
   int64_t kt = s->k_tile > 0 ? s->k_tile : (int64_t)(16.0e9 / (2.0 * (double)cs * qb * E));
   kt = std::max<int64_t>(1, std::min(kt, nk));
 
+  // up to 32 bands with every k in one tile: the band-rotation kernels, and up to
+  // 24 modes the mode kernel (products of 48 x 8 outputs and K = 8 per pair, 6 x
+  // 64 and K = 6 per Re, are mostly padding on GEMM tiles: 340 and 170 us at 512
+  // k x 64 q, 90 and 41 us here)
+  const bool small = nw <= 32 && kt == nk && qb * nk <= 0x7fffffff, small_modes = small && nm <= 24;
   // phases as Eq. (6) writes them (no lattice-vector weights); the q ones
   // carry 1/(Ne Np)
   EPHW_TRY(ws_need(s, WS_CPK, (size_t)nk * ne * cs));
@@ -1156,10 +1216,10 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
     const double* e = static_cast<const double*>(wsp(s, WS_E));
     if (kind == 0)
       hipLaunchKernelGGL(mode_inverse_kernel<double>, dim3(grid1(n, 256)), dim3(256), 0, st, e, nq, (int)nm, s->ism,
-                         static_cast<double*>(wsp(s, WS_UINV)));
+                         static_cast<double*>(wsp(s, WS_UINV)), small_modes);
     else
       hipLaunchKernelGGL(mode_inverse_kernel<float>, dim3(grid1(n, 256)), dim3(256), 0, st, e, nq, (int)nm, s->ism,
-                         static_cast<float*>(wsp(s, WS_UINV)));
+                         static_cast<float*>(wsp(s, WS_UINV)), small_modes);
     EPHW_CHECK_LAUNCH();
   }
 
@@ -1179,11 +1239,71 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
   const char* uinv = static_cast<const char*>(wsp(s, WS_UINV));
   const char* gb = static_cast<const char*>(g_bloch);
   char* vt = static_cast<char*>(ks->vt);
+  if (small) {
+    EPHW_TRY(ws_need(s, WS_VH, (size_t)nk * nw2 * cs));
+    const int64_t n = nk * nw2;
+    if (kind == 0)
+      hipLaunchKernelGGL(conj_transpose_kernel<double>, dim3(grid1(n, 256)), dim3(256), 0, st,
+                         static_cast<const double*>(ks->vt), nk, (int)nw, static_cast<double*>(wsp(s, WS_VH)));
+    else
+      hipLaunchKernelGGL(conj_transpose_kernel<float>, dim3(grid1(n, 256)), dim3(256), 0, st,
+                         static_cast<const float*>(ks->vt), nk, (int)nw, static_cast<float*>(wsp(s, WS_VH)));
+    EPHW_CHECK_LAUNCH();
+  }
 
   for (int64_t q0 = 0; q0 < nq; q0 += qb) {
     const int64_t nb = std::min(qb, nq - q0);
     for (int64_t k0 = 0; k0 < nk; k0 += kt) {
       const int64_t kl = std::min(kt, nk - k0);
+      if (small) {
+        // W_nu = V'(k+q)^dagger g_nu V'(k) with V' = V^dagger: the band-rotation
+        // kernels on the q-major pairs as they lie in g_bloch, then the sum over
+        // k per q
+        const int64_t np_b = nb * nk;
+        int32_t* pk = reinterpret_cast<int32_t*>(offp);
+        hipLaunchKernelGGL(pair_k_kernel, dim3(grid1(np_b, 256)), dim3(256), 0, st, np_b, nk, pk);
+        EPHW_CHECK_LAUNCH();
+        BandRotateArgs br;
+        br.W = gb + (size_t)q0 * nk * E * cs;
+        br.Vk = wsp(s, WS_VH);
+        br.Vkq = nullptr;
+        br.kq_index = kq_index + q0 * nk;
+        br.nk = np_b;
+        br.nk_tile = np_b;
+        br.qb = 1;
+        br.nm = (int)nm;
+        br.nw = (int)nw;
+        br.flags = EPHW_OUT_G;
+        br.g_out = Wb;
+        br.band_sum = nullptr;
+        br.loss_partial = nullptr;
+        br.loss_seed = 0;
+        br.q_global0 = 0;
+        br.status = s->ctx->status;
+        br.pair_k = pk;
+        br.pair_q = pk;   // read for the loss index only
+        br.nk_set = nk;
+        EPHW_TRY(band_rotate(kind, br, st));
+        GemmParams rk;
+        rk.M = ne;
+        rk.N = E;
+        rk.K = nk;
+        rk.batch = nb;
+        rk.A = cpk;
+        rk.transA = true;
+        rk.conjA = true;
+        rk.lda = ne;
+        rk.strideA = 0;
+        rk.B = Wb;
+        rk.ldb = E;
+        rk.strideB = nk * E;
+        rk.C = Gnubar;
+        rk.ldc = small_modes ? E : nb * E;
+        rk.strideC = small_modes ? ne * E : E;
+        rk.any_rounding = true;
+        EPHW_TRY(cgemm(kind, rk, st));
+        continue;
+      }
       hipLaunchKernelGGL(kq_offsets_kernel, dim3(grid1(kl * nb, 256)), dim3(256), 0, st, kq_index, nk, q0, k0, (int)kl,
                          (int)nb, nw2, offp, s->ctx->status);
       EPHW_CHECK_LAUNCH();
@@ -1232,25 +1352,29 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
       EPHW_TRY(cgemm(kind, rk, st));
     }
     // G[q][e][ka] = sum_nu u^-1_{nu,ka}(q) G_nu[e][q]
-    GemmParams mi;
-    mi.M = nm;
-    mi.N = nw2;
-    mi.K = nm;
-    mi.batch = nb * ne;
-    mi.n2 = ne;
-    mi.A = uinv + (size_t)q0 * nm * nm * cs;
-    mi.lda = nm;
-    mi.strideA = nm * nm;
-    mi.B = Gnubar;
-    mi.ldb = nw2;
-    mi.strideB = E;
-    mi.strideB2 = nb * E;
-    mi.C = Gbar;
-    mi.ldc = nw2;
-    mi.strideC = ne * E;
-    mi.strideC2 = E;
-    mi.any_rounding = true;
-    EPHW_TRY(cgemm(kind, mi, st));
+    if (small_modes) {
+      EPHW_TRY(mode_rotate(kind, Gnubar, uinv + (size_t)q0 * nm * nm * cs, Gbar, ne, (int)nb, (int)nm, nw2, st, true));
+    } else {
+      GemmParams mi;
+      mi.M = nm;
+      mi.N = nw2;
+      mi.K = nm;
+      mi.batch = nb * ne;
+      mi.n2 = ne;
+      mi.A = uinv + (size_t)q0 * nm * nm * cs;
+      mi.lda = nm;
+      mi.strideA = nm * nm;
+      mi.B = Gnubar;
+      mi.ldb = nw2;
+      mi.strideB = E;
+      mi.strideB2 = nb * E;
+      mi.C = Gbar;
+      mi.ldc = nw2;
+      mi.strideC = ne * E;
+      mi.strideC2 = E;
+      mi.any_rounding = true;
+      EPHW_TRY(cgemm(kind, mi, st));
+    }
     // g(Re, Rp) (+)= 1/(Ne Np) sum_q e^{-iq.Rp} G(Re, q)
     GemmParams rq;
     rq.M = np;

@@ -241,6 +241,10 @@ ephw_status ephw_system_load(ephw_ctx* ctx, const ephw_system_desc* d, ephw_syst
     return upload(dst, w, (size_t)n, &s->bytes, s->mem.get());
   };
   if ((st = weights(&s->w_e, d->w_e, d->ne)) != EPHW_OK) return fail(st);
+  for (int dd = 0; dd < 3; ++dd) {
+    for (int64_t i = 0; i < d->ne; ++i) s->dir_e[dd] = s->dir_e[dd] || d->r_e[3 * i + dd] != 0;
+    for (int64_t i = 0; i < d->np; ++i) s->dir_p[dd] = s->dir_p[dd] || d->r_p[3 * i + dd] != 0;
+  }
   {
     // packed phases keep every weight's leading 22 bits only within a range of
     // 2^8 of the largest (smaller ones would lose bits to the FP16 range)
@@ -487,7 +491,7 @@ ephw_status ephw_phase_sum_rp(ephw_system* s, const double* q, int64_t nq, int32
 ephw_status ephw_kset_free(ephw_kset* ks) {
   if (!ks) return EPHW_OK;
   (void)hipDeviceSynchronize();
-  void* ptrs[] = {ks->k, ks->pk, ks->pkp, ks->pkh, ks->eps, ks->v64, ks->vt, ks->dv64, ks->dpk,
+  void* ptrs[] = {ks->block, ks->pkp, ks->dv64, ks->dpk,
                   ks->dv != ks->dv64 ? ks->dv : nullptr};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -529,16 +533,29 @@ ephw_status ephw_kset_create(ephw_system* s, const double* k, int64_t nk, int32_
     ephw_kset_free(ks);
     return r;
   };
-  if ((e = alloc((void**)&ks->k, (size_t)nk * 24)) != EPHW_OK) return fail(e);
+  {
+    // one block for the set's arrays: an allocation and, when it is freed, a
+    // wait for the device each would cost more than a small set's kernels
+    const size_t sizes[] = {(size_t)nk * 24, (size_t)nk * s->ne * csize(kind), (size_t)nk * s->nh * 16,
+                            (size_t)nk * s->nw * 8, (size_t)nk * nw2 * 16, (size_t)nk * nw2 * csize(kind)};
+    size_t off[6], total = 0;
+    for (int i = 0; i < 6; ++i) {
+      off[i] = total;
+      total += (sizes[i] + 255) & ~(size_t)255;
+    }
+    if ((e = alloc(&ks->block, total)) != EPHW_OK) return fail(e);
+    char* base = static_cast<char*>(ks->block);
+    ks->k = reinterpret_cast<double*>(base + off[0]);
+    ks->pk = base + off[1];
+    ks->pkh = reinterpret_cast<double*>(base + off[2]);
+    ks->eps = reinterpret_cast<double*>(base + off[3]);
+    ks->v64 = reinterpret_cast<double*>(base + off[4]);
+    ks->vt = base + off[5];
+  }
   if (hipMemcpyAsync(ks->k, k, (size_t)nk * 24, hipMemcpyDeviceToDevice, st) != hipSuccess) {
     set_error("ephw_kset_create: copy of k failed");
     return fail(EPHW_EDEVICE);
   }
-  if ((e = alloc(&ks->pk, (size_t)nk * s->ne * csize(kind))) != EPHW_OK) return fail(e);
-  if ((e = alloc((void**)&ks->pkh, (size_t)nk * s->nh * 16)) != EPHW_OK) return fail(e);
-  if ((e = alloc((void**)&ks->eps, (size_t)nk * s->nw * 8)) != EPHW_OK) return fail(e);
-  if ((e = alloc((void**)&ks->v64, (size_t)nk * nw2 * 16)) != EPHW_OK) return fail(e);
-  if ((e = alloc(&ks->vt, (size_t)nk * nw2 * csize(kind))) != EPHW_OK) return fail(e);
   {
     Stage sg_(s, EPHW_STAGE_PHASE, st);
     if ((e = phase_matrix(kind, ks->k, nk, s->r_e, s->w_e, s->ne, ks->pk, st)) != EPHW_OK)
@@ -624,6 +641,10 @@ struct InterpReq {
 bool interp_fusable(const ephw_system* s, const InterpReq& r) {
   if (r.prec != EPHW_FP32 || (r.flags & EPHW_OUT_WANNIER) || !r.need_g) return false;
   const int64_t E = (int64_t)s->nm * s->nw * s->nw, tail = r.nq % r.qb;
+  // behind the faster product of free rounding the epilogues on VALU are most
+  // of the kernel (Nw = 4, K = 250: 1070 us fused, 540 us with W stored and
+  // the rotations in a pass of their own)
+  if (r.any_rounding && s->ne >= kSplitMinK && !(s->nw == 8 && s->nm % 2 == 0)) return false;
   return cgemm_band_fusable(1, r.nk, r.qb * E, s->nw, s->ne, r.qb * E) &&
          (tail == 0 || cgemm_band_fusable(1, r.nk, tail * E, s->nw, s->ne, tail * E));
 }

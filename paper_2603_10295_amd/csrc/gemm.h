@@ -59,6 +59,11 @@ struct BandEpilogue {
   uint32_t* status = nullptr;     // kStatusIndex for an index outside [0, nk)
 };
 
+// Least K of a product on the 16-bit matrix cores: with few slabs per tile the
+// first load and the store are the larger part of it, and an FP32 sum of few
+// terms has few roundings to save.
+constexpr int kSplitMinK = 64;
+
 // Packed operands of an FP32 product C = A B (pack.hip): rows of A and columns
 // of B scaled by powers of two and held as two binary16 values per real value.
 struct PackedOperands {

@@ -1718,14 +1718,12 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
       set_error("cgemm: the fused band epilogue stores g in 16-byte chunks (g must be 16-byte aligned)");
       return EPHW_EINVAL;
     }
-    if (p.packed.on) {
-      if (b.nw == 8 && b.nm % 2 == 0) return launch_packed<16>(p, stream);
-      return b.nw == 8 ? launch_packed<8>(p, stream) : launch_packed<4>(p, stream);
-    }
-    if (p.any_rounding && p.K >= kSplitMinK && split_fits(false, false, p.lda, p.ldb)) {
-      if (b.nw == 8 && b.nm % 2 == 0) return launch_split<Split128, false, false, false, 16>(p, stream);
-      return b.nw == 8 ? launch_split<Split128, false, false, false, 8>(p, stream)
-                       : launch_split<Split128, false, false, false, 4>(p, stream);
+    if (p.packed.on || (p.any_rounding && p.K >= kSplitMinK && split_fits(false, false, p.lda, p.ldb))) {
+      if (b.nw != 8 || b.nm % 2 != 0) {
+        set_error("cgemm: products of free rounding fuse the Nw = 8 rotations on the matrix cores only");
+        return EPHW_EUNSUPPORTED;
+      }
+      return p.packed.on ? launch_packed<16>(p, stream) : launch_split<Split128, false, false, false, 16>(p, stream);
     }
     // Nw = 8 with an even mode count: every tile holds two whole modes of one
     // q, which the MFMA form of the rotations needs

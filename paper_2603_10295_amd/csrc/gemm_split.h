@@ -27,10 +27,6 @@ __device__ __forceinline__ Acc32 mma32(U4 a, U4 b, Acc32 c) {
 __device__ __forceinline__ int row32(int lane, int v) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
 constexpr int kSplitNp = 3, kSplitK = 16;
-// shorter products keep the FP32 tiles: with few slabs per tile the first
-// load and the store are the larger part of it, and an FP32 sum of few terms
-// has few roundings to save
-constexpr int kSplitMinK = 64;
 
 // WM x WN waves of FM x FN blocks of 32x32 outputs
 template <int WM_, int WN_, int FM_, int FN_>
@@ -290,14 +286,14 @@ __device__ __forceinline__ void split_epilogue(const TileJob<float>& j, int64_t 
     }
 }
 
-// BANDNW: 0 plain epilogues, 4 or 8 the band rotations on VALU, 16 the Nw = 8
-// rotations on the matrix cores (see BandEpilogue)
+// BANDNW: 0 plain epilogues, 16 the Nw = 8 rotations on the matrix cores (see
+// BandEpilogue)
 template <typename S, int BANDNW>
 __device__ __forceinline__ void split_finish(const TileJob<float>& j, int64_t m0, int64_t n0, float* smem,
                                              const BandEpilogue* band, const Acc32 (&acc_r)[S::FM][S::FN],
                                              const Acc32 (&acc_i)[S::FM][S::FN]) {
   if constexpr (BANDNW > 0) {
-    static_assert(S::FM == 2 && S::FN == 2 && S::WM == 2, "the band epilogues take 64x64 outputs per wave");
+    static_assert(BANDNW == 16 && S::FM == 2 && S::FN == 2 && S::WM == 2, "the band epilogues take 64x64 outputs per wave");
     const int lane = threadIdx.x & 63;
     // W rows of half h (32 k points) of the wave's 64x64 block, [row][ldw] complex
     auto put_rows = [&](const Acc32 (&r)[2], const Acc32 (&i)[2], float* wl, int ldw) {
@@ -314,10 +310,7 @@ __device__ __forceinline__ void split_finish(const TileJob<float>& j, int64_t m0
       else
         put_rows(acc_r[1], acc_i[1], wl, ldw);
     };
-    if constexpr (BANDNW == 16)
-      band_epilogue_mfma8(j, *band, m0, n0, put, smem);
-    else
-      band_epilogue<BANDNW>(j, *band, m0, n0, put, smem);
+    band_epilogue_mfma8(j, *band, m0, n0, put, smem);
   } else {
     split_epilogue<S>(j, m0, n0, acc_r, acc_i);
   }

@@ -115,7 +115,7 @@ enum WsSlot {
   WS_ADJ_A, WS_ADJ_B, WS_ADJ_C, WS_DPQ, WS_DE64, WS_DU, WS_VKBAR, WS_PAIRS, WS_DKACC, WS_GBAR, WS_GNUBAR, WS_T,
   WS_YBAR, WS_Z, WS_WBAR, WS_PAIRBAR, WS_OFF, WS_UBAR, WS_SPLIT, WS_SPLITB, WS_DOTPART,
   // coarse Bloch -> Wannier transform
-  WS_CPK, WS_UINV,
+  WS_CPK, WS_UINV, WS_VH,
   // energy-window screen and the pair-list interpolation
   WS_WINDOW, WS_PAIRSET,
   // the buffers of an interpolation call (Nw <= 32) in one block
@@ -156,6 +156,7 @@ struct ephw_system {
   double* c_scaled = nullptr; // c128 [nc][nm][nm] = C / sqrt(M M')
   double* ism = nullptr;      // [nm] 1/sqrt(M_kappa) per mode index
   void* g = nullptr;
+  bool dir_e[3] = {false, false, false}, dir_p[3] = {false, false, false};   // lattice directions Re and Rp extend in
   // scale of the packed Re phases w_R e^{2 pi i k.R} (pack.hip), a power of two
   // with |w_R| scale <= 2^14, or 0 where the weights do not allow packing
   float pack_scale = 0.f;
@@ -176,6 +177,7 @@ struct ephw_kset {
   int64_t nk = 0;
   int32_t prec = 0;
   int64_t bytes = 0;
+  void* block = nullptr;    // holds k, pk, pkh, eps, v64 and vt
   double* k = nullptr;      // [nk][3]
   void* pk = nullptr;       // T [nk][ne]
   void* pkp = nullptr;      // packed copy of pk (FP32 sets of kPackMinPoints points or more), or NULL

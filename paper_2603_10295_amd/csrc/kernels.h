@@ -65,14 +65,15 @@ ephw_status abs_sqrt(const double* lam, double* omega, int64_t n, hipStream_t s)
 ephw_status scale_rows_by_phase(const double* phase, int64_t nq, const double* H, int64_t nr,
                                 int64_t nab, double* B, hipStream_t s);
 
-// Gnu[e][q][nu][mn] = sum_a u[q][a][nu] G[q][e][a][mn]  (u = NULL: Gnu = G transposed)
 // pack.hip: operands of packed FP32 products (PackedOperands)
 ephw_status pack_phases(const double* pts, int64_t n, const int32_t* R, const double* w, int64_t nr, float scale,
                         void* out, hipStream_t s);
 ephw_status pack_columns(const void* src, int64_t K, int64_t N, int64_t ld_src, void* out, float* inv_scale,
                          hipStream_t s);
+// Gnu[e][q][nu][mn] (q_major: [q][e]...) = sum_a u[q][a][nu] G[q][e][a][mn]
+// (u = NULL: Gnu = G transposed)
 ephw_status mode_rotate(int prec, const void* G, const void* u, void* Gnu, int64_t ne, int qb,
-                        int nm, int64_t nw2, hipStream_t s);
+                        int nm, int64_t nw2, hipStream_t s, bool q_major = false);
 
 struct BandRotateArgs {
   const void* W;          // [nk_tile][qb][nm][nw][nw]  (Re-GEMM output, row stride qb*nm*nw*nw)

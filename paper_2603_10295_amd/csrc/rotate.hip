@@ -54,7 +54,7 @@ constexpr int kModeReg = 24;
 template <typename T>
 __device__ __forceinline__ void mode_rotate_body(const T* __restrict__ G, const T* __restrict__ u,
                                                  T* __restrict__ Gnu, int64_t ne, int qb, int nm,
-                                                 int64_t nw2, int q, int64_t bx, T* us) {
+                                                 int64_t nw2, int q, int64_t bx, T* us, bool q_major = false) {
   const int64_t E = (int64_t)nm * nw2;
   if (u) {
     for (int i = threadIdx.x; i < nm * nm; i += blockDim.x) {
@@ -67,7 +67,7 @@ __device__ __forceinline__ void mode_rotate_body(const T* __restrict__ G, const 
   if (idx >= ne * nw2) return;
   const int64_t e = idx / nw2, mn = idx % nw2;
   const T* src = G + 2 * (((int64_t)q * ne + e) * E + mn);
-  T* dst = Gnu + 2 * ((e * qb + q) * E + mn);
+  T* dst = Gnu + 2 * ((q_major ? (int64_t)q * ne + e : e * qb + q) * E + mn);
   if (!u) {
     for (int a = 0; a < nm; ++a) {
       dst[2 * a * nw2] = src[2 * a * nw2];
@@ -102,9 +102,9 @@ __device__ __forceinline__ void mode_rotate_body(const T* __restrict__ G, const 
 
 template <typename T>
 __global__ void mode_rotate_kernel(const T* __restrict__ G, const T* __restrict__ u, T* __restrict__ Gnu,
-                                   int64_t ne, int qb, int nm, int64_t nw2) {
+                                   int64_t ne, int qb, int nm, int64_t nw2, bool q_major) {
   extern __shared__ unsigned char smem_raw[];
-  mode_rotate_body<T>(G, u, Gnu, ne, qb, nm, nw2, blockIdx.y, blockIdx.x, reinterpret_cast<T*>(smem_raw));
+  mode_rotate_body<T>(G, u, Gnu, ne, qb, nm, nw2, blockIdx.y, blockIdx.x, reinterpret_cast<T*>(smem_raw), q_major);
 }
 
 // The job whose [block_base, next block_base) holds block b: block_base
@@ -781,7 +781,7 @@ ephw_status scale_rows_by_phase(const double* phase, int64_t nq, const double* H
 }
 
 ephw_status mode_rotate(int prec, const void* G, const void* u, void* Gnu, int64_t ne, int qb, int nm,
-                        int64_t nw2, hipStream_t s) {
+                        int64_t nw2, hipStream_t s, bool q_major) {
   const int64_t cols = ne * nw2;
   if (cols <= 0 || qb <= 0) return EPHW_OK;
   const int bs = 256;
@@ -789,11 +789,11 @@ ephw_status mode_rotate(int prec, const void* G, const void* u, void* Gnu, int64
   if (prec == 0)
     hipLaunchKernelGGL(mode_rotate_kernel<double>, dim3(grid1(cols, bs), qb), dim3(bs), lds, s,
                        static_cast<const double*>(G), static_cast<const double*>(u),
-                       static_cast<double*>(Gnu), ne, qb, nm, nw2);
+                       static_cast<double*>(Gnu), ne, qb, nm, nw2, q_major);
   else
     hipLaunchKernelGGL(mode_rotate_kernel<float>, dim3(grid1(cols, bs), qb), dim3(bs), lds, s,
                        static_cast<const float*>(G), static_cast<const float*>(u),
-                       static_cast<float*>(Gnu), ne, qb, nm, nw2);
+                       static_cast<float*>(Gnu), ne, qb, nm, nw2, q_major);
   EPHW_CHECK_LAUNCH();
   return EPHW_OK;
 }

@@ -140,3 +140,30 @@ def test_rp_sum_fp64_few_rows(run, nq, box):
     got = run.phase_sum_rp(run.system(s), q, 0).reshape(nq, -1)
     mag = np.abs(ph) @ (np.abs(g.real) + np.abs(g.imag))
     assert np.all(np.abs(got - ph @ g) <= 2 * (2 * K + 4) * 2.0 ** -53 * mag)
+
+
+@pytest.mark.parametrize("prec,nw,na,box,m", [(1, 8, 2, (4, 4, 4), (2, 2, 2)), (0, 5, 1, (3, 2, 1), (3, 1, 1)),
+                                              (1, 12, 9, (3, 3, 1), (3, 3, 1)), (1, 33, 1, (2, 2, 1), (2, 1, 1))])
+def test_coarse_transform_forms(run, prec, nw, na, box, m):
+    """Eq. (6) inverts Eq. (7) in each of its forms: rotations and modes on the
+    small kernels, more than 24 modes, more than 32 bands."""
+    import torch
+    from paper_2603_10295_amd import ephw
+    from gpu_run import cplx_dtype, dev
+    s = synth.make_system(nw, na, synth.box(box), synth.box(m), [nw, 33],
+                          g_dtype=np.complex128 if prec == 0 else np.complex64)
+    k, q = synth.uniform_grid(box), synth.uniform_grid(m)
+    n = np.asarray(box)
+    ik, iq = np.rint(k * n).astype(int), np.rint(q * n).astype(int)
+    t = (ik[None] + iq[:, None]) % n
+    kqi = dev((t[..., 0] * n[1] * n[2] + t[..., 1] * n[2] + t[..., 2]).astype(np.int32))
+    h = run.system(s)
+    ks = ephw.KSet(h, dev(k), prec)
+    gb = torch.empty((len(q), len(k), s.nm, nw, nw), dtype=cplx_dtype(prec), device="cuda:0")
+    out = torch.empty(s.g.shape, dtype=cplx_dtype(prec), device="cuda:0")
+    ephw.interpolate(ks, dev(q), kq_index=kqi, flags=ephw.OUT_G, g_out=gb)
+    ephw.wannier_transform(ks, dev(q), kqi, gb, out)
+    run.ctx.check()
+    ks.close()
+    # two passes of sums and unitary rotations over at most 64 terms each way
+    assert np.abs(out.cpu().numpy() - s.g).max() <= (1e-12 if prec == 0 else 1e-5) * np.abs(s.g).max()
