@@ -87,7 +87,8 @@ inline size_t csize(int kind) { return kind == 0 ? 16 : 8; }
 // with caller-given buffers: hk [n][dim][dim] c128 and, for dim > 32, jwork of
 // jacobi_work_doubles(dim, n) doubles
 ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64_t nr, const double* mats, int dim,
-                           double* out_eps, double* out_v, double* hk, double* jwork, bool stages, hipStream_t st);
+                           double* out_eps, double* out_v, double* hk, double* jwork, bool stages, hipStream_t st,
+                           bool any_rounding = false);
 
 ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const int32_t* kq_index, int64_t q_offset,
                               uint32_t flags, void* g_out, double* band_sum, double* loss, uint64_t loss_seed,

@@ -1,0 +1,430 @@
+// Batched Hermitian eigensolver in FP64 for orders up to 32 by Householder
+// tridiagonalisation and implicit QL, for solves whose last bits are free
+// (those of jacobi.hip keep theirs): about 10 n^3 operations a matrix, where
+// the Jacobi sweeps take about 6 n rounds of all n^2 / 2 blocks.
+//
+// Reduction (reduce_kernel): a wavefront takes 64 / L matrices, L lanes each
+// (the order rounded up to 8, 16 or 32), lane r holding row r of A and of Q in
+// registers.  For each column, v and tau of H = I - tau v v^H with H x = e e1,
+// A <- H A H as a rank-2 update and Q <- Q H; v and w pass through LDS, where
+// every lane reads them as a broadcast.  The off-diagonals' phases go into Q's
+// columns.  The matrix is scaled by a power of two to entries near 1 first, so
+// no square under- or overflows.
+//
+// QL (ql_kernel; the classical implicit shifts, Bowdler, Martin, Reinsch and
+// Wilkinson 1968): the recurrence is one serial chain of some 25 dependent FP64
+// operations per rotation and about 0.9 n^2 rotations, the rotations of Q are
+// wide.  So one lane runs a matrix's recurrence for a few steps and logs them
+// in LDS, then a thread per row of Q applies the log to its row in registers.
+// (With all lanes of a group computing the recurrence alike, in one kernel with
+// the reduction, the recurrence was most of the time.)
+// 131 072 matrices (us, reduction + QL, Jacobi): n = 8: 102 + 281, 741; n = 11:
+// 336 + 619, 2339; n = 16: 688 + 1586, 7457.  32 768 of n = 24: 936 + 1318,
+// 11 592; of n = 32: 1763 + 3579, 33 699.  The QL of a few matrices is its chain
+// alone (n = 8: 40 us, n = 16: 130).
+#include "kernels.h"
+
+namespace ephw {
+namespace {
+
+// Reduction: N padded order, L lanes per matrix
+template <int N, int L>
+struct TriShape {
+  static constexpr int G = 64 / L;              // matrices per wavefront
+  static constexpr int waves = 4;               // per workgroup
+  static constexpr size_t wave_elems = (size_t)G * 3 * N;   // double2: v, w, column phases
+};
+
+// QL: M matrices per workgroup, a thread per row; T steps per log
+template <int N>
+struct QlShape {
+  static constexpr int M = N <= 16 ? 16 : 8;
+  static constexpr int T = N <= 16 ? 8 : 4;
+  static constexpr int CB = 4;                  // columns per block of the phase search
+  static constexpr size_t log_elems = (size_t)M * T * N, stage_elems = (size_t)M * N * CB;
+  static constexpr size_t shared = log_elems > stage_elems ? log_elems : stage_elems;
+};
+
+template <int L>
+__device__ __forceinline__ double group_sum(double v) {
+#pragma unroll
+  for (int off = 1; off < L; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+template <int L>
+__device__ __forceinline__ double group_max(double v) {
+#pragma unroll
+  for (int off = 1; off < L; off <<= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+
+// 1/sqrt(x) for x > 0 in the normal range: the hardware estimate and one step
+// of third order (e is the estimate's relative error doubled, near 2^-25)
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// 1/x, |x| in the normal range, likewise
+__device__ __forceinline__ double rcp_nr(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y * e, 1.0 + e, y);
+}
+
+// the power of two that takes the largest entry to [1, 2)
+__device__ __forceinline__ int scale_exponent(double big) {
+  const int ex = big > 0.0 && big < 1.7e308 ? ilogb(big) : 0;
+  return ex < -1000 ? -1000 : ex;
+}
+
+// H -> d in eps, |e| and the scale's exponent in the first n + 1 doubles of H's
+// own matrix, Q in V
+template <int N, int L>
+__global__ void __launch_bounds__((64 * TriShape<N, L>::waves))
+    reduce_kernel(double2* __restrict__ H, int64_t batch, int n, double* __restrict__ eps, double2* __restrict__ V) {
+  using S = TriShape<N, L>;
+  __shared__ double2 lds[S::waves * S::wave_elems];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane % L, g = lane / L;          // row, matrix of the wave
+  double2* sv = lds + wave * S::wave_elems + g * 3 * N;   // v
+  double2* sw = sv + N;
+  double2* sd = sw + N;
+  const int64_t b = ((int64_t)blockIdx.x * S::waves + wave) * S::G + g;
+  const bool live = b < batch;                   // a group past the end reduces a zero matrix
+  double2* h = H + (live ? b : 0) * n * n;
+  double* off = reinterpret_cast<double*>(h);
+
+  double2 a[N], q[N];
+  double big = 0.0;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    a[c] = live && r < n && c < n ? h[r * n + c] : make_double2(0.0, 0.0);
+    if (c == r) a[c].y = 0.0;
+    big = fmax(big, fmax(fabs(a[c].x), fabs(a[c].y)));
+    q[c] = make_double2(c == r ? 1.0 : 0.0, 0.0);
+  }
+  big = group_max<L>(big);
+  const int ex = scale_exponent(big);
+  const double scale = ldexp(1.0, -ex);
+#pragma unroll
+  for (int c = 0; c < N; ++c) a[c] = make_double2(a[c].x * scale, a[c].y * scale);
+
+  double2 delta = make_double2(1.0, 0.0);        // phase of Q's column k
+  double dr = 0.0, er = 0.0;                     // d and |e| of this lane's index
+#pragma unroll 1
+  for (int k = 0; k < n; ++k) {
+    // row k in LDS: lane r reads A[r][k] as its conjugate
+    wave_sync();
+    if (r == k) {
+#pragma unroll
+      for (int c = 0; c < N; ++c) sv[c] = a[c];
+    }
+    wave_sync();
+    const double2 row = r < N ? sv[r] : make_double2(0.0, 0.0);
+    const double2 alpha = k + 1 < n ? make_double2(sv[k + 1].x, -sv[k + 1].y) : make_double2(0.0, 0.0);
+    double2 v = make_double2(0.0, 0.0);
+    if (r > k + 1 && r < n) v = make_double2(row.x, -row.y);
+    const double rest = group_sum<L>(v.x * v.x + v.y * v.y);
+    const double a2 = alpha.x * alpha.x + alpha.y * alpha.y;
+    // columns below 1e-140 of the matrix count as zero: their squares are near
+    // the end of the range
+    const bool has = a2 > 1e-280, reflect = rest > 1e-280;
+    const double ia = has ? rsqrt_nr(a2) : 0.0, aabs = a2 * ia;
+    const double2 ph = has ? make_double2(alpha.x * ia, alpha.y * ia) : make_double2(1.0, 0.0);
+    double norm = aabs, tau = 0.0, sgn = 1.0;
+    if (reflect) {
+      const double t = a2 + rest, in = rsqrt_nr(t);
+      norm = t * in;
+      tau = in * rcp_nr(norm + aabs);
+      sgn = -1.0;
+      if (r == k + 1) v = make_double2(alpha.x + ph.x * norm, alpha.y + ph.y * norm);
+    } else {
+      v = make_double2(0.0, 0.0);
+    }
+    if (r == k) {
+      dr = row.x;
+      er = k + 1 < n ? norm : 0.0;               // |e|: e = sgn ph norm
+      sd[k] = delta;
+    }
+    // delta_{k+1} = delta_k e / |e|
+    delta = make_double2(sgn * (delta.x * ph.x - delta.y * ph.y), sgn * (delta.x * ph.y + delta.y * ph.x));
+    wave_sync();                                 // everyone has read row k
+    if (r < N) sv[r] = v;
+    wave_sync();
+    // v is zero up to row k: blocks of columns before it are left out
+    double2 p = make_double2(0.0, 0.0), s = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int c0 = 0; c0 < N; c0 += 4) {
+      if (c0 + 3 <= k) continue;
+#pragma unroll
+      for (int c = c0; c < c0 + 4; ++c) {
+        const double2 vc = sv[c];
+        p.x = fma(a[c].x, vc.x, fma(-a[c].y, vc.y, p.x));
+        p.y = fma(a[c].x, vc.y, fma(a[c].y, vc.x, p.y));
+        s.x = fma(q[c].x, vc.x, fma(-q[c].y, vc.y, s.x));
+        s.y = fma(q[c].x, vc.y, fma(q[c].y, vc.x, s.y));
+      }
+    }
+    p = make_double2(tau * p.x, tau * p.y);
+    s = make_double2(tau * s.x, tau * s.y);
+    const double kk = 0.5 * tau * group_sum<L>(v.x * p.x + v.y * p.y);
+    const double2 w = make_double2(p.x - kk * v.x, p.y - kk * v.y);
+    if (r < N) sw[r] = w;
+    wave_sync();
+#pragma unroll
+    for (int c0 = 0; c0 < N; c0 += 4) {
+      if (c0 + 3 <= k) continue;
+#pragma unroll
+      for (int c = c0; c < c0 + 4; ++c) {
+        const double2 vc = sv[c], wc = sw[c];
+        // a -= v conj(w_c) + w conj(v_c); q -= s conj(v_c)
+        a[c].x = fma(-v.x, wc.x, fma(-v.y, wc.y, fma(-w.x, vc.x, fma(-w.y, vc.y, a[c].x))));
+        a[c].y = fma(-v.y, wc.x, fma(v.x, wc.y, fma(-w.y, vc.x, fma(w.x, vc.y, a[c].y))));
+        q[c].x = fma(-s.x, vc.x, fma(-s.y, vc.y, q[c].x));
+        q[c].y = fma(-s.y, vc.x, fma(s.x, vc.y, q[c].y));
+      }
+    }
+  }
+  wave_sync();
+  if (!live || r >= n) return;
+  eps[b * n + r] = dr;
+  off[r] = er;
+  if (r == 0) off[n] = (double)ex;               // n = 1: the matrix has two doubles
+  double2* out = V + (b * n + r) * n;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    const double2 del = sd[c];
+    if (c < n) out[c] = make_double2(q[c].x * del.x - q[c].y * del.y, q[c].x * del.y + q[c].y * del.x);
+  }
+}
+
+// (d, e, Q) -> eigenvalues ascending (ties by index) and their vectors, each
+// with its largest entry real positive
+template <int N>
+__global__ void __launch_bounds__((QlShape<N>::M * N))
+    ql_kernel(const double2* __restrict__ H, int64_t batch, int n, double* __restrict__ eps, double2* __restrict__ V,
+              uint32_t* status) {
+  using S = QlShape<N>;
+  constexpr int M = S::M, T = S::T, CB = S::CB;
+  __shared__ double2 shared[S::shared];
+  __shared__ double sdp[(N + 1) * M], sep[(N + 1) * M];   // [index][matrix], index -1 is read and not used
+  double *const sd = sdp + M, *const se = sep + M;
+  __shared__ uint32_t steps[M * T];              // l | m << 16 of each logged step
+  __shared__ int rank[M * N];
+  __shared__ double2 fix[M * CB];
+  const int tid = threadIdx.x;
+  const int r = tid % n, mt = tid / n;           // row, matrix of the workgroup
+  const int64_t b0 = (int64_t)blockIdx.x * M, b = b0 + mt;
+  const bool live = mt < M && b < batch;
+  double2 z[N];
+  if (live) {
+    sd[r * M + mt] = eps[b * n + r];
+    se[r * M + mt] = reinterpret_cast<const double*>(H + b * n * n)[r];
+    const double2* in = V + (b * n + r) * n;
+#pragma unroll
+    for (int c = 0; c < N; ++c) z[c] = c < n ? in[c] : make_double2(0.0, 0.0);
+  }
+  __syncthreads();
+
+  // the recurrence's state: matrix tid of the workgroup
+  const bool owner = tid < M && b0 + tid < batch;
+  double* d = sd + tid;
+  double* e = se + tid;
+  double2* log = shared + tid * T * N;
+  uint32_t small = 1u << (n - 1);                // bit i: e[i] is negligible
+  auto negligible = [](double e, double d0, double d1) {
+    return fabs(e) <= fmax(2.220446049250313e-16 * (fabs(d0) + fabs(d1)), 1e-140);
+  };
+  if (owner)
+    for (int i = 0; i + 1 < n; ++i) small |= negligible(e[i * M], d[i * M], d[(i + 1) * M]) ? 1u << i : 0u;
+  const int limit = sweep_limit(status);
+  int l = owner ? 0 : n, iter = 0;
+  for (;;) {
+    int count = 0;
+    while (l < n && count < T) {
+      const int skip = __builtin_ctzll(~(uint64_t)(small >> l));   // eigenvalues that are done, up to 32
+      if (skip > 0 || iter >= limit) {
+        if (skip == 0) atomicOr(status, kStatusNoConv);
+        l += skip > 0 ? skip : 1;
+        iter = 0;
+        continue;
+      }
+      const int m = l + __builtin_ctz(small >> l);
+      ++iter;
+      const double dl = d[l * M], el = e[l * M];
+      double gg = 0.5 * (d[(l + 1) * M] - dl) * rcp_nr(el);
+      double dn = d[m * M];                      // d[i + 1]
+      const double h2 = fma(gg, gg, 1.0);
+      gg = dn - dl + el * rcp_nr(gg + copysign(h2 * rsqrt_nr(h2), gg));
+      double s = 1.0, c = 1.0, p = 0.0;
+      double ei = e[(m - 1) * M], di = d[(m - 1) * M], above = 0.0;   // above: d[i + 2] after this step
+      uint32_t hits = 0;
+      asm volatile("" : "+v"(di), "+v"(ei), "+v"(dn), "+v"(gg));   // the loop begins with nothing in flight
+#pragma unroll 1
+      for (int i = m - 1; i >= l; --i) {
+        // the next step's operands while this one's chain runs
+        double en = e[(i - 1) * M], dp = d[(i - 1) * M];
+        const double f = s * ei, bb = c * ei;
+        const double t = fma(f, f, gg * gg);
+        const bool zero = t < 1e-290;            // underflowed: no rotation
+        const double inv = rsqrt_nr(zero ? 1.0 : t), eo = t * inv;
+        s = f * inv;
+        c = zero ? 1.0 : gg * inv;
+        gg = dn - p;
+        const double rr = fma(di - gg, s, 2.0 * c * bb);
+        p = s * rr;
+        const double dw = gg + p;
+        gg = fma(c, rr, -bb);
+        d[(i + 1) * M] = dw;
+        e[(i + 1) * M] = eo;                     // e[m] is negligible and not read again
+        hits |= (negligible(eo, dw, above) ? 1u : 0u) << (i + 1);
+        log[count * N + i] = make_double2(c, s);
+        above = dw;
+        dn = di;
+        // (not copied before this step's results are there: the copy would wait for LDS)
+        asm volatile("" : "+v"(dp), "+v"(en) : "v"(gg), "v"(p));
+        di = dp;
+        ei = en;
+      }
+      const double dw = dn - p;
+      d[l * M] = dw;
+      e[l * M] = gg;
+      hits |= (negligible(gg, dw, above) ? 1u : 0u) << l;
+      const uint32_t inner = ((1u << m) - 1) & ~((1u << l) - 1);
+      small = (small & ~inner) | (hits & inner);
+      steps[tid * T + count] = (uint32_t)l | (uint32_t)m << 16;
+      ++count;
+    }
+    if (tid < M)
+      for (int t = count; t < T; ++t) steps[tid * T + t] = 0;
+    const bool more = __syncthreads_or(l < n);
+    if (live) {
+#pragma unroll 1
+      for (int t = 0; t < T; ++t) {
+        const uint32_t lm = steps[mt * T + t];
+        const int lo = lm & 0xffff, hi = lm >> 16;
+        const double2* cs = shared + (mt * T + t) * N;
+#pragma unroll
+        for (int i0 = N - 4; i0 >= 0; i0 -= 4) {
+          if (!__any(lo < i0 + 4 && hi > i0)) continue;
+#pragma unroll
+          for (int i = i0 + 3; i >= i0; --i) {
+            if (i == N - 1) continue;
+            // outside the step's range the log is another step's: no rotation
+            double2 x = cs[i];
+            const bool in = i >= lo && i < hi;
+            x.x = in ? x.x : 1.0;
+            x.y = in ? x.y : 0.0;
+            const double2 z0 = z[i], z1 = z[i + 1];
+            z[i + 1] = make_double2(fma(x.y, z0.x, x.x * z1.x), fma(x.y, z0.y, x.x * z1.y));
+            z[i] = make_double2(fma(x.x, z0.x, -(x.y * z1.x)), fma(x.x, z0.y, -(x.y * z1.y)));
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (!more) break;
+  }
+
+  // ascending order
+  if (live) {
+    const double mine = sd[r * M + mt];
+    int place = 0;
+    bool order = true;                           // NaN eigenvalues (a matrix that is not finite) would share ranks
+    for (int j = 0; j < n; ++j) {
+      const double o = sd[j * M + mt];
+      order = order && o == o;
+      place += (o < mine) || (o == mine && j < r);
+    }
+    if (!order) place = r;
+    rank[mt * N + r] = place;
+    const double* tail = reinterpret_cast<const double*>(H + b * n * n);
+    eps[b * n + place] = ldexp(mine, (int)tail[n]);
+  }
+  // phases, CB columns at a time: rows to LDS, a thread per column
+#pragma unroll
+  for (int c0 = 0; c0 < N; c0 += CB) {
+    __syncthreads();
+    if (live) {
+#pragma unroll
+      for (int c = 0; c < CB; ++c) shared[(mt * N + r) * CB + c] = z[c0 + c];
+    }
+    __syncthreads();
+    if (tid < M * CB && b0 + tid / CB < batch) {
+      double best = -1.0;
+      double2 bv = make_double2(1.0, 0.0);
+      for (int j = 0; j < n; ++j) {
+        const double2 x = shared[(tid / CB * N + j) * CB + tid % CB];
+        const double m2 = x.x * x.x + x.y * x.y;
+        if (m2 > best) {
+          best = m2;
+          bv = x;
+        }
+      }
+      const double mag = sqrt(best);
+      fix[tid] = mag > 0.0 ? make_double2(bv.x / mag, -bv.y / mag) : make_double2(1.0, 0.0);
+    }
+    __syncthreads();
+    if (live) {
+      double2* out = V + (b * n + r) * n;
+#pragma unroll
+      for (int c = 0; c < CB; ++c) {
+        const double2 x = z[c0 + c], y = fix[mt * CB + c];
+        if (c0 + c < n) out[rank[mt * N + c0 + c]] = make_double2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x);
+      }
+    }
+  }
+}
+
+template <int N, int L>
+ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s) {
+  using S = TriShape<N, L>;
+  const int64_t grid = ceil_div(batch, (int64_t)S::waves * S::G), gridq = ceil_div(batch, QlShape<N>::M);
+  if (grid > 0x7fffffff || gridq > 0x7fffffff) {
+    set_error("tridiag_eigh: too many matrices for one launch");
+    return EPHW_EUNSUPPORTED;
+  }
+  // every column's phase needs a thread as well as every row
+  const int rows = QlShape<N>::M * (n > QlShape<N>::CB ? n : QlShape<N>::CB);
+  hipLaunchKernelGGL((reduce_kernel<N, L>), dim3((unsigned)grid), dim3(64 * S::waves), 0, s,
+                     reinterpret_cast<double2*>(H), batch, n, eps, reinterpret_cast<double2*>(V));
+  EPHW_CHECK_LAUNCH();
+  hipLaunchKernelGGL((ql_kernel<N>), dim3((unsigned)gridq), dim3((unsigned)((rows + 63) / 64 * 64)), 0, s,
+                     reinterpret_cast<const double2*>(H), batch, n, eps, reinterpret_cast<double2*>(V), status);
+  EPHW_CHECK_LAUNCH();
+  return EPHW_OK;
+}
+
+}  // namespace
+
+// Up to order 6 the two are level (n = 3: 82 us by Jacobi and 99 here at 131 072
+// matrices, n = 6: 280 and 261).  From 7 to 16 a call that leaves the chip idle
+// is Jacobi's, whose rounds are the shorter chain: n = 8, 4096 matrices 54 and
+// 57 us; n = 11, 1024: 81 and 90, 4096: 104 and 94; n = 16, 1024: 117 and 164,
+// 4096: 289 and 169; n^3 x matrices is near 4 million where they meet.  Above 16
+// this one is ahead at every count (n = 24: 452 and 306 us at 64 matrices).
+bool tridiag_better(int n, int64_t batch) {
+  return n > 16 ? n <= 32 : n > 6 && (int64_t)n * n * n * batch >= 4000000;
+}
+
+ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status,
+                         hipStream_t s) {
+  if (batch <= 0) return EPHW_OK;
+  if (n < 1 || n > 32) {
+    set_error("tridiag_eigh: matrix order must be in [1, 32]");
+    return EPHW_EUNSUPPORTED;
+  }
+  if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
+    set_error("tridiag_eigh: matrices and eigenvectors must be 16-byte aligned complex128 arrays");
+    return EPHW_EINVAL;
+  }
+  if (n <= 8) return launch<8, 8>(H, batch, n, eps, V, status, s);
+  if (n <= 12) return launch<12, 16>(H, batch, n, eps, V, status, s);
+  if (n <= 16) return launch<16, 16>(H, batch, n, eps, V, status, s);
+  if (n <= 24) return launch<24, 32>(H, batch, n, eps, V, status, s);
+  return launch<32, 32>(H, batch, n, eps, V, status, s);
+}
+
+}  // namespace ephw

@@ -27,3 +27,42 @@ def test_orders(nw):
         assert np.abs(vec[i].conj().T @ vec[i] - np.eye(nw)).max() <= 8 * nw * 2.0 ** -53 + 1e-14
         top = np.take_along_axis(vec[i], np.abs(vec[i]).argmax(0)[None], 0)[0]
         assert np.all(top.real > 0) and np.abs(top.imag).max() <= 1e-15
+
+
+@pytest.mark.parametrize("nw", [7, 8, 9, 11, 12, 13, 16, 17, 23, 24, 25, 31, 32])
+def test_tridiagonal_orders(nw):
+    """The k+q eigensolves of the calls whose rounding is free, at every padded
+    order's edges, a last wavefront that is not full, and a block-diagonal
+    H(k) (reflections and QL rotations that vanish) with a repeated
+    eigenvalue: bands against LAPACK, g by block sums against the oracle."""
+    import dataclasses
+    from gpu_run import Runner
+    from paper_2603_10295_amd import ephw
+    run = Runner()
+    s = synth.make_system(nw, 1, synth.box((3, 2, 1)), synth.box((2, 1, 1)), [nw, 6])
+    rng = np.random.default_rng(nw)
+    # up to order 16 it takes n^3 x matrices of 4 million
+    nk = 7 if nw > 16 else 4000000 // (5 * nw ** 3) + 2
+    k, q = rng.random((nk, 3)), rng.random((5, 3))
+    h = s.h_r.copy()
+    h[:, 0, :] = h[:, :, 0] = h[:, 4, :] = h[:, :, 4] = 0   # two uncoupled equal bands
+    zero = np.flatnonzero(~s.r_h.any(1))[0]
+    h[zero, 0, 0] = h[zero, 4, 4] = 0.7
+    for hr in (s.h_r, h, 1e-160 * s.h_r, 0 * h):
+        t = dataclasses.replace(s, h_r=hr)
+        got = run.interpolate(run.system(t), k, q, 0, flags=ephw.OUT_G)
+        ref = oracle.interpolate(t, k, q, return_all=True)
+        scale = max(np.abs(ref["eps_kq"]).max(), 1e-300)
+        assert np.abs(got["eps_kq"] - ref["eps_kq"]).max() <= (1e-14 + 8 * nw * 2.0 ** -53) * nw * scale
+        if hr is s.h_r:
+            a = oracle.block_sums(np.abs(got["g"]) ** 2, ref["eps_kq"], ref["eps_k"], ref["lam"])
+            b = oracle.block_sums(np.abs(ref["ghat"]) ** 2, ref["eps_kq"], ref["eps_k"], ref["lam"])
+            assert oracle.compare_block_sums(a, b)[0] <= 1e-10
+        # the rotations stay unitary whatever the spectrum: the sum over all bands
+        # (the V(k) in it come from the k-set's own solves, whose squares leave
+        # the FP64 range at 1e-160: eigenvalues only there)
+        if 0 < scale < 1e-150 and hr.any():
+            continue
+        ta = (np.abs(got["g"]) ** 2).sum((-2, -1))
+        tb = (np.abs(ref["ghat"]) ** 2).sum((-2, -1))
+        assert np.abs(ta - tb).max() <= 1e-12 * tb.max()
