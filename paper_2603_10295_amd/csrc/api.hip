@@ -247,21 +247,24 @@ ephw_status ephw_system_load(ephw_ctx* ctx, const ephw_system_desc* d, ephw_syst
     for (int64_t i = 0; i < d->ne; ++i) s->dir_e[dd] = s->dir_e[dd] || d->r_e[3 * i + dd] != 0;
     for (int64_t i = 0; i < d->np; ++i) s->dir_p[dd] = s->dir_p[dd] || d->r_p[3 * i + dd] != 0;
   }
-  {
-    // packed phases keep every weight's leading 22 bits only within a range of
-    // 2^8 of the largest (smaller ones would lose bits to the FP16 range)
+  // packed phases keep every weight's leading 22 bits only within a range of
+  // 2^8 of the largest (smaller ones would lose bits to the FP16 range)
+  auto pack_scale = [](const double* weight, int64_t n) {
     double big = 0.0, small = HUGE_VAL;
     bool finite = true;
-    for (int64_t i = 0; i < d->ne; ++i) {
-      const double w = d->w_e ? fabs(d->w_e[i]) : 1.0;
+    for (int64_t i = 0; i < n; ++i) {
+      const double w = weight ? fabs(weight[i]) : 1.0;
       finite = finite && std::isfinite(w);
       big = fmax(big, w);
       if (w > 0.0) small = fmin(small, w);
     }
+    if (!finite || !(big > 0.0) || big > 256.0 * small) return 0.f;
     int ex = 0;
-    if (finite && big > 0.0 && big <= 256.0 * small) (void)frexp(big, &ex);   // big <= 2^ex
-    if (finite && big > 0.0 && big <= 256.0 * small && ex > -60 && ex < 60) s->pack_scale = (float)ldexp(1.0, 14 - ex);
-  }
+    (void)frexp(big, &ex);   // big <= 2^ex
+    return ex > -60 && ex < 60 ? (float)ldexp(1.0, 14 - ex) : 0.f;
+  };
+  s->pack_scale = pack_scale(d->w_e, d->ne);
+  s->pack_scale_p = pack_scale(d->w_p, d->np);
   if ((st = weights(&s->w_p, d->w_p, d->np)) != EPHW_OK) return fail(st);
   if ((st = weights(&s->w_h, d->w_h, d->nh)) != EPHW_OK) return fail(st);
   if ((st = weights(&s->w_c, d->w_c, d->nc)) != EPHW_OK) return fail(st);

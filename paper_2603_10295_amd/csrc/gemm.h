@@ -73,11 +73,16 @@ struct PackedOperands {
   int64_t lda = 0, ldb = 0;        // packed_ld of M and N
   float inv_a = 1.f;               // 1 / the scale of A's values
   const float* inv_b = nullptr;    // [N], 1 / the scale of each column
+  // grouped products: the rows of A are picked by each problem's index list
+  // from `nrows` kept row by row (pack.hip), packed_row_bytes each
+  int64_t nrows = 0;
+  uint32_t* status = nullptr;      // kStatusIndex for an index outside [0, nrows)
 };
 // rows a packed operand is padded to, its groups of eight k, its bytes
 inline int64_t packed_ld(int64_t rows) { return ceil_div(rows, 128) * 128; }
 inline int64_t packed_groups(int64_t K) { return ceil_div(K, 16) * 2; }
 inline int64_t packed_bytes(int64_t rows, int64_t K) { return packed_groups(K) * 4 * packed_ld(rows) * 16; }
+inline int64_t packed_row_bytes(int64_t K) { return packed_groups(K) * 64; }
 
 // All sizes, leading dimensions, strides and offsets count complex elements.
 // Operands are interleaved complex (T re, T im), T = double (prec 0) or float
@@ -153,6 +158,9 @@ struct GroupProblem {
   int32_t cfg = 0;
   int64_t tiles_m = 0, tiles_n = 0, tile_base = 0;  // set by cgemm_grouped_layout
   int32_t flat = 0;   // set by cgemm_grouped_layout: both operands' extents fit 32-bit byte offsets
+  // packed products (in place of A and B): the problem's M row indices, its first column of B
+  const int32_t* rows = nullptr;
+  int64_t col0 = 0;
 };
 void cgemm_tile_shape(int prec, int cfg, int* bm, int* bn);
 // workgroups of the grouped kernel one CU holds at once (its persistent grid
@@ -172,6 +180,11 @@ int64_t cgemm_grouped_layout(int prec, GroupProblem* probs, int n);
 constexpr int kGroupQueues = 8;
 ephw_status cgemm_grouped(int prec, int cfg, const GroupProblem* d_probs, int n, int64_t total_tiles, int grid,
                           int* queue, hipStream_t stream);
+// The same for FP32 problems on packed operands, one K for all, laid out with
+// cfg 2 (tiles of 128 x 128): C = A[rows] B[:, col0 : col0 + N]
+bool cgemm_grouped_packable(int64_t nrows, int64_t columns, int64_t K);
+ephw_status cgemm_grouped_packed(const PackedOperands& P, int64_t K, const GroupProblem* d_probs, int n,
+                                 int64_t total_tiles, hipStream_t stream);
 ephw_status cgemm_grouped_reset(int* queues, int count, hipStream_t stream);
 
 }  // namespace ephw

@@ -1636,6 +1636,24 @@ int64_t cgemm_grouped_layout(int prec, GroupProblem* probs, int n) {
   return base;
 }
 
+bool cgemm_grouped_packable(int64_t nrows, int64_t columns, int64_t K) {
+  constexpr int64_t lim = ((int64_t)1 << 32) - 65536;
+  return K >= kSplitMinK && nrows * packed_row_bytes(K) < lim && packed_bytes(columns, K) < lim;
+}
+
+ephw_status cgemm_grouped_packed(const PackedOperands& P, int64_t K, const GroupProblem* d_probs, int n,
+                                 int64_t total_tiles, hipStream_t stream) {
+  if (n <= 0 || total_tiles <= 0) return EPHW_OK;
+  if (total_tiles > 0x7fffffffll) {
+    set_error("cgemm_grouped_packed: too many tiles");
+    return EPHW_EUNSUPPORTED;
+  }
+  hipLaunchKernelGGL(cgemm_packed_grouped_kernel, dim3((unsigned)total_tiles), dim3(256), 0, stream, P, K, d_probs, n,
+                     total_tiles);
+  EPHW_CHECK_LAUNCH();
+  return EPHW_OK;
+}
+
 ephw_status cgemm_grouped(int prec, int cfg, const GroupProblem* d_probs, int n, int64_t total_tiles, int grid,
                           int* queue, hipStream_t stream) {
   if (n <= 0 || total_tiles <= 0) return EPHW_OK;

@@ -158,9 +158,9 @@ struct ephw_system {
   double* ism = nullptr;      // [nm] 1/sqrt(M_kappa) per mode index
   void* g = nullptr;
   bool dir_e[3] = {false, false, false}, dir_p[3] = {false, false, false};   // lattice directions Re and Rp extend in
-  // scale of the packed Re phases w_R e^{2 pi i k.R} (pack.hip), a power of two
-  // with |w_R| scale <= 2^14, or 0 where the weights do not allow packing
-  float pack_scale = 0.f;
+  // scales of the packed phases w_R e^{2 pi i k.R} of Re and of Rp (pack.hip),
+  // powers of two with |w_R| scale <= 2^14, or 0 where the weights do not allow packing
+  float pack_scale = 0.f, pack_scale_p = 0.f;
   int32_t q_batch = 0;
   int32_t k_tile = 0;
   int64_t bytes = 0;

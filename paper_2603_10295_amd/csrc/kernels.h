@@ -75,10 +75,12 @@ ephw_status scale_rows_by_phase(const double* phase, int64_t nq, const double* H
                                 int64_t nab, double* B, hipStream_t s);
 
 // pack.hip: operands of packed FP32 products (PackedOperands)
+// (by_row: the layout of PackedOperands::rows)
 ephw_status pack_phases(const double* pts, int64_t n, const int32_t* R, const double* w, int64_t nr, float scale,
-                        void* out, hipStream_t s);
+                        void* out, hipStream_t s, bool by_row = false);
+// columns of `batch` matrices stride_src values apart, one operand of batch * N columns
 ephw_status pack_columns(const void* src, int64_t K, int64_t N, int64_t ld_src, void* out, float* inv_scale,
-                         hipStream_t s);
+                         hipStream_t s, int64_t batch = 1, int64_t stride_src = 0);
 // Gnu[e][q][nu][mn] (q_major: [q][e]...) = sum_a u[q][a][nu] G[q][e][a][mn]
 // (u = NULL: Gnu = G transposed)
 ephw_status mode_rotate(int prec, const void* G, const void* u, void* Gnu, int64_t ne, int qb,

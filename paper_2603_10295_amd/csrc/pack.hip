@@ -6,7 +6,10 @@
 //   [k / 8][plane][row][k % 8],
 // rows padded to a multiple of 128 (their contents are never stored) and k to
 // a multiple of 16 with zeros.  The 8 bytes a complex value takes are those of
-// complex64.
+// complex64.  Phases whose rows a product picks through an index list are kept
+// row by row instead, [row][k / 8][plane][k % 8]: the eight planes of a 16-deep
+// slab are then the 128 bytes of one cache line, where rows picked from the
+// planes would each take a line of their own.
 #include "gemm.h"
 #include "kernels.h"
 
@@ -38,7 +41,7 @@ __device__ __forceinline__ void store_planes(const float (&x)[16], uint4* dst, i
 // FP64 and not rounded to complex64 in between), times `scale`
 __global__ void pack_phase_kernel(const double* __restrict__ pts, int64_t n, const int32_t* __restrict__ R,
                                   const double* __restrict__ w, int64_t nr, float scale, uint4* __restrict__ out,
-                                  int64_t ld) {
+                                  int64_t plane, int64_t row, int64_t group) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, k8 = blockIdx.y;
   if (i >= n) return;
   const double px = pts[3 * i], py = pts[3 * i + 1], pz = pts[3 * i + 2];
@@ -60,11 +63,11 @@ __global__ void pack_phase_kernel(const double* __restrict__ pts, int64_t n, con
     hi[1][e / 2][e & 1] = hs;
     lo[1][e / 2][e & 1] = (_Float16)(float)(sn - (double)hs);
   }
-  uint4* dst = out + k8 * 4 * ld + i;
+  uint4* dst = out + k8 * group + i * row;
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
-    dst[(2 * part) * ld] = __builtin_bit_cast(uint4, hi[part]);
-    dst[(2 * part + 1) * ld] = __builtin_bit_cast(uint4, lo[part]);
+    dst[(2 * part) * plane] = __builtin_bit_cast(uint4, hi[part]);
+    dst[(2 * part + 1) * plane] = __builtin_bit_cast(uint4, lo[part]);
   }
 }
 
@@ -78,17 +81,20 @@ __device__ __forceinline__ float column_scale(float m) {
   return __uint_as_float((uint32_t)(127 + e) << 23);
 }
 
-// Columns of the row-major complex64 src [K][N] (N contiguous).  A workgroup
+// Columns of row-major complex64 matrices [K][N] (N contiguous).  A workgroup
 // takes 64 columns: its waves first find each column's largest component (the
 // second read of the columns is then served by the caches), then scale and
 // pack eight k at a time.  Memory bound: src is read twice, once from HBM.
 __global__ void __launch_bounds__(256)
-    pack_columns_kernel(const float* __restrict__ src, int64_t K, int64_t N, int64_t ld_src, uint4* __restrict__ out,
-                        int64_t ld, float* __restrict__ inv_scale) {
+    pack_columns_kernel(const float* __restrict__ src, int64_t K, int64_t N, int64_t ld_src, int64_t stride_src,
+                        uint4* __restrict__ out, int64_t ld, float* __restrict__ inv_scale) {
   __shared__ float red[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t n = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t blocks = (N + 63) / 64, b = blockIdx.x / blocks, n = (blockIdx.x % blocks) * 64 + lane;
   const bool ok = n < N;
+  src += 2 * b * stride_src;
+  out += b * N;
+  inv_scale += b * N;
   const float2* col = reinterpret_cast<const float2*>(src) + (ok ? n : N - 1);
   float m = 0.f;
   bool bad = false;
@@ -120,25 +126,31 @@ __global__ void __launch_bounds__(256)
 }  // namespace
 
 ephw_status pack_phases(const double* pts, int64_t n, const int32_t* R, const double* w, int64_t nr, float scale,
-                        void* out, hipStream_t s) {
+                        void* out, hipStream_t s, bool by_row) {
   if (n <= 0 || nr <= 0) return EPHW_OK;
   const int64_t groups = packed_groups(nr);
+  const int64_t plane = by_row ? 1 : packed_ld(n), row = by_row ? 4 * groups : 1, group = 4 * plane;
   for (int64_t g0 = 0; g0 < groups; g0 += 65535) {
     // nr past the groups of this launch is cut by the group index itself
     const int64_t ng = groups - g0 < 65535 ? groups - g0 : 65535;
     hipLaunchKernelGGL(pack_phase_kernel, dim3((unsigned)ceil_div(n, 256), (unsigned)ng), dim3(256), 0, s, pts, n,
                        R + 3 * 8 * g0, w + 8 * g0, nr - 8 * g0, scale,
-                       static_cast<uint4*>(out) + g0 * 4 * packed_ld(n), packed_ld(n));
+                       static_cast<uint4*>(out) + g0 * group, plane, row, group);
     EPHW_CHECK_LAUNCH();
   }
   return EPHW_OK;
 }
 
 ephw_status pack_columns(const void* src, int64_t K, int64_t N, int64_t ld_src, void* out, float* inv_scale,
-                         hipStream_t s) {
-  if (K <= 0 || N <= 0) return EPHW_OK;
-  hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)ceil_div(N, 64)), dim3(256), 0, s,
-                     static_cast<const float*>(src), K, N, ld_src, static_cast<uint4*>(out), packed_ld(N), inv_scale);
+                         hipStream_t s, int64_t batch, int64_t stride_src) {
+  if (K <= 0 || N <= 0 || batch <= 0) return EPHW_OK;
+  if (batch * ceil_div(N, 64) > 0x7fffffff) {
+    set_error("pack_columns: too many columns for one launch");
+    return EPHW_EUNSUPPORTED;
+  }
+  hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)(batch * ceil_div(N, 64))), dim3(256), 0, s,
+                     static_cast<const float*>(src), K, N, ld_src, stride_src, static_cast<uint4*>(out),
+                     packed_ld(batch * N), inv_scale);
   EPHW_CHECK_LAUNCH();
   return EPHW_OK;
 }

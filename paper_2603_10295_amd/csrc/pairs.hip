@@ -17,6 +17,11 @@
 // pairs), and the band rotations V(k+q)^dagger W V(k) and the epilogues run
 // per pair in the band-rotation kernel's pair mode.  Outputs are indexed by
 // pair, in the order of the list.
+//
+// FP32 calls whose rounding is free (see GemmParams) run the per-group sums,
+// and by k the sum before them, on packed operands (pack.hip) where enough rows
+// share a packed column.  The phase rows of a group are then picked by the
+// product's loads and never gathered.
 #include <algorithm>
 #include <cstring>
 
@@ -72,8 +77,10 @@ __global__ void gather_q_kernel(const double* __restrict__ q, const int32_t* __r
 }
 
 // Mode vectors per pair: out[p][nu][e] = sum_a W[p][a][e] u(q_p)[a][nu]
-// (e over the Nw^2 band pairs), one thread per (pair, e).
-template <typename T>
+// (e over the Nw^2 band pairs), one thread per (pair, e).  NM > 0: that many
+// modes, the thread's values of W read once and held in registers (six modes,
+// Nw = 8, 320 000 pairs: 460 us; reading them again for every mode 990).
+template <typename T, int NM>
 __global__ void pair_mode_rotate_kernel(const T* __restrict__ W, const T* __restrict__ u,
                                         const int32_t* __restrict__ pair_q, int64_t nq, int64_t npairs, int nm,
                                         int nw2, T* __restrict__ out, uint32_t* status) {
@@ -89,6 +96,20 @@ __global__ void pair_mode_rotate_kernel(const T* __restrict__ W, const T* __rest
   const T* w = W + 2 * (p * nm * nw2 + e);
   const T* uq = u + 2 * q * nm * nm;
   T* o = out + 2 * (p * nm * nw2 + e);
+  if constexpr (NM > 0) {
+    cplx<T> x[NM];
+#pragma unroll
+    for (int a = 0; a < NM; ++a) x[a] = cplx<T>{w[2 * a * nw2], w[2 * a * nw2 + 1]};
+#pragma unroll
+    for (int v = 0; v < NM; ++v) {
+      cplx<T> acc{0, 0};
+#pragma unroll
+      for (int a = 0; a < NM; ++a) cfma(acc, x[a], cplx<T>{uq[2 * (a * NM + v)], uq[2 * (a * NM + v) + 1]});
+      o[2 * v * nw2] = acc.re;
+      o[2 * v * nw2 + 1] = acc.im;
+    }
+    return;
+  }
   for (int v = 0; v < nm; ++v) {
     cplx<T> acc{0, 0};
     for (int a = 0; a < nm; ++a)
@@ -96,6 +117,19 @@ __global__ void pair_mode_rotate_kernel(const T* __restrict__ W, const T* __rest
     o[2 * v * nw2] = acc.re;
     o[2 * v * nw2 + 1] = acc.im;
   }
+}
+
+template <typename T>
+ephw_status pair_mode_rotate(const void* W, const void* u, const int32_t* pair_q, int64_t nq, int64_t npairs, int nm,
+                             int nw2, void* out, uint32_t* status, hipStream_t st) {
+  auto kernel = nm == 3   ? pair_mode_rotate_kernel<T, 3>
+                : nm == 6 ? pair_mode_rotate_kernel<T, 6>
+                : nm == 9 ? pair_mode_rotate_kernel<T, 9>
+                          : pair_mode_rotate_kernel<T, 0>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(npairs * nw2, 256)), dim3(256), 0, st, static_cast<const T*>(W),
+                     static_cast<const T*>(u), pair_q, nq, npairs, nm, nw2, static_cast<T*>(out), status);
+  EPHW_CHECK_LAUNCH();
+  return EPHW_OK;
 }
 
 // pinned host staging of at least `bytes`, once the previous call's copy from it is done
@@ -125,7 +159,7 @@ struct PairWs {
   int64_t* seg = nullptr;    // [na + 1] pair offsets of those groups
   GroupProblem* probs = nullptr;  // [na]
   int32_t* pair_idx = nullptr;    // [npairs] the group index of every pair (q by q, k by k)
-  double* qa = nullptr;      // by q: [na][3] coordinates of the active q
+  double* qa = nullptr;      // [na][3] coordinates of the active q or (packed sums) k
   void* pq = nullptr;        // T [nqp][np]: Rp phases of the q the call needs
   double *pqc = nullptr, *lam = nullptr, *e = nullptr, *hk = nullptr, *jwork = nullptr;
   void* u = nullptr;         // T [nqp][nm][nm]
@@ -134,6 +168,8 @@ struct PairWs {
   void* pg = nullptr;        // gathered phase rows of the pairs of a group chunk
   void* wc = nullptr;        // [pairs][E] second-stage sums
   void* wnu = nullptr;       // by k: [pairs][E] after the mode vectors
+  void *pa1 = nullptr, *pb1 = nullptr;   // packed operands of the Re sum by k: P_k of a chunk, g of Rp groups
+  void *pa2 = nullptr, *pb2 = nullptr;   // of the per-group sums: phase rows of every point, columns of `big`
   double* loss = nullptr;    // [pairs]
   int* queues = nullptr;     // [chunks][kGroupQueues]
   size_t bytes = 0;
@@ -144,7 +180,18 @@ struct PairPlan {
   int64_t na = 0, npairs = 0, nqp = 0;      // groups owning pairs, pairs, q points with phases
   int64_t chunk = 0, nchunk = 0, max_pairs = 0;
   size_t first_bytes = 0, big_bytes = 0, pg_row = 0;
+  bool pack1 = false, pack2 = false;        // packed Re sum by k; packed per-group sums
+  int64_t rp_group = 0;                     // Rp packed at a time
+  int64_t points = 0, depth = 0;            // of the per-group sums: points with phase rows, K
 };
+
+// A packed operand with its column scales
+size_t packed_columns_bytes(int64_t columns, int64_t K) {
+  return al256((size_t)packed_bytes(columns, K)) + (size_t)columns * 4;
+}
+float* packed_columns_inv(void* p, int64_t columns, int64_t K) {
+  return reinterpret_cast<float*>(static_cast<char*>(p) + al256((size_t)packed_bytes(columns, K)));
+}
 
 PairWs pair_layout(const ephw_system* s, int kind, const PairPlan& pl, char* base) {
   PairWs w;
@@ -160,7 +207,7 @@ PairWs pair_layout(const ephw_system* s, int kind, const PairPlan& pl, char* bas
   w.seg = reinterpret_cast<int64_t*>(take((size_t)(pl.na + 1) * 8));
   w.probs = reinterpret_cast<GroupProblem*>(take((size_t)pl.na * sizeof(GroupProblem)));
   w.pair_idx = reinterpret_cast<int32_t*>(take((size_t)pl.npairs * 4));
-  if (!pl.by_k) w.qa = reinterpret_cast<double*>(take((size_t)pl.na * 24));
+  if (!pl.by_k || pl.pack1) w.qa = reinterpret_cast<double*>(take((size_t)pl.na * 24));
   w.pq = take((size_t)pl.nqp * s->np * cs);
   w.pqc = reinterpret_cast<double*>(take((size_t)pl.nqp * s->nc * 16));
   w.lam = reinterpret_cast<double*>(take((size_t)pl.nqp * nm * 8));
@@ -169,9 +216,20 @@ PairWs pair_layout(const ephw_system* s, int kind, const PairPlan& pl, char* bas
   const int64_t jw = jacobi_work_doubles((int)nm, pl.nqp);
   if (jw > 0) w.jwork = reinterpret_cast<double*>(take((size_t)jw * 8));
   w.u = take((size_t)pl.nqp * nm * nm * cs);
-  w.first = take(pl.first_bytes);
+  const size_t pb2 = pl.pack2 ? packed_columns_bytes(pl.chunk * E, pl.depth) : 0;
+  if (pl.pack1) {
+    w.pa1 = take((size_t)packed_bytes(pl.chunk, s->ne));
+    w.pb1 = take(packed_columns_bytes(pl.rp_group * E, s->ne));
+  }
+  // by q the packed columns take the place of g(Re,q), which is dead by then
+  if (!pl.pack1) w.first = take(std::max(pl.first_bytes, pl.by_k ? 0 : pb2));
   w.big = take(pl.big_bytes);
-  w.pg = take((size_t)pl.max_pairs * pl.pg_row * cs);
+  if (pl.pack2) {
+    w.pa2 = take((size_t)(pl.points * packed_row_bytes(pl.depth)));
+    w.pb2 = pl.by_k ? take(pb2) : static_cast<char*>(w.first);
+  } else {
+    w.pg = take((size_t)pl.max_pairs * pl.pg_row * cs);
+  }
   w.wc = take((size_t)pl.max_pairs * E * cs);
   if (pl.by_k) w.wnu = take((size_t)pl.max_pairs * E * cs);
   w.loss = reinterpret_cast<double*>(take((size_t)pl.max_pairs * 8));
@@ -290,17 +348,39 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
     return EPHW_EUNSUPPORTED;
   }
 
-  const size_t need = pair_layout(s, kind, pl, nullptr).bytes;
-  EPHW_TRY(ws_need(s, WS_PAIRSET, need));
+  // Packed sums: packing a column costs 24 bytes of traffic per value, which
+  // kPackMinPoints rows repay.  By k the columns are those of every g(Rp) (once
+  // per call, or group by group for every chunk where they pass 4 GB) and then
+  // those of a chunk's G', each for its own k's pairs; by q those of a batch's
+  // G_nu.  Without memory for them the call runs unpacked.  (1000 k, 1000 Rp of
+  // 384 columns, K = 1000: the Re sums 7.2 + 1.8 ms packed, 14.8 split.)
+  const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
+  const float scale2 = by_k ? s->pack_scale_p : s->pack_scale;
+  pl.points = by_k ? nq : ks->nk;
+  pl.depth = by_k ? np : ne;
+  if (kind == 1 && any_rounding) {
+    if (by_k && s->pack_scale > 0.f && cgemm_packable(chunk, E, ne)) {
+      pl.rp_group = np;
+      while (!cgemm_packable(chunk, pl.rp_group * E, ne)) pl.rp_group = (pl.rp_group + 1) / 2;
+      pl.pack1 = (pl.rp_group == np ? pl.na : chunk) >= kPackMinPoints;
+    }
+    pl.pack2 = scale2 > 0.f && npairs / pl.na >= kPackMinPoints && npairs >= pl.points &&
+               cgemm_grouped_packable(pl.points, chunk * E, pl.depth);
+  }
+  ephw_status got = ws_need(s, WS_PAIRSET, pair_layout(s, kind, pl, nullptr).bytes);
+  if (got == EPHW_ENOMEM && (pl.pack1 || pl.pack2)) {
+    pl.pack1 = pl.pack2 = false;
+    got = ws_need(s, WS_PAIRSET, pair_layout(s, kind, pl, nullptr).bytes);
+  }
+  EPHW_TRY(got);
   const PairWs w = pair_layout(s, kind, pl, static_cast<char*>(wsp(s, WS_PAIRSET)));
 
   // one grouped-GEMM problem per group: by q, W_q = P_k[kept k] G_nu(q); by
   // k, W_k = P_q[kept q] G'(k); operand pointers relative to the chunk's buffers
   // 64 x 64 tiles: the problems have tens of rows; FP32 split tiles where the
   // rounding is free (see GemmParams)
-  const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   const int cfg_split = kind == 1 && any_rounding ? cgemm_grouped_split_cfg(by_k ? np : ne, lda_pair, ldb_pair, seg.data(), pl.na) : -1;
-  const int cfg = cfg_split > 0 ? cfg_split : 1;
+  const int cfg = pl.pack2 ? 2 : cfg_split > 0 ? cfg_split : 1;
   std::vector<GroupProblem> probs(pl.na);
   std::vector<int64_t> chunk_tiles(pl.nchunk);
   for (int64_t c = 0; c < pl.nchunk; ++c) {
@@ -318,6 +398,8 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
       P.C = static_cast<char*>(w.wc) + (size_t)(seg[i] - seg[a0]) * E * cs;
       P.ldc = E;
       P.cfg = cfg;
+      P.rows = pair_other + seg[i];
+      P.col0 = (i - a0) * E;
     }
     chunk_tiles[c] = cgemm_grouped_layout(kind, probs.data() + a0, (int)nb);
   }
@@ -346,8 +428,15 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
                          pl.na, w.qa);
       EPHW_CHECK_LAUNCH();
       qp = w.qa;
+    } else if (pl.pack1) {
+      hipLaunchKernelGGL(gather_q_kernel, dim3((unsigned)ceil_div(3 * pl.na, 256)), dim3(256), 0, st, ks->k, w.act,
+                         pl.na, w.qa);
+      EPHW_CHECK_LAUNCH();
     }
-    EPHW_TRY(phase_matrix(kind, qp, pl.nqp, s->r_p, s->w_p, s->np, w.pq, st));
+    if (pl.pack2)
+      EPHW_TRY(by_k ? pack_phases(q, nq, s->r_p, s->w_p, np, scale2, w.pa2, st, true)
+                    : pack_phases(ks->k, ks->nk, s->r_e, s->w_e, ne, scale2, w.pa2, st, true));
+    if (!by_k || !pl.pack2) EPHW_TRY(phase_matrix(kind, qp, pl.nqp, s->r_p, s->w_p, s->np, w.pq, st));
     EPHW_TRY(phase_matrix(0, qp, pl.nqp, s->r_c, s->w_c, s->nc, w.pqc, st));
   }
   EPHW_TRY(interp_eigh_ws(s, w.pqc, pl.nqp, s->nc, s->c_scaled, nm, w.lam, w.e, w.hk, w.jwork, true, st, kind == 0));
@@ -366,6 +455,19 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
   auto gather = [&](const void* src, int64_t nsrc, const int32_t* idx, int64_t cnt, int64_t width, void* dst) {
     return kind == 0 ? gather_complex_rows<double>(src, nsrc, idx, cnt, width, dst, s->ctx->status, st)
                      : gather_complex_rows<float>(src, nsrc, idx, cnt, width, dst, s->ctx->status, st);
+  };
+  // the per-group sums of chunk c, packed
+  auto packed_groups_sum = [&](int64_t c, int64_t nb) {
+    PackedOperands P;
+    P.on = true;
+    P.A = w.pa2;
+    P.nrows = pl.points;
+    P.inv_a = 1.f / scale2;
+    P.B = w.pb2;
+    P.ldb = packed_ld(nb * E);
+    P.inv_b = packed_columns_inv(w.pb2, nb * E, pl.depth);
+    P.status = s->ctx->status;
+    return cgemm_grouped_packed(P, pl.depth, w.probs + c * chunk, (int)nb, chunk_tiles[c], st);
   };
   for (int64_t c = 0; c < pl.nchunk; ++c) {
     const int64_t a0 = c * chunk, a1 = std::min(pl.na, a0 + chunk), nb = a1 - a0;
@@ -395,15 +497,23 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
                              (int)nb, nm, nw2, st));
       }
       Stage sg_(s, EPHW_STAGE_RE_GEMM, st);
-      EPHW_TRY(gather(ks->pk, ks->nk, pair_other + p0, nbp, ne, w.pg));
-      EPHW_TRY(cgemm_grouped(kind, cfg, w.probs + a0, (int)nb, chunk_tiles[c],
-                             (int)std::min<int64_t>(grid, chunk_tiles[c]), w.queues + c * kGroupQueues, st));
+      if (pl.pack2) {
+        EPHW_TRY(pack_columns(w.big, ne, nb * E, nb * E, w.pb2, packed_columns_inv(w.pb2, nb * E, ne), st));
+        EPHW_TRY(packed_groups_sum(c, nb));
+      } else {
+        EPHW_TRY(gather(ks->pk, ks->nk, pair_other + p0, nbp, ne, w.pg));
+        EPHW_TRY(cgemm_grouped(kind, cfg, w.probs + a0, (int)nb, chunk_tiles[c],
+                               (int)std::min<int64_t>(grid, chunk_tiles[c]), w.queues + c * kGroupQueues, st));
+      }
     } else {
       // the Re sum over every Rp for the chunk's k: one GEMM batched over Rp,
       // G'[k][Rp][:] = P_k[k][:] g(Rp)[Re][:]
       {
         Stage sg_(s, EPHW_STAGE_RE_GEMM, st);
-        EPHW_TRY(gather(ks->pk, ks->nk, w.act + a0, nb, ne, w.first));
+        if (pl.pack1)
+          EPHW_TRY(pack_phases(w.qa + 3 * a0, nb, s->r_e, s->w_e, ne, s->pack_scale, w.pa1, st));
+        else
+          EPHW_TRY(gather(ks->pk, ks->nk, w.act + a0, nb, ne, w.first));
         GemmParams re;
         re.M = nb;
         re.N = E;
@@ -419,27 +529,42 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
         re.ldc = np * E;
         re.strideC = E;
         re.any_rounding = any_rounding;
-        EPHW_TRY(cgemm(kind, re, st));
+        if (!pl.pack1) EPHW_TRY(cgemm(kind, re, st));
+        for (int64_t r0 = 0; pl.pack1 && r0 < np; r0 += pl.rp_group) {
+          const int64_t nr = std::min(pl.rp_group, np - r0);
+          float* inv = packed_columns_inv(w.pb1, nr * E, ne);
+          if (c == 0 || pl.rp_group < np)
+            EPHW_TRY(pack_columns(static_cast<const char*>(s->g) + (size_t)(r0 * ne * E) * cs, ne, E, E, w.pb1, inv, st,
+                                  nr, ne * E));
+          re.N = nr * E;
+          re.batch = 1;
+          re.C = static_cast<char*>(w.big) + (size_t)(r0 * E) * cs;
+          re.packed.on = true;
+          re.packed.A = w.pa1;
+          re.packed.lda = packed_ld(nb);
+          re.packed.inv_a = 1.f / s->pack_scale;
+          re.packed.B = w.pb1;
+          re.packed.ldb = packed_ld(nr * E);
+          re.packed.inv_b = inv;
+          EPHW_TRY(cgemm(kind, re, st));
+        }
       }
       // the Rp sum per k over its kept q, then the mode vectors per pair
       {
         Stage sg_(s, EPHW_STAGE_RP_GEMM, st);
-        EPHW_TRY(gather(w.pq, nq, pair_other + p0, nbp, np, w.pg));
-        EPHW_TRY(cgemm_grouped(kind, cfg, w.probs + a0, (int)nb, chunk_tiles[c],
-                               (int)std::min<int64_t>(grid, chunk_tiles[c]), w.queues + c * kGroupQueues, st));
+        if (pl.pack2) {
+          EPHW_TRY(pack_columns(w.big, np, E, E, w.pb2, packed_columns_inv(w.pb2, nb * E, np), st, nb, np * E));
+          EPHW_TRY(packed_groups_sum(c, nb));
+        } else {
+          EPHW_TRY(gather(w.pq, nq, pair_other + p0, nbp, np, w.pg));
+          EPHW_TRY(cgemm_grouped(kind, cfg, w.probs + a0, (int)nb, chunk_tiles[c],
+                                 (int)std::min<int64_t>(grid, chunk_tiles[c]), w.queues + c * kGroupQueues, st));
+        }
       }
       if (!wannier) {
         Stage sg_(s, EPHW_STAGE_MODE_ROT, st);
-        const int64_t n = nbp * nw2;
-        if (kind == 0)
-          hipLaunchKernelGGL(pair_mode_rotate_kernel<double>, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st,
-                             static_cast<const double*>(w.wc), static_cast<const double*>(w.u), pair_other + p0, nq,
-                             nbp, nm, (int)nw2, static_cast<double*>(w.wnu), s->ctx->status);
-        else
-          hipLaunchKernelGGL(pair_mode_rotate_kernel<float>, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st,
-                             static_cast<const float*>(w.wc), static_cast<const float*>(w.u), pair_other + p0, nq,
-                             nbp, nm, (int)nw2, static_cast<float*>(w.wnu), s->ctx->status);
-        EPHW_CHECK_LAUNCH();
+        EPHW_TRY((kind == 0 ? pair_mode_rotate<double> : pair_mode_rotate<float>)(
+            w.wc, w.u, pair_other + p0, nq, nbp, nm, (int)nw2, w.wnu, s->ctx->status, st));
         wpair = w.wnu;
       }
     }

@@ -167,3 +167,62 @@ def test_coarse_transform_forms(run, prec, nw, na, box, m):
     ks.close()
     # two passes of sums and unitary rotations over at most 64 terms each way
     assert np.abs(out.cpu().numpy() - s.g).max() <= (1e-12 if prec == 0 else 1e-5) * np.abs(s.g).max()
+
+
+@pytest.mark.parametrize("order,nk,nq,fill,nw,na,tight", [
+    ("by_k", 560, 700, 0.95, 3, 1, False),    # both sums packed; 27 columns a group, ragged last rows
+    ("by_k", 560, 40, 0.9, 4, 1, False),      # the Re sum alone (few pairs per k)
+    ("by_k", 560, 40, 0.9, 4, 1, True),       # the same without the memory for its operands
+    ("by_q", 700, 5, 0.95, 3, 1, False),      # 135 columns in a batch, their last tile partly the next plane's
+    ("by_q", 1100, 3, 0.55, 4, 2, False),     # several row and column tiles a group
+])
+def test_pairs_packed(run, order, nk, nq, fill, nw, na, tight):
+    """Pair lists whose sums take packed operands, groups of different sizes and
+    empty ones, Wannier gauge, against 64 bits: both sums' bounds."""
+    import torch
+    from paper_2603_10295_amd import ephw
+    rng = np.random.default_rng(nk + nq)
+    s = system((4, 17, 1), nw, na, 5, ws=True, rp=synth.box((13, 5, 1)))
+    s = dataclasses.replace(s, w_p=1.0 / rng.choice([1, 2, 4], len(s.r_p)))
+    k, q = rng.random((nk, 3)), rng.random((nq, 3))
+    by_k = order == "by_k"
+    keep = rng.random((nk, nq) if by_k else (nq, nk)) < fill
+    if by_k:
+        keep[3] = keep[17] = False
+    start = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int64)
+    other = np.nonzero(keep)[1].astype(np.int32)
+    h = run.system(s)
+    ks = ephw.KSet(h, torch.from_numpy(k).cuda(), 1)
+    args = (torch.from_numpy(q).cuda(), ephw.PAIRS_BY_K if by_k else ephw.PAIRS_BY_Q, start,
+            torch.from_numpy(other).cuda(), torch.zeros(len(other), dtype=torch.int32, device="cuda"))
+    g = torch.empty((len(other), s.nm, nw, nw), dtype=torch.complex64, device="cuda")
+
+    def call():
+        ephw.interpolate_pairs(ks, *args, flags=ephw.OUT_G | ephw.OUT_WANNIER, g_out=g)
+        run.ctx.check()
+    call()
+    if tight:
+        used = run.ctx.memory()[0]
+        h.trim()
+        g.zero_()
+        run.ctx.set_limits(max_device_bytes=used - 4096)
+        try:
+            call()
+        finally:
+            run.ctx.set_limits()
+        assert run.ctx.memory()[0] < used - 4096
+    # 64 bits, [k][q][E] of the kept pairs
+    pe, pp = (torch.from_numpy(x).cuda() for x in (oracle.phases(k, s.r_e, s.w_e), oracle.phases(q, s.r_p, s.w_p)))
+    w = torch.from_numpy(s.g.astype(np.complex128)).cuda().reshape(len(s.r_p), len(s.r_e), -1)
+    E = w.shape[2]
+
+    def both(pe, w, pp):
+        a = torch.mm(pe, w.permute(1, 0, 2).reshape(len(s.r_e), -1)).reshape(nk, len(s.r_p), E)
+        return torch.mm(pp, a.permute(1, 0, 2).reshape(len(s.r_p), -1)).reshape(nq, nk, E)
+    mag = both(pe.abs(), w.real.abs() + w.imag.abs(), pp.abs())
+    ref = both(pe, w, pp)
+    major = np.nonzero(keep)[0]
+    ki, qi = (torch.from_numpy(x.astype(np.int64)).cuda() for x in ((major, other) if by_k else (other, major)))
+    tol = 1.01 * (bound(len(s.r_e), 6) + bound(len(s.r_p), 6))
+    assert bool(((g.reshape(-1, E) - ref[qi, ki]).abs() <= tol * mag[qi, ki]).all())
+    ks.close()
