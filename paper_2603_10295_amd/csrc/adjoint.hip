@@ -537,6 +537,8 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
   const int64_t nw = s->nw, nm = s->nm, nw2 = nw * nw, E = nm * nw2, nk = ks->nk, ne = s->ne, np = s->np;
   int64_t qb, kt;
   unit_shape(s, nq, nk, E, cs, 2, true, &qb, &kt);
+  // see GemmParams
+  const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   // q side
   EPHW_TRY(ws_need(s, WS_PQ, (size_t)nq * np * cs));
   EPHW_TRY(phase_matrix(kind, q, nq, s->r_p, s->w_p, np, wsp(s, WS_PQ), st));
@@ -559,16 +561,17 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
     EPHW_TRY(cgemm(0, g, st));
     const int64_t jw = jacobi_work_doubles((int)nm, nq);
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
-    EPHW_TRY(jacobi_eigh(static_cast<double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
-                         static_cast<double*>(wsp(s, WS_E)), jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr,
-                         s->ctx->status, s->ctx->max_sweeps, st));
+    double *hk = static_cast<double*>(wsp(s, WS_HK)), *lam = static_cast<double*>(wsp(s, WS_LAM));
+    double *e = static_cast<double*>(wsp(s, WS_E)), *work = jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr;
+    if (any_rounding && tridiag_better((int)nm, nq))
+      EPHW_TRY(tridiag_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, st));
+    else
+      EPHW_TRY(jacobi_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, s->ctx->max_sweeps, st));
   }
   if (omega) EPHW_TRY(abs_sqrt(static_cast<const double*>(wsp(s, WS_LAM)), omega, nq * nm, st));
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
   EPHW_TRY(mode_vectors(kind, static_cast<const double*>(wsp(s, WS_E)), nq, (int)nm, s->ism, wsp(s, WS_U), st));
   const bool rot = (flags & (EPHW_OUT_G | EPHW_OUT_LOSS)) != 0;
-  // see GemmParams
-  const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   const bool need_g = (flags & (EPHW_OUT_G | EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) != 0;
   const size_t gsz = (size_t)qb * ne * E * cs, wsz = (size_t)kt * qb * E * cs;
   const int64_t rot_tiles = cgemm_tiles(kind, nm * nw, nw);  // per pair

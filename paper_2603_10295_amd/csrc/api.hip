@@ -33,7 +33,7 @@ ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64
   p.C = hk;
   p.ldc = d2;
   EPHW_TRY(cgemm(0, p, st));
-  if (any_rounding && tridiag_better(dim, n)) return tridiag_eigh(hk, n, dim, out_eps, out_v, s->ctx->status, st);
+  if (any_rounding && tridiag_better(dim, n)) return tridiag_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, st);
   return jacobi_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, s->ctx->max_sweeps, st);
 }
 
@@ -822,7 +822,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
       // total (eigenvalues then exact to ~1e-20 relative, eigenvectors to ~1e-10,
       // far below the complex64 rounding they are cast to); FP64 at 1e-14
       if (r.any_rounding && tridiag_better(nw, (int64_t)nb * nk))
-        EPHW_TRY(tridiag_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, s->ctx->status, st));
+        EPHW_TRY(tridiag_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, st));
       else
         EPHW_TRY(jacobi_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, s->ctx->max_sweeps,
                              st, kind == 0 ? 1e-28 : 1e-20));

@@ -22,13 +22,13 @@ int64_t jacobi_work_doubles(int n, int64_t batch);
 ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
                         int max_sweeps, hipStream_t s, double off_tol2 = 1e-28);
 
-// The same eigenproblem for n <= 32 by tridiagonalisation and QL (tridiag.hip),
+// The same eigenproblem (and workspace) by tridiagonalisation and QL (tridiag.hip),
 // several times faster; eigenvectors agree with jacobi_eigh's to rounding over
 // the gaps, not bit for bit.  H is overwritten.  The sweep limit bounds the QL
 // steps per eigenvalue.
 // tridiag_better: the rule for taking it.
 bool tridiag_better(int n, int64_t batch);
-ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status,
+ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
                          hipStream_t s);
 
 // many small (n <= 32) eigensolves of different orders in one launch;

@@ -1,9 +1,9 @@
-// Batched Hermitian eigensolver in FP64 for orders up to 32 by Householder
+// Batched Hermitian eigensolver in FP64 for orders up to 256 by Householder
 // tridiagonalisation and implicit QL, for solves whose last bits are free
 // (those of jacobi.hip keep theirs): about 10 n^3 operations a matrix, where
 // the Jacobi sweeps take about 6 n rounds of all n^2 / 2 blocks.
 //
-// Reduction (reduce_kernel): a wavefront takes 64 / L matrices, L lanes each
+// Up to order 32, reduction (reduce_kernel): a wavefront takes 64 / L matrices, L lanes each
 // (the order rounded up to 8, 16 or 32), lane r holding row r of A and of Q in
 // registers.  For each column, v and tau of H = I - tau v v^H with H x = e e1,
 // A <- H A H as a rank-2 update and Q <- Q H; v and w pass through LDS, where
@@ -77,6 +77,11 @@ __device__ __forceinline__ double rcp_nr(double x) {
 __device__ __forceinline__ int scale_exponent(double big) {
   const int ex = big > 0.0 && big < 1.7e308 ? ilogb(big) : 0;
   return ex < -1000 ? -1000 : ex;
+}
+
+// the off-diagonal e between d0 and d1 (of a matrix scaled to entries near 1) counts as zero
+__device__ __forceinline__ bool negligible(double e, double d0, double d1) {
+  return fabs(e) <= fmax(2.220446049250313e-16 * (fabs(d0) + fabs(d1)), 1e-140);
 }
 
 // H -> d in eps, |e| and the scale's exponent in the first n + 1 doubles of H's
@@ -234,9 +239,6 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
   double* e = se + tid;
   double2* log = shared + tid * T * N;
   uint32_t small = 1u << (n - 1);                // bit i: e[i] is negligible
-  auto negligible = [](double e, double d0, double d1) {
-    return fabs(e) <= fmax(2.220446049250313e-16 * (fabs(d0) + fabs(d1)), 1e-140);
-  };
   if (owner)
     for (int i = 0; i + 1 < n; ++i) small |= negligible(e[i * M], d[i * M], d[(i + 1) * M]) ? 1u << i : 0u;
   const int limit = sweep_limit(status);
@@ -378,6 +380,418 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
   }
 }
 
+// ---------------------------------------------------------------------------
+// Orders 33 to 256: the same method over a workspace, one matrix per workgroup
+// in the serial parts.  The reduction works in place (from L2: n^2 complex
+// values do not fit the LDS above n = 100) and leaves v_k in row k; QL runs on
+// the real tridiagonal with its rotations logged to memory; the rotations are
+// applied to the rows of a real Z, 64 rows per wavefront; the reflectors, last
+// first, take the columns of Z back, a wavefront per column.  Bound by the QL
+// chain (about 0.85 n^2 rotations in a row) and the reduction's n steps of five
+// barriers.  8 matrices of n = 150: reduction 1.27 ms,
+// QL 2.84, rotations 1.23, back 0.12; Jacobi 9.9.
+// ---------------------------------------------------------------------------
+constexpr int kBigThreads = 1024, kBigMax = 256, kBigRounds = 3;
+
+// A matrix's part of the workspace: jacobi_work_doubles' share, 4 n (n - 1)
+// doubles or more, holds the 3 n^2 + 9 n + 4 of these for n >= 33.
+struct BigWork {
+  double2 *log, *delta;       // [n^2] rotations (c, s) of a round; [n] phases of Q's columns
+  double *zt, *d, *e, *tau;   // Z transposed [col][row]; [n] each
+  uint2* step;                // [4 n] of a round: l | m << 16, first rotation
+  int* state;                 // scale exponent, next eigenvalue, steps of the round
+  __device__ BigWork(double* base, int n) {
+    const int64_t n2 = (int64_t)n * n;
+    log = reinterpret_cast<double2*>(base);
+    delta = log + n2;
+    zt = reinterpret_cast<double*>(delta + n);
+    d = zt + n2;
+    e = d + n;
+    tau = e + n;
+    step = reinterpret_cast<uint2*>(tau + n);
+    state = reinterpret_cast<int*>(step + 4 * n);
+  }
+};
+
+// sum of v over the workgroup; red: 16 values no one reads any more
+__device__ __forceinline__ double block_sum(double v, double* red) {
+  v = group_sum<64>(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int i = 0; i < kBigThreads / 64; ++i) t += red[i];
+  return t;
+}
+
+__global__ void __launch_bounds__(kBigThreads)
+    reduce_big_kernel(double2* __restrict__ H, int n, double* __restrict__ work, int64_t wstride) {
+  __shared__ double2 sv[kBigMax], sw[kBigMax], part[kBigThreads];
+  __shared__ double red[2][kBigThreads / 64];
+  const int tid = threadIdx.x, W = (n + 63) / 64 * 64, G = kBigThreads / W;
+  const int c = tid % W, g = tid / W;            // column; thread g takes the rows r = g modulo G
+  const bool own = g < G && c < n;
+  double2* A = H + (int64_t)blockIdx.x * n * n;
+  const BigWork w(work + (int64_t)blockIdx.x * wstride, n);
+
+  double big = 0.0;
+  if (own)
+    for (int r = g; r < n; r += G) {
+      const double2 x = A[(int64_t)r * n + c];
+      big = fmax(big, fmax(fabs(x.x), r == c ? 0.0 : fabs(x.y)));
+    }
+  big = group_max<64>(big);
+  if ((tid & 63) == 0) red[0][tid >> 6] = big;
+  __syncthreads();
+  for (int i = 0; i < kBigThreads / 64; ++i) big = fmax(big, red[0][i]);
+  const int ex = scale_exponent(big);
+  const double scale = ldexp(1.0, -ex);
+  if (tid == 0) {
+    w.state[0] = ex;
+    w.state[1] = 0;
+  }
+  if (own)
+    for (int r = g; r < n; r += G) {
+      const double2 x = A[(int64_t)r * n + c];
+      A[(int64_t)r * n + c] = make_double2(x.x * scale, r == c ? 0.0 : x.y * scale);
+    }
+  __syncthreads();
+
+  double2 delta = make_double2(1.0, 0.0);
+#pragma unroll 1
+  for (int k = 0; k < n; ++k) {
+    const double2* row = A + (int64_t)k * n;
+    const double dk = row[k].x;
+    double2 alpha = make_double2(0.0, 0.0), v = make_double2(0.0, 0.0);
+    if (k + 1 < n) alpha = make_double2(row[k + 1].x, -row[k + 1].y);
+    if (g == 0 && c > k + 1 && c < n) v = make_double2(row[c].x, -row[c].y);
+    const double rest = block_sum(v.x * v.x + v.y * v.y, red[0]);
+    const double a2 = alpha.x * alpha.x + alpha.y * alpha.y;
+    const bool has = a2 > 1e-280, reflect = rest > 1e-280;   // see reduce_kernel
+    const double ia = has ? rsqrt_nr(a2) : 0.0, aabs = a2 * ia;
+    const double2 ph = has ? make_double2(alpha.x * ia, alpha.y * ia) : make_double2(1.0, 0.0);
+    double norm = aabs, tau = 0.0;
+    if (reflect) {
+      const double t = a2 + rest, in = rsqrt_nr(t);
+      norm = t * in;
+      tau = in * rcp_nr(norm + aabs);
+      if (g == 0 && c == k + 1) v = make_double2(alpha.x + ph.x * norm, alpha.y + ph.y * norm);
+    }
+    if (tid == 0) {
+      w.d[k] = dk;
+      w.e[k] = k + 1 < n ? norm : 0.0;
+      w.tau[k] = tau;
+      w.delta[k] = delta;
+    }
+    const double sgn = reflect ? -1.0 : 1.0;
+    delta = make_double2(sgn * (delta.x * ph.x - delta.y * ph.y), sgn * (delta.x * ph.y + delta.y * ph.x));
+    if (!reflect) {
+      __syncthreads();                           // red is free again
+      continue;
+    }
+    if (g == 0 && c < n) sv[c] = v;
+    __syncthreads();
+    if (g == 0 && c > k && c < n) A[(int64_t)k * n + c] = v;
+    const int r0 = k + 1 + (g + G - (k + 1) % G) % G;   // first own row past k
+    double2 p = make_double2(0.0, 0.0);
+    if (own && c > k) {
+#pragma unroll 8
+      for (int r = r0; r < n; r += G) {          // A[c][r] is the conjugate of A[r][c]
+        const double2 x = A[(int64_t)r * n + c], vr = sv[r];
+        p.x = fma(x.x, vr.x, fma(x.y, vr.y, p.x));
+        p.y = fma(x.x, vr.y, fma(-x.y, vr.x, p.y));
+      }
+    }
+    part[tid] = p;
+    __syncthreads();
+    double dot = 0.0;
+    if (g == 0) {
+      for (int i = 1; i < G; ++i) {
+        p.x += part[i * W + c].x;
+        p.y += part[i * W + c].y;
+      }
+      p = make_double2(tau * p.x, tau * p.y);
+      dot = v.x * p.x + v.y * p.y;
+    }
+    const double kk = 0.5 * tau * block_sum(dot, red[1]);
+    if (g == 0 && c < n) sw[c] = make_double2(p.x - kk * v.x, p.y - kk * v.y);
+    __syncthreads();
+    if (own && c > k) {
+      const double2 vc = sv[c], wc = sw[c];
+#pragma unroll 8
+      for (int r = r0; r < n; r += G) {
+        double2 x = A[(int64_t)r * n + c];
+        const double2 vr = sv[r], wr = sw[r];
+        x.x = fma(-vr.x, wc.x, fma(-vr.y, wc.y, fma(-wr.x, vc.x, fma(-wr.y, vc.y, x.x))));
+        x.y = fma(-vr.y, wc.x, fma(vr.x, wc.y, fma(-wr.y, vc.x, fma(wr.x, vc.y, x.y))));
+        if (r == c) x.y = 0.0;
+        A[(int64_t)r * n + c] = x;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// One wavefront per matrix runs the recurrence, every lane alike, until the
+// log of the round is full or all eigenvalues are done.
+__global__ void __launch_bounds__(64)
+    ql_big_kernel(int n, double* __restrict__ work, int64_t wstride, uint32_t* status, bool last) {
+  __shared__ double dpad[kBigMax + 1], epad[kBigMax + 1];   // index -1 is read and not used
+  double *const d = dpad + 1, *const e = epad + 1;
+  const int lane = threadIdx.x;
+  const BigWork w(work + (int64_t)blockIdx.x * wstride, n);
+  int l = w.state[1], steps = 0, t = 0, iter = 0;
+  if (l < n) {
+    for (int i = lane; i < n; i += 64) {
+      d[i] = w.d[i];
+      e[i] = w.e[i];
+    }
+    const int limit = sweep_limit(status), room = n * n;
+    wave_sync();
+#pragma unroll 1
+    while (l < n) {
+      int m = n - 1;
+      for (int i0 = l;; i0 += 64) {
+        const int i = i0 + lane;
+        const uint64_t mask = __ballot(i >= n - 1 || negligible(e[i], d[i], d[i + 1]));
+        if (mask != 0) {
+          m = i0 + __builtin_ctzll(mask);
+          break;
+        }
+      }
+      m = __builtin_amdgcn_readfirstlane(m);
+      if (m == l || iter >= limit) {
+        if (m != l && lane == 0) atomicOr(status, kStatusNoConv);
+        ++l;
+        iter = 0;
+        continue;
+      }
+      if (steps == 4 * n || t + (m - l) > room) break;
+      if (lane == 0) w.step[steps] = make_uint2((uint32_t)l | (uint32_t)m << 16, (uint32_t)t);
+      ++steps;
+      ++iter;
+      const double dl = d[l], el = e[l];
+      double gg = 0.5 * (d[l + 1] - dl) * rcp_nr(el);
+      double dn = d[m];
+      const double h2 = fma(gg, gg, 1.0);
+      gg = dn - dl + el * rcp_nr(gg + copysign(h2 * rsqrt_nr(h2), gg));
+      double s = 1.0, c = 1.0, p = 0.0, ei = e[m - 1], di = d[m - 1];
+      asm volatile("" : "+v"(di), "+v"(ei), "+v"(dn), "+v"(gg));   // see ql_kernel
+#pragma unroll 1
+      for (int i = m - 1; i >= l; --i) {
+        double en = e[i - 1], dp = d[i - 1];
+        const double f = s * ei, bb = c * ei;
+        const double q = fma(f, f, gg * gg);
+        const bool zero = q < 1e-290;
+        const double inv = rsqrt_nr(zero ? 1.0 : q), eo = q * inv;
+        s = f * inv;
+        c = zero ? 1.0 : gg * inv;
+        gg = dn - p;
+        const double rr = fma(di - gg, s, 2.0 * c * bb);
+        p = s * rr;
+        d[i + 1] = gg + p;
+        e[i + 1] = eo;
+        gg = fma(c, rr, -bb);
+        w.log[t] = make_double2(c, s);           // every lane the same value: no branch in the chain
+        ++t;
+        dn = di;
+        asm volatile("" : "+v"(dp), "+v"(en) : "v"(gg), "v"(p));
+        di = dp;
+        ei = en;
+      }
+      d[l] = dn - p;
+      e[l] = gg;
+      e[m] = 0.0;
+      wave_sync();
+    }
+    for (int i = lane; i < n; i += 64) {
+      w.d[i] = d[i];
+      w.e[i] = e[i];
+    }
+    if (last && l < n && lane == 0) atomicOr(status, kStatusNoConv);
+  }
+  if (lane == 0) {
+    w.state[1] = l;
+    w.state[2] = steps;
+  }
+}
+
+__device__ __forceinline__ double read_lane(double x, int lane) {
+  const int2 v = __builtin_bit_cast(int2, x);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(v.x, lane), __builtin_amdgcn_readlane(v.y, lane)));
+}
+
+// The round's rotations on 64 rows of Z (identity before the first round),
+// a lane per row, columns in LDS.
+__global__ void __launch_bounds__(64) rotate_big_kernel(int n, double* __restrict__ work, int64_t wstride, bool first) {
+  extern __shared__ double tri_z[];              // [n][64]
+  const int lane = threadIdx.x, r = blockIdx.x * 64 + lane;
+  const BigWork w(work + (int64_t)blockIdx.y * wstride, n);
+  const int steps = w.state[2];
+  if (steps == 0 && !first) return;
+  double* z = tri_z + lane;
+  for (int c = 0; c < n; ++c) z[c * 64] = first ? (c == r ? 1.0 : 0.0) : r < n ? w.zt[(int64_t)c * n + r] : 0.0;
+#pragma unroll 1
+  for (int k = 0; k < steps; ++k) {
+    const uint2 st = w.step[k];
+    const int lo = __builtin_amdgcn_readfirstlane(st.x & 0xffff), hi = __builtin_amdgcn_readfirstlane(st.x >> 16);
+    const int t0 = __builtin_amdgcn_readfirstlane(st.y), len = hi - lo;
+    double zc = z[hi * 64];
+    int i = hi - 1;
+#pragma unroll 1
+    for (int b = 0; b < len; b += 64) {
+      const double2 x = w.log[t0 + (b + lane < len ? b + lane : len - 1)];
+      const int cnt = len - b < 64 ? len - b : 64;
+      int j = 0;
+#pragma unroll 1
+      for (; j + 4 <= cnt; j += 4, i -= 4) {
+        double z0[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) z0[u] = z[(i - u) * 64];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double c = read_lane(x.x, j + u), s = read_lane(x.y, j + u);
+          z[(i - u + 1) * 64] = fma(s, z0[u], c * zc);
+          zc = fma(c, z0[u], -(s * zc));
+        }
+      }
+#pragma unroll 1
+      for (; j < cnt; ++j, --i) {
+        const double c = read_lane(x.x, j), s = read_lane(x.y, j), z0 = z[i * 64];
+        z[(i + 1) * 64] = fma(s, z0, c * zc);
+        zc = fma(c, z0, -(s * zc));
+      }
+    }
+    z[lo * 64] = zc;
+  }
+  if (r < n)
+    for (int c = 0; c < n; ++c) w.zt[(int64_t)c * n + r] = z[c * 64];
+}
+
+// Column j of V = H_0 .. H_{n-2} diag(delta) z_j, its phase and its place
+__global__ void __launch_bounds__(256)
+    back_big_kernel(const double2* __restrict__ H, int n, const double* __restrict__ work, int64_t wstride,
+                    double* __restrict__ eps, double2* __restrict__ V) {
+  constexpr int NX = kBigMax / 64;
+  const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (j >= n) return;
+  const int64_t b = blockIdx.y;
+  const BigWork w(const_cast<double*>(work) + b * wstride, n);
+  const double2* A = H + b * n * n;
+  double2 x[NX], v[NX];
+#pragma unroll
+  for (int u = 0; u < NX; ++u) {
+    const int r = lane + 64 * u;
+    const double z = r < n ? w.zt[(int64_t)j * n + r] : 0.0;
+    const double2 del = r < n ? w.delta[r] : make_double2(0.0, 0.0);
+    x[u] = make_double2(z * del.x, z * del.y);
+  }
+  auto load = [&](int k) {
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+      const int r = lane + 64 * u;
+      v[u] = k >= 0 && r > k && r < n ? A[(int64_t)k * n + r] : make_double2(0.0, 0.0);
+    }
+  };
+  load(n - 2);
+#pragma unroll 1
+  for (int k = n - 2; k >= 0; --k) {
+    double2 y[NX];
+#pragma unroll
+    for (int u = 0; u < NX; ++u) y[u] = v[u];
+    const double tau = w.tau[k];
+    load(k - 1);
+    if (tau == 0.0) continue;                    // row k holds no reflector
+    double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+      s.x = fma(y[u].x, x[u].x, fma(y[u].y, x[u].y, s.x));
+      s.y = fma(y[u].x, x[u].y, fma(-y[u].y, x[u].x, s.y));
+    }
+    s.x = tau * group_sum<64>(s.x);
+    s.y = tau * group_sum<64>(s.y);
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+      x[u].x = fma(-y[u].x, s.x, fma(y[u].y, s.y, x[u].x));
+      x[u].y = fma(-y[u].x, s.y, fma(-y[u].y, s.x, x[u].y));
+    }
+  }
+  // the largest entry (the first of equals)
+  double best = -1.0;
+  int at = 0;
+  double2 bv = make_double2(1.0, 0.0);
+#pragma unroll
+  for (int u = 0; u < NX; ++u) {
+    const double m2 = x[u].x * x[u].x + x[u].y * x[u].y;
+    if (lane + 64 * u < n && m2 > best) {
+      best = m2;
+      at = lane + 64 * u;
+      bv = x[u];
+    }
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const double ob = __shfl_xor(best, off, 64), ox = __shfl_xor(bv.x, off, 64), oy = __shfl_xor(bv.y, off, 64);
+    const int oa = __shfl_xor(at, off, 64);
+    if (ob > best || (ob == best && oa < at)) {
+      best = ob;
+      at = oa;
+      bv = make_double2(ox, oy);
+    }
+  }
+  const double mag = sqrt(best);
+  const double2 fix = mag > 0.0 ? make_double2(bv.x / mag, -bv.y / mag) : make_double2(1.0, 0.0);
+  // ascending order (ties by index)
+  const double mine = w.d[j];
+  int place = 0;
+  bool order = true;
+  for (int i = lane; i < n; i += 64) {
+    const double o = w.d[i];
+    order = order && o == o;
+    place += (o < mine) || (o == mine && i < j);
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) place += __shfl_xor(place, off, 64);
+  if (!__all(order)) place = j;                  // NaN eigenvalues (a matrix that is not finite) would share places
+  if (lane == 0) eps[b * n + place] = ldexp(mine, w.state[0]);
+#pragma unroll
+  for (int u = 0; u < NX; ++u) {
+    const int r = lane + 64 * u;
+    if (r < n)
+      V[(b * n + r) * n + place] = make_double2(x[u].x * fix.x - x[u].y * fix.y, x[u].x * fix.y + x[u].y * fix.x);
+  }
+}
+
+ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                       hipStream_t s) {
+  if (!work) {
+    set_error("tridiag_eigh: orders above 32 need a workspace");
+    return EPHW_EINVAL;
+  }
+  constexpr int64_t kChunk = 1024;               // that of jacobi_work_doubles
+  const int64_t chunk = batch < kChunk ? batch : kChunk;
+  const int64_t wstride = jacobi_work_doubles(n, chunk) / chunk & ~(int64_t)1;
+  const size_t lds = (size_t)n * 64 * sizeof(double);
+  EPHW_HIP(hipFuncSetAttribute((const void*)rotate_big_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  for (int64_t b0 = 0; b0 < batch; b0 += chunk) {
+    const unsigned nb = (unsigned)(batch - b0 < chunk ? batch - b0 : chunk);
+    double2* h = reinterpret_cast<double2*>(H) + b0 * n * n;
+    hipLaunchKernelGGL(reduce_big_kernel, dim3(nb), dim3(kBigThreads), 0, s, h, n, work, wstride);
+    EPHW_CHECK_LAUNCH();
+    for (int round = 0; round < kBigRounds; ++round) {
+      hipLaunchKernelGGL(ql_big_kernel, dim3(nb), dim3(64), 0, s, n, work, wstride, status, round + 1 == kBigRounds);
+      EPHW_CHECK_LAUNCH();
+      hipLaunchKernelGGL(rotate_big_kernel, dim3((unsigned)ceil_div(n, 64), nb), dim3(64), lds, s, n, work, wstride,
+                         round == 0);
+      EPHW_CHECK_LAUNCH();
+    }
+    hipLaunchKernelGGL(back_big_kernel, dim3((unsigned)ceil_div(n, 4), nb), dim3(256), 0, s, h, n, work, wstride,
+                       eps + b0 * n, reinterpret_cast<double2*>(V) + b0 * n * n);
+    EPHW_CHECK_LAUNCH();
+  }
+  return EPHW_OK;
+}
+
 template <int N, int L>
 ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s) {
   using S = TriShape<N, L>;
@@ -403,17 +817,22 @@ ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint
 // matrices, n = 6: 280 and 261).  From 7 to 16 a call that leaves the chip idle
 // is Jacobi's, whose rounds are the shorter chain: n = 8, 4096 matrices 54 and
 // 57 us; n = 11, 1024: 81 and 90, 4096: 104 and 94; n = 16, 1024: 117 and 164,
-// 4096: 289 and 169; n^3 x matrices is near 4 million where they meet.  Above 16
-// this one is ahead at every count (n = 24: 452 and 306 us at 64 matrices).
+// 4096: 289 and 169; n^3 x matrices is near 4 million where they meet.  From 17
+// to 32 this one is ahead at every count (n = 24: 452 and 306 us at 64 matrices).
+// From 33 to 63 few matrices are level (n = 33: 469 and 445 us, n = 48: 680 and
+// 750), 512 are not (n = 48: 2824 and 1371); n = 66, one matrix: 1362 and 1270,
+// n = 150: 9913 and 5409, n = 255, 64 matrices: 73 500 and 18 140.
 bool tridiag_better(int n, int64_t batch) {
-  return n > 16 ? n <= 32 : n > 6 && (int64_t)n * n * n * batch >= 4000000;
+  if (n <= 16) return n > 6 && (int64_t)n * n * n * batch >= 4000000;
+  if (n <= 32 || n >= 64) return n <= kBigMax;
+  return batch >= 256;
 }
 
-ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status,
+ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
                          hipStream_t s) {
   if (batch <= 0) return EPHW_OK;
-  if (n < 1 || n > 32) {
-    set_error("tridiag_eigh: matrix order must be in [1, 32]");
+  if (n < 1 || n > kBigMax) {
+    set_error("tridiag_eigh: matrix order must be in [1, 256]");
     return EPHW_EUNSUPPORTED;
   }
   if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
@@ -424,7 +843,8 @@ ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V
   if (n <= 12) return launch<12, 16>(H, batch, n, eps, V, status, s);
   if (n <= 16) return launch<16, 16>(H, batch, n, eps, V, status, s);
   if (n <= 24) return launch<24, 32>(H, batch, n, eps, V, status, s);
-  return launch<32, 32>(H, batch, n, eps, V, status, s);
+  if (n <= 32) return launch<32, 32>(H, batch, n, eps, V, status, s);
+  return launch_big(H, batch, n, eps, V, work, status, s);
 }
 
 }  // namespace ephw

@@ -66,3 +66,40 @@ def test_tridiagonal_orders(nw):
         ta = (np.abs(got["g"]) ** 2).sum((-2, -1))
         tb = (np.abs(ref["ghat"]) ** 2).sum((-2, -1))
         assert np.abs(ta - tb).max() <= 1e-12 * tb.max()
+
+
+@pytest.mark.parametrize("na,nq", [(11, 256), (12, 257), (21, 260), (22, 3), (43, 4), (64, 4), (85, 4)])
+def test_tridiagonal_phonons(na, nq):
+    """D(q) of orders 33 to 255 in a call whose rounding is free: one or two
+    row blocks and their edges, uncoupled equal modes (columns with nothing to
+    reflect, QL that splits), all zero; frequencies against LAPACK, g by block
+    sums against the oracle, and the sum over all modes, which is that of any
+    unitary e."""
+    import dataclasses
+    from gpu_run import Runner
+    from paper_2603_10295_amd import ephw
+    run = Runner()
+    s = synth.make_system(2 if na < 33 else 33, na, synth.box((2, 2, 1)), synth.box((3, 2, 1)), [na, 7])
+    nm = 3 * na
+    rng = np.random.default_rng(na)
+    k, q, kqi = rng.random((3, 3)), rng.random((nq, 3)), None
+    if na >= 33:                      # so many modes take Nw > 32, and that a k grid
+        k = q = np.array([[0, 0, 0], [0.25, 0, 0], [0.5, 0, 0], [0.75, 0, 0]])
+        kqi = ((np.arange(4)[:, None] + np.arange(4)) % 4).astype(np.int32)
+    c = s.c_r.copy()
+    c[:, 0, :] = c[:, :, 0] = c[:, 4, :] = c[:, :, 4] = 0
+    zero = np.flatnonzero(~s.r_c.any(1))[0]
+    c[zero, 0, 0] = c[zero, 4, 4] = 0.7
+    for cr in (s.c_r, c, 0 * c):
+        t = dataclasses.replace(s, c_r=cr)
+        got = run.interpolate(run.system(t), k, q, 0, kq_index=kqi, flags=ephw.OUT_G)
+        ref = oracle.interpolate(t, k, q, return_all=True)
+        lam = np.sort(np.abs(ref["lam"]), -1)
+        assert np.abs(np.sort(got["omega"] ** 2, -1) - lam).max() <= (1e-14 + 8 * nm * 2.0 ** -53) * nm * lam.max()
+        if cr is s.c_r:
+            a = oracle.block_sums(np.abs(got["g"]) ** 2, ref["eps_kq"], ref["eps_k"], ref["lam"])
+            b = oracle.block_sums(np.abs(ref["ghat"]) ** 2, ref["eps_kq"], ref["eps_k"], ref["lam"])
+            assert oracle.compare_block_sums(a, b)[0] <= 1e-10
+        ta = (np.abs(got["g"]) ** 2).sum((-3, -2, -1))
+        tb = (np.abs(ref["ghat"]) ** 2).sum((-3, -2, -1))
+        assert np.abs(ta - tb).max() <= 1e-12 * tb.max()
