@@ -18,10 +18,10 @@
 // in LDS, then a thread per row of Q applies the log to its row in registers.
 // (With all lanes of a group computing the recurrence alike, in one kernel with
 // the reduction, the recurrence was most of the time.)
-// 131 072 matrices (us, reduction + QL, Jacobi): n = 8: 102 + 281, 741; n = 11:
-// 336 + 619, 2339; n = 16: 688 + 1586, 7457.  32 768 of n = 24: 936 + 1318,
-// 11 592; of n = 32: 1763 + 3579, 33 699.  The QL of a few matrices is its chain
-// alone (n = 8: 40 us, n = 16: 130).
+// 131 072 matrices (us, reduction + QL, Jacobi): n = 8: 104 + 246, 753; n = 11:
+// 334 + 539, 2363; n = 16: 677 + 1285, 7431.  32 768 of n = 24: 939 + 1091,
+// 11 583; of n = 32: 1782 + 2849, 33 633.  The QL of a few matrices is its chain
+// alone (n = 16: 105 us).
 #include "kernels.h"
 
 namespace ephw {
@@ -246,10 +246,15 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
   for (;;) {
     int count = 0;
     while (l < n && count < T) {
-      const int skip = __builtin_ctzll(~(uint64_t)(small >> l));   // eigenvalues that are done, up to 32
-      if (skip > 0 || iter >= limit) {
-        if (skip == 0) atomicOr(status, kStatusNoConv);
-        l += skip > 0 ? skip : 1;
+      // past the eigenvalues that are done (up to 32), in the same pass of the
+      // loop: its passes last as long as the longest lane's
+      const int skip = __builtin_ctzll(~(uint64_t)(small >> l));
+      l += skip;
+      iter = skip > 0 ? 0 : iter;
+      if (l >= n) break;
+      if (iter >= limit) {
+        atomicOr(status, kStatusNoConv);
+        ++l;
         iter = 0;
         continue;
       }
@@ -816,9 +821,9 @@ ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint
 // Up to order 6 the two are level (n = 3: 82 us by Jacobi and 99 here at 131 072
 // matrices, n = 6: 280 and 261).  From 7 to 16 a call that leaves the chip idle
 // is Jacobi's, whose rounds are the shorter chain: n = 8, 4096 matrices 54 and
-// 57 us; n = 11, 1024: 81 and 90, 4096: 104 and 94; n = 16, 1024: 117 and 164,
-// 4096: 289 and 169; n^3 x matrices is near 4 million where they meet.  From 17
-// to 32 this one is ahead at every count (n = 24: 452 and 306 us at 64 matrices).
+// 52 us; n = 11, 1024: 81 and 78, 4096: 104 and 82; n = 16, 1024: 117 and 138,
+// 4096: 290 and 149; n^3 x matrices is near 4 million where they meet.  From 17
+// to 32 this one is ahead at every count (n = 24: 449 and 259 us at 64 matrices).
 // From 33 to 63 few matrices are level (n = 33: 469 and 445 us, n = 48: 680 and
 // 750), 512 are not (n = 48: 2824 and 1371); n = 66, one matrix: 1362 and 1270,
 // n = 150: 9913 and 5409, n = 255, 64 matrices: 73 500 and 18 140.
