@@ -226,3 +226,17 @@ def test_pairs_packed(run, order, nk, nq, fill, nw, na, tight):
     tol = 1.01 * (bound(len(s.r_e), 6) + bound(len(s.r_p), 6))
     assert bool(((g.reshape(-1, E) - ref[qi, ki]).abs() <= tol * mag[qi, ki]).all())
     ks.close()
+
+
+@pytest.mark.parametrize("nk,nw,na", [(1, 3, 1), (64, 5, 1), (65, 3, 1), (130, 4, 2), (192, 3, 1)])
+def test_compensated_rows(run, nk, nw, na):
+    """The compensated FP32 sums of a call that also returns band sums, with
+    64-row tiles (an odd number of them) and without: blocks of 32 k of two
+    roundings each, then one per block."""
+    from paper_2603_10295_amd import ephw
+    s = system((5, 13, 1), nw, na, 9)
+    k = np.random.default_rng(nk).random((nk, 3))
+    got = run.interpolate(run.system(s), k, np.zeros((1, 3)), 2, want_eps_kq=False,
+                          flags=ephw.OUT_G | ephw.OUT_BAND_SUM | ephw.OUT_WANNIER)["g"][0]
+    ref, mag = re_sums(s, k)
+    assert np.all(np.abs(got - ref) <= 2 * (64 + 65 // 32 + 4) * 2.0 ** -24 * mag)
