@@ -71,10 +71,18 @@ typedef int32_t ephw_status;
 
 /* arithmetic of the phase sums and rotations; eigensolves are always FP64 */
 #define EPHW_FP64        0  /* complex128 GEMMs on FP64 MFMA, g stored c128 */
-#define EPHW_FP32        1  /* complex64 GEMMs on FP32 MFMA, g stored c64 */
+#define EPHW_FP32        1  /* complex64 GEMMs on FP32 MFMA, g stored c64.  A call
+                               that returns g alone may run its phase sums on the
+                               16-bit matrix cores with every value split in two
+                               or three parts (error against FP64 no larger), and
+                               its eigensolves by tridiagonalisation: its g then
+                               differs in rounding from that of a call which also
+                               returns band sums or the loss, and within
+                               degenerate blocks by a unitary mixing */
 #define EPHW_FP32_COMP   2  /* compensated FP32: as EPHW_FP32, but each phase sum
                                accumulates in K blocks of 32 (fresh FP32 MFMA
-                               accumulators per block, block sums added in FP32),
+                               accumulators per block, block sums added in FP32;
+                               blocks of 16 of split values for g alone),
                                which cuts the FP32 accumulation error, the
                                dominant one, about 3x; backward, Eq. (6) and
                                batches take FP64 or FP32 sets only */
@@ -116,7 +124,9 @@ ephw_status ephw_ctx_check(ephw_ctx* ctx, void* stream);
                        raises EPHW_ENOCONV in the status word (the kernel still
                        writes its current eigenvalues and vectors and exits
                        normally); 0 <= max_sweeps <= 1000, default 40 (an order-n
-                       solve converges in well under 20 for n <= 256). */
+                       solve converges in well under 20 for n <= 256).  Solves
+                       that run by tridiagonalisation and QL take it as the QL
+                       steps one eigenvalue may take (2 on average). */
 ephw_status ephw_ctx_set_limits(ephw_ctx* ctx, int64_t max_device_bytes, int32_t max_sweeps);
 /* device memory the context's objects hold now, and its cap (0 = none) */
 ephw_status ephw_ctx_memory(const ephw_ctx* ctx, int64_t* used, int64_t* limit);
@@ -222,9 +232,10 @@ ephw_status ephw_interpolate(ephw_kset* ks, const double* q, int64_t nq, const i
 
 /* ephw_interpolate for callers that cannot allocate device memory (code under
    HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
-   same arguments, outputs and results, but every intermediate buffer (phase
-   factors, mode vectors, the g(Re,q) sweeps, the Re-sum output, loss
-   partials, k+q eigensolves) lives in a static scratch array of the library,
+   same arguments and outputs (which may differ in rounding, as those of
+   batches of another size do), but every intermediate buffer (phase factors,
+   mode vectors, the g(Re,q) sweeps, the Re-sum output, loss partials, k+q
+   eigensolves) lives in a static scratch array of the library,
    256 MiB per device, which each device the library runs on holds until the
    process ends.  No device memory is allocated or freed by the call.
    - The q points are processed in batches small enough for the scratch (at
