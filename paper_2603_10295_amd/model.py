@@ -70,4 +70,5 @@ def stage_counts(nw: int, nm: int, ne: int, np_: int, nk: int, nq: int, nh: int 
 # MI355X published peaks (dense)
 PEAK_FP64_TFLOPS = 78.6
 PEAK_FP32_TFLOPS = 157.3
+PEAK_FP16_TFLOPS = 2516.6
 PEAK_HBM_GBS = 8000.0
