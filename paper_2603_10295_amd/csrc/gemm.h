@@ -64,6 +64,16 @@ struct BandEpilogue {
 // terms has few roundings to save.
 constexpr int kSplitMinK = 64;
 
+// The 16-bit matrix instructions do not round their running sum to nearest:
+// what they drop has one sign, whatever that of the sum.  A product whose
+// columns are summed next (Eq. (9) before Eq. (10)) would carry it into that
+// sum coherently where the phases agree, near k or q = 0.  So the columns are
+// multiplied with pseudo-random signs, taken out of the result again, which
+// costs nothing: at q = 0 of the dense-Si window the error of |g|^2 was 1.28e-6
+// (2.26e-6 after a first sum on BF16 parts) against 6.9e-7 over all q, and is
+// 5.5e-7 with the signs (9.3e-7 in FP32 instructions).
+__device__ __forceinline__ bool column_negated(int64_t col) { return (uint32_t)col * 0x9E3779B1u >> 31; }
+
 // Packed operands of an FP32 product C = A B (pack.hip): rows of A and columns
 // of B scaled by powers of two and held as two binary16 values per real value.
 struct PackedOperands {
@@ -72,7 +82,7 @@ struct PackedOperands {
   const void* B = nullptr;
   int64_t lda = 0, ldb = 0;        // packed_ld of M and N
   float inv_a = 1.f;               // 1 / the scale of A's values
-  const float* inv_b = nullptr;    // [N], 1 / the scale of each column
+  const float* inv_b = nullptr;    // [N], 1 / the scale of each column, whose sign is column_negated's
   // grouped products: the rows of A are picked by each problem's index list
   // from `nrows` kept row by row (pack.hip), packed_row_bytes each
   int64_t nrows = 0;

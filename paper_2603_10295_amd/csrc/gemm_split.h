@@ -46,7 +46,9 @@ typedef SplitShape<2, 2, 1, 2> Split64;    // 64x128, for M <= 64
 
 // x[0..15] = eight complex values (re, im); writes the planes of the eight re
 // and the eight im values to dst[p * plane]
-__device__ __forceinline__ void split_store(const float (&x)[16], uint32_t im_sign, U4* dst, int plane) {
+// (sign bits flipped by re_sign and im_sign)
+__device__ __forceinline__ void split_store(const float (&x)[16], uint32_t re_sign, uint32_t im_sign, U4* dst,
+                                            int plane) {
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
     U4 pl[kSplitNp];
@@ -56,7 +58,7 @@ __device__ __forceinline__ void split_store(const float (&x)[16], uint32_t im_si
 #pragma unroll
       for (int p = 0; p < kSplitNp; ++p) {
         const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(F2{a, b}, Bf2));
-        pl[p][h] = part == 1 ? w ^ im_sign : w;
+        pl[p][h] = w ^ (part == 1 ? im_sign : re_sign);
         if (p + 1 < kSplitNp) {   // the rest, exact
           a -= __uint_as_float(w << 16);
           b -= __uint_as_float(w & 0xffff0000u);
@@ -146,9 +148,12 @@ __device__ __forceinline__ void split_mainloop(const TileJob<float>& j, int64_t 
           if (i >= left) x[t][2 * i] = x[t][2 * i + 1] = 0.f;
       }
       if (is_a)
-        split_store(x[t], sa, smem + (g & 1) * S::group_a + (g >> 1) * 64 + lane, S::BM);
-      else if (g < S::GA + S::GB)
-        split_store(x[t], sb, smem + S::base_b + (g & 1) * S::group_b + ((g - S::GA) >> 1) * 64 + lane, S::BN);
+        split_store(x[t], 0u, sa, smem + (g & 1) * S::group_a + (g >> 1) * 64 + lane, S::BM);
+      else if (g < S::GA + S::GB) {
+        const int col = ((g - S::GA) >> 1) * 64 + lane;
+        const uint32_t flip = column_negated(n0 + col) ? 0x80008000u : 0u;
+        split_store(x[t], flip, sb ^ flip, smem + S::base_b + (g & 1) * S::group_b + col, S::BN);
+      }
     }
   };
 #pragma unroll
@@ -217,6 +222,15 @@ __device__ __forceinline__ void split_mainloop(const TileJob<float>& j, int64_t 
     if (more) {
       stash(k0 + kSplitK);
       __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < S::FN; ++c) {
+    const float sign = column_negated(n0 + wn * 32 * S::FN + c * 32 + (lane & 31)) ? -1.f : 1.f;
+#pragma unroll
+    for (int i = 0; i < S::FM; ++i) {
+      acc_r[i][c] = acc_r[i][c] * sign;
+      acc_i[i][c] = acc_i[i][c] * sign;
     }
   }
 }

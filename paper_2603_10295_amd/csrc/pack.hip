@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(256)
   red[wave][lane] = bad ? __builtin_inff() : m;   // fmaxf drops a NaN
   __syncthreads();
   m = fmaxf(fmaxf(red[0][lane], red[1][lane]), fmaxf(red[2][lane], red[3][lane]));
-  const float sc = column_scale(m);
+  const float sc = column_negated(b * N + n) ? -column_scale(m) : column_scale(m);
   if (wave == 0 && ok) inv_scale[n] = 1.f / sc;
   const int64_t groups = (K + 15) / 16 * 2;
   for (int64_t g = wave; g < groups; g += 4) {

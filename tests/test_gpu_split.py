@@ -240,3 +240,23 @@ def test_compensated_rows(run, nk, nw, na):
                           flags=ephw.OUT_G | ephw.OUT_BAND_SUM | ephw.OUT_WANNIER)["g"][0]
     ref, mag = re_sums(s, k)
     assert np.all(np.abs(got - ref) <= 2 * (64 + 65 // 32 + 4) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("nk", [40, 520])
+def test_error_where_the_phases_agree(run, nk):
+    """Both phase sums at q = 0 and around k = 0, where a one-sided rounding of
+    the first sum would add up over the lattice vectors of the second: the
+    error against 64 bits is no larger than that of the FP32 instructions (a
+    call that also returns band sums)."""
+    from paper_2603_10295_amd import ephw
+    s = system((10, 10, 10), 8, 1, 13, rp=synth.box((8, 8, 8)))
+    k = 1e-3 * np.random.default_rng(nk).random((nk, 3))
+    q = np.zeros((1, 3))
+    pe = oracle.phases(k, s.r_e)
+    ref = (pe @ s.g.astype(np.complex128).sum(0).reshape(len(s.r_e), -1)).reshape(nk, s.nm, 8, 8)
+    h = run.system(s)
+    err = []
+    for flags in (ephw.OUT_G, ephw.OUT_G | ephw.OUT_BAND_SUM):
+        g = run.interpolate(h, k, q, 1, flags=flags | ephw.OUT_WANNIER, want_eps_kq=False)["g"][0]
+        err.append(np.linalg.norm(g - ref) / np.linalg.norm(ref))
+    assert err[0] <= err[1]
