@@ -117,8 +117,7 @@ struct TileShape {
 // Wave (wm, wn) holds W for 64 k points (rows) and 64 columns, i.e. 64/Nw^2
 // whole (q, nu) blocks of Nw x Nw.  Its rows go through LDS in two halves of
 // 32 k points (the wave's own 32 x 65 complex region; the K loop's stages are
-// free by then): put(h, wl, LDW) writes the wave's rows of half h to wl, in
-// the accumulator layout of the caller's K loop.  Two lanes share a k point and split its 64/Nw rows (b, m')
+// free by then).  Two lanes share a k point and split its 64/Nw rows (b, m')
 // into four-row groups: Nw = 8, one block, rows 4s..4s+3; Nw = 4, blocks
 // 2s, 2s+1, all four rows (s = lane parity).  Per half:
 //   1. T_b[m'][:] = W_b[m'][:] V(k) for the lane's rows, written over them in
@@ -133,14 +132,16 @@ struct TileShape {
 //      the k point's rows and stored per wave column.
 // Sums run in a fixed order (shuffles and a fixed wave order), so the results
 // are deterministic.
-template <int NW, typename Put>
+template <int NW>
 __device__ __forceinline__ void band_epilogue(const TileJob<float>& j, const BandEpilogue& B, int64_t m0, int64_t n0,
-                                              Put put, float* smem) {
+                                              typename Mfma<float>::v4 (&acc_r)[4][4],
+                                              typename Mfma<float>::v4 (&acc_i)[4][4], float* smem) {
   static_assert(NW == 4 || NW == 8, "four-row groups of whole blocks");
   constexpr int TM = 64, TN = 64, HR = 32, LDW = TN + 1;
   constexpr int NW2 = NW * NW, NB = 8 / NW, MR = 4;   // blocks per lane, rows per block group
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % 2, wn = wave / 2;
+  const int lrow = lane >> 4, lcol = lane & 15;
   float* wl = smem + wave * (HR * LDW * 2);
   const int kl = lane >> 1, sb = lane & 1;               // k point within the half, lane of the pair
   const int64_t cw0 = n0 + wn * TN;                      // first column of the wave
@@ -180,7 +181,19 @@ __device__ __forceinline__ void band_epilogue(const TileJob<float>& j, const Ban
       __syncthreads();   // every wave is done with the K loop's LDS stages
     else
       wave_sync();       // this wave is done with the first half's rows
-    put(h, wl, LDW);
+    // (the value is chosen, not the store: a branch on h around the stores kept
+    // the accumulators in scratch here, 1.15x the kernel's time at Nw = 4)
+#pragma unroll
+    for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = ii * 16 + Mfma<float>::row(lrow, v), col = jj * 16 + lcol;
+          const float re = h == 0 ? acc_r[ii][jj][v] : acc_r[2 + ii][jj][v];
+          const float im = h == 0 ? acc_i[ii][jj][v] : acc_i[2 + ii][jj][v];
+          *reinterpret_cast<float2*>(wl + 2 * (row * LDW + col)) = make_float2(re, im);
+        }
     wave_sync();
     const int64_t k = m0 + wm * TM + h * HR + kl;
     const bool kok = k < j.M;
@@ -986,7 +999,7 @@ __device__ __forceinline__ void gemm_tile(const TileJob<T>& j, int64_t m0, int64
     if constexpr (BANDNW == 16)
       band_epilogue_mfma8(j, *band, m0, n0, put, smem);
     else
-      band_epilogue<BANDNW>(j, *band, m0, n0, put, smem);
+      band_epilogue<BANDNW>(j, *band, m0, n0, acc_r, acc_i, smem);
     return;
   }
   // --- epilogue: lane holds column lcol of every block, rows per Mfma<T>::row --
