@@ -58,6 +58,22 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// Place of value i among at(0 .. n - 1) in ascending order, ties by index.  The
+// places index memory, so they are a permutation for every input: where a value
+// is NaN (which compares below nothing and would share place 0) each keeps its own.
+template <typename At>
+__host__ __device__ __forceinline__ int ascending_place(At at, int n, int i) {
+  const double mine = at(i);
+  int place = 0;
+  bool order = true;
+  for (int j = 0; j < n; ++j) {
+    const double o = at(j);
+    order = order && o == o;
+    place += (o < mine) || (o == mine && j < i);
+  }
+  return order ? place : i;
+}
+
 // ---------------------------------------------------------------------------
 // phonon-limited linewidth weights (the downstream reduction of stored or
 // freshly rotated matrix elements): parameters and occupations

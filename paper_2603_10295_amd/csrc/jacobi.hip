@@ -368,15 +368,7 @@ __device__ __forceinline__ void jacobi_small_body(const double* __restrict__ H, 
   }
   if (!converged && lane == 0) atomicOr(status, kStatusNoConv);
   // ascending order (ties by index), then each column's largest entry made real positive
-  if (lane < n) {
-    const double li = A[lane * N2 + lane].x;
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const double lj = A[j * N2 + j].x;
-      rank += (lj < li) || (lj == li && j < lane);
-    }
-    perm[rank] = lane;
-  }
+  if (lane < n) perm[ascending_place([&](int j) { return A[j * N2 + j].x; }, n, lane)] = lane;
   wave_sync();
   if (lane < n) {
     const int src = perm[lane];
@@ -622,15 +614,7 @@ __device__ __forceinline__ void jacobi_small_body_pos(JobAt job_at, uint32_t* st
     double2* A = slices + s * SL;
     int* perm = reinterpret_cast<int*>(A + PO + L::prm_elems + L::fix_elems);
     const int n = job_at(s).n;
-    if (lg < n) {
-      const double li = A[at_a(lg, lg)].x;
-      int rank = 0;
-      for (int j = 0; j < n; ++j) {
-        const double lj = A[at_a(j, j)].x;
-        rank += (lj < li) || (lj == li && j < lg);
-      }
-      perm[rank] = lg;
-    }
+    if (lg < n) perm[ascending_place([&](int j) { return A[at_a(j, j)].x; }, n, lg)] = lg;
   }
   wave_sync();
 #pragma unroll
@@ -1014,15 +998,7 @@ __global__ void __launch_bounds__(kLargeThreads)
   double2* vb = V + (int64_t)blockIdx.x * n * n;
   double* eo = eps + (int64_t)blockIdx.x * n;
   if (tid == 0 && !state[3 * blockIdx.x]) atomicOr(status, kStatusNoConv);
-  for (int i = tid; i < n; i += kLargeThreads) {
-    const double li = A[i * n + i].x;
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const double lj = A[j * n + j].x;
-      rank += (lj < li) || (lj == li && j < i);
-    }
-    perm[rank] = i;
-  }
+  for (int i = tid; i < n; i += kLargeThreads) perm[ascending_place([&](int j) { return A[j * n + j].x; }, n, i)] = i;
   __syncthreads();
   for (int c = tid; c < n; c += kLargeThreads) {
     const int src = perm[c];

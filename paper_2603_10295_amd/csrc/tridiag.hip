@@ -337,18 +337,10 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
 
   // ascending order
   if (live) {
-    const double mine = sd[r * M + mt];
-    int place = 0;
-    bool order = true;                           // NaN eigenvalues (a matrix that is not finite) would share ranks
-    for (int j = 0; j < n; ++j) {
-      const double o = sd[j * M + mt];
-      order = order && o == o;
-      place += (o < mine) || (o == mine && j < r);
-    }
-    if (!order) place = r;
+    const int place = ascending_place([&](int j) { return sd[j * M + mt]; }, n, r);
     rank[mt * N + r] = place;
     const double* tail = reinterpret_cast<const double*>(H + b * n * n);
-    eps[b * n + place] = ldexp(mine, (int)tail[n]);
+    eps[b * n + place] = ldexp(sd[r * M + mt], (int)tail[n]);
   }
   // phases, CB columns at a time: rows to LDS, a thread per column
 #pragma unroll
