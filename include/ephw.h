@@ -74,11 +74,12 @@ typedef int32_t ephw_status;
 #define EPHW_FP32        1  /* complex64 GEMMs on FP32 MFMA, g stored c64.  A call
                                that returns g alone may run its phase sums on the
                                16-bit matrix cores with every value split in two
-                               or three parts (error against FP64 no larger), and
-                               its eigensolves by tridiagonalisation: its g then
-                               differs in rounding from that of a call which also
-                               returns band sums or the loss, and within
-                               degenerate blocks by a unitary mixing */
+                               or three parts (error against FP64 no larger): its
+                               g then differs in rounding from that of a call
+                               which also returns band sums or the loss.  So do
+                               its bands at interpolated k+q, solved by
+                               tridiagonalisation, and their states also by a
+                               unitary mixing within degenerate blocks */
 #define EPHW_FP32_COMP   2  /* compensated FP32: as EPHW_FP32, but each phase sum
                                accumulates in K blocks of 32 (fresh FP32 MFMA
                                accumulators per block, block sums added in FP32;
@@ -186,7 +187,9 @@ ephw_status ephw_bands(ephw_system* sys, const double* k, int64_t nk, double* ep
      lam   [nq][nm] f64 eigenvalues of D(q), or NULL
      omega [nq][nm] f64 sqrt(|lam|), or NULL
      evecs [nq][nm][nm] c128 eigenvectors e (columns), or NULL  (u = e/sqrt(M)),
-           16-byte aligned (EPHW_EINVAL otherwise) */
+           16-byte aligned (EPHW_EINVAL otherwise)
+   The modes nu of every other call are these, also within degenerate blocks
+   (to complex64 rounding where g is complex64). */
 ephw_status ephw_phonons(ephw_system* sys, const double* q, int64_t nq, double* lam,
                          double* omega, void* evecs, void* stream);
 

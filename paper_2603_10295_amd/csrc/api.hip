@@ -19,7 +19,7 @@ void set_error(const std::string& msg) { g_last_error = msg; }
 
 ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64_t nr, const double* mats, int dim,
                            double* out_eps, double* out_v, double* hk, double* jwork, bool stages, hipStream_t st,
-                           bool any_rounding) {
+                           bool c64) {
   const int64_t d2 = (int64_t)dim * dim;
   Stage sg_(s, EPHW_STAGE_EIG, st, stages);
   GemmParams p;
@@ -33,7 +33,8 @@ ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64
   p.C = hk;
   p.ldc = d2;
   EPHW_TRY(cgemm(0, p, st));
-  if (any_rounding && tridiag_better(dim, n)) return tridiag_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, st);
+  if (c64 && tridiag_large_better(dim, n))
+    return tridiag_large_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, s->ctx->max_sweeps, st);
   return jacobi_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, s->ctx->max_sweeps, st);
 }
 
@@ -780,7 +781,8 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     Stage sg_(s, EPHW_STAGE_PHASE, st, stages);
     EPHW_TRY(phase_matrix(0, q, nq, s->r_c, s->w_c, s->nc, w.pqc, st));
   }
-  EPHW_TRY(interp_eigh_ws(s, w.pqc, nq, s->nc, s->c_scaled, nm, w.lam, w.e, w.hk, w.jwork, stages, st, r.any_rounding));
+  EPHW_TRY(interp_eigh_ws(s, w.pqc, nq, s->nc, s->c_scaled, nm, w.lam, w.e, w.hk, w.jwork, stages, st,
+                          kind != 0 && r.any_rounding));
   {
     Stage sg_(s, EPHW_STAGE_OTHER, st, stages);
     if (omega) EPHW_TRY(abs_sqrt(w.lam, omega, nq * nm, st));
@@ -822,7 +824,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
       // total (eigenvalues then exact to ~1e-20 relative, eigenvectors to ~1e-10,
       // far below the complex64 rounding they are cast to); FP64 at 1e-14
       if (r.any_rounding && tridiag_better(nw, (nq < qb ? nq : qb) * nk))   // for all batches of the call
-        EPHW_TRY(tridiag_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, st));
+        EPHW_TRY(tridiag_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, s->ctx->status, st));
       else
         EPHW_TRY(jacobi_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, s->ctx->max_sweeps,
                              st, kind == 0 ? 1e-28 : 1e-20));

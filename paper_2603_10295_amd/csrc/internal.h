@@ -85,10 +85,13 @@ inline size_t csize(int kind) { return kind == 0 ? 16 : 8; }
 // FP64 interpolation + eigensolve: out_eps [n][dim], out_v c128 [n][dim][dim]
 // from A = phases [n][nr] (c128) and B = R-space matrices [nr][dim*dim] (c128),
 // with caller-given buffers: hk [n][dim][dim] c128 and, for dim > 32, jwork of
-// jacobi_work_doubles(dim, n) doubles
+// jacobi_work_doubles(dim, n) doubles.  c64: the vectors are used rounded to
+// complex64 only.  The mode vectors of D(q) are the same basis in every call,
+// also inside degenerate blocks: a loss, its gradient, band sums per mode and
+// the modes of ephw_phonons belong together.
 ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64_t nr, const double* mats, int dim,
                            double* out_eps, double* out_v, double* hk, double* jwork, bool stages, hipStream_t st,
-                           bool any_rounding = false);
+                           bool c64 = false);
 
 ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const int32_t* kq_index, int64_t q_offset,
                               uint32_t flags, void* g_out, double* band_sum, double* loss, uint64_t loss_seed,

@@ -829,16 +829,22 @@ __device__ __forceinline__ void rotate_rows(const LargeRot& r, double2& x, doubl
 // number of pairs with two real players in a round, and the log's stride
 __host__ __device__ inline int large_pairs(int n) { return n / 2; }
 
-// Per matrix, state[0]: converged; state[1 + parity]: rounds in the log that
-// the sweep of that parity wrote.  Sweep number `sweep` of matrix b.
+// Per matrix, state[0]: converged, or kLeaveOut; state[1 + parity]: rounds in the
+// log that the sweep of that parity wrote.  Sweep number `sweep` of matrix b.
+// some: state[0] is set before the first sweep, to kLeaveOut for the matrices
+// whose eps and V are to stay as they are.
 __device__ __forceinline__ void jacobi_sweep(double2* __restrict__ H, int n, LargeRot* __restrict__ log,
                                              int* __restrict__ state, const uint32_t* __restrict__ status, int sweep,
-                                             int b) {
+                                             int b, bool some) {
   __shared__ LargeRot prm[128];
   __shared__ int ip[128], iq[128];   // players of a pair, iq = -1 for the pair with the missing player
   __shared__ double red[kLargeThreads / 64];
   const int tid = threadIdx.x;
   int* st = state + 3 * b;
+  if (sweep == 0 && some && st[0] == kLeaveOut) {
+    if (tid == 0) st[1] = -1;
+    return;
+  }
   if ((sweep > 0 && st[0]) || sweep >= sweep_limit(status)) {
     if (tid == 0) {
       if (sweep == 0) st[0] = 0;
@@ -929,7 +935,7 @@ __device__ __forceinline__ void jacobi_replay(double2* __restrict__ V, int n, co
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row0 = (part * (kLargeThreads / 64) + wave) * kReplayRows;
   const int rounds = state[3 * b + 1 + (sweep & 1)];
-  if (row0 >= n || (rounds == 0 && sweep > 0)) return;
+  if (row0 >= n || rounds < 0 || (rounds == 0 && sweep > 0)) return;
   const int n2 = n + (n & 1), full = large_pairs(n);
   const LargeRot* lg = log + ((int64_t)b * 2 + (sweep & 1)) * (n2 - 1) * full;
   double2* vb = V + (int64_t)b * n * n;
@@ -977,11 +983,11 @@ __device__ __forceinline__ void jacobi_replay(double2* __restrict__ V, int n, co
 __global__ void __launch_bounds__(kLargeThreads)
     jacobi_sweep_kernel(double2* __restrict__ H, double2* __restrict__ V, int n, int nb, int parts,
                         LargeRot* __restrict__ log, int* __restrict__ state, const uint32_t* __restrict__ status,
-                        int sweep) {
+                        int sweep, bool some) {
   extern __shared__ double2 replay_rows[];
   const int b = blockIdx.x;
   if (b < nb)
-    jacobi_sweep(H, n, log, state, status, sweep, b);
+    jacobi_sweep(H, n, log, state, status, sweep, b, some);
   else
     jacobi_replay(V, n, log, state, sweep - 1, (b - nb) / parts, (b - nb) % parts, replay_rows);
 }
@@ -990,7 +996,8 @@ __global__ void __launch_bounds__(kLargeThreads)
 // columns of V permuted and scaled in place, a row at a time.
 __global__ void __launch_bounds__(kLargeThreads)
     jacobi_finish_kernel(const double2* __restrict__ H, int n, double* __restrict__ eps, double2* __restrict__ V,
-                         const int* __restrict__ state, uint32_t* status) {
+                         const int* __restrict__ state, uint32_t* status, bool some) {
+  if (some && state[3 * blockIdx.x] == kLeaveOut) return;
   __shared__ int perm[256];
   __shared__ double2 ph[256], row[kLargeThreads / 64][256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1034,7 +1041,39 @@ constexpr int64_t kLargeChunk = 1024;  // matrices per large-n launch (bounds th
 // doubles of one matrix's two logs: n2 - 1 rounds of n / 2 rotations each
 inline int64_t log_doubles(int n) { return (int64_t)4 * 2 * (n + (n & 1) - 1) * large_pairs(n); }
 
+// nb <= kLargeChunk matrices
+ephw_status launch_large(double2* h, int64_t nb, int n, double* eps, double2* v, double* work, uint32_t* status,
+                         int max_sweeps, bool some, hipStream_t s) {
+  const size_t lds = (size_t)(kLargeThreads / 64) * kReplayRows * n * sizeof(double2);
+  const int parts = (int)ceil_div(n, (kLargeThreads / 64) * kReplayRows);
+  EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_sweep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  LargeRot* log = reinterpret_cast<LargeRot*>(work);
+  int* state = jacobi_large_state(work, n, nb);
+  for (int sweep = 0; sweep <= (max_sweeps > 0 ? max_sweeps : 1); ++sweep) {
+    const int64_t grid = nb + (sweep > 0 ? nb * parts : 0);
+    hipLaunchKernelGGL(jacobi_sweep_kernel, dim3((unsigned)grid), dim3(kLargeThreads), lds, s, h, v, n, (int)nb, parts,
+                       log, state, status, sweep, some);
+    EPHW_CHECK_LAUNCH();
+  }
+  hipLaunchKernelGGL(jacobi_finish_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, eps, v, state, status,
+                     some);
+  EPHW_CHECK_LAUNCH();
+  return EPHW_OK;
+}
+
 }  // namespace
+
+int* jacobi_large_state(double* work, int n, int64_t nb) { return reinterpret_cast<int*>(work + log_doubles(n) * nb); }
+
+ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* V, double* work, uint32_t* status,
+                             int max_sweeps, hipStream_t s) {
+  if (n <= kSmallN || n > 256 || nb < 1 || nb > kLargeChunk || !work) {
+    set_error("jacobi_eigh_some: a chunk of matrices of order 33 to 256 and their workspace");
+    return EPHW_EINVAL;
+  }
+  return launch_large(reinterpret_cast<double2*>(H), nb, n, eps, reinterpret_cast<double2*>(V), work, status,
+                      max_sweeps, true, s);
+}
 
 int64_t jacobi_work_doubles(int n, int64_t batch) {
   if (n <= kSmallN) return 0;
@@ -1089,24 +1128,10 @@ ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V,
     set_error("jacobi_eigh: large matrices need a workspace");
     return EPHW_EINVAL;
   }
-  const size_t lds = (size_t)(kLargeThreads / 64) * kReplayRows * n * sizeof(double2);
-  const int parts = (int)ceil_div(n, (kLargeThreads / 64) * kReplayRows);
-  EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_sweep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   for (int64_t b0 = 0; b0 < batch; b0 += kLargeChunk) {
     const int64_t nb = (batch - b0) < kLargeChunk ? (batch - b0) : kLargeChunk;
-    double2* h = reinterpret_cast<double2*>(H) + b0 * n * n;
-    double2* v = reinterpret_cast<double2*>(V) + b0 * n * n;
-    LargeRot* log = reinterpret_cast<LargeRot*>(work);
-    int* state = reinterpret_cast<int*>(work + log_doubles(n) * nb);
-    for (int sweep = 0; sweep <= (max_sweeps > 0 ? max_sweeps : 1); ++sweep) {
-      const int64_t grid = nb + (sweep > 0 ? nb * parts : 0);
-      hipLaunchKernelGGL(jacobi_sweep_kernel, dim3((unsigned)grid), dim3(kLargeThreads), lds, s, h, v, n, (int)nb,
-                         parts, log, state, status, sweep);
-      EPHW_CHECK_LAUNCH();
-    }
-    hipLaunchKernelGGL(jacobi_finish_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, eps + b0 * n, v,
-                       state, status);
-    EPHW_CHECK_LAUNCH();
+    EPHW_TRY(launch_large(reinterpret_cast<double2*>(H) + b0 * n * n, nb, n, eps + b0 * n,
+                          reinterpret_cast<double2*>(V) + b0 * n * n, work, status, max_sweeps, false, s));
   }
   return EPHW_OK;
 }

@@ -22,14 +22,26 @@ int64_t jacobi_work_doubles(int n, int64_t batch);
 ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
                         int max_sweeps, hipStream_t s, double off_tol2 = 1e-28);
 
-// The same eigenproblem (and workspace) by tridiagonalisation and QL (tridiag.hip),
-// several times faster; eigenvectors agree with jacobi_eigh's to rounding over
-// the gaps, not bit for bit.  H is overwritten.  The sweep limit bounds the QL
-// steps per eigenvalue.
+// Orders above 32, at most 1024 matrices, some of them left out: those whose
+// state (3 ints a matrix in the workspace, here) holds kLeaveOut keep their eps and V.
+constexpr int kLeaveOut = 2;
+int* jacobi_large_state(double* work, int n, int64_t nb);
+ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* V, double* work, uint32_t* status,
+                             int max_sweeps, hipStream_t s);
+
+// The same eigenproblem by tridiagonalisation and QL (tridiag.hip), several
+// times faster, for orders up to 32: eigenvectors agree with jacobi_eigh's to
+// rounding over the gaps, in degenerate blocks within a unitary mixing.  H is
+// overwritten.  The sweep limit bounds the QL steps per eigenvalue.
 // tridiag_better: the rule for taking it.
 bool tridiag_better(int n, int64_t batch);
-ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                         hipStream_t s);
+ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s);
+// Orders 33 to 256 (and jacobi_eigh's workspace): matrices with eigenvalues
+// closer than 1e-6 of the largest are solved by jacobi_eigh's kernels, so that
+// the vectors of every matrix agree with its to complex64 rounding.
+bool tridiag_large_better(int n, int64_t batch);
+ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                               int max_sweeps, hipStream_t s);
 
 // many small (n <= 32) eigensolves of different orders in one launch;
 // matrix m of the launch belongs to the job with the largest block_base <= m

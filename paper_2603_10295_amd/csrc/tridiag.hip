@@ -379,7 +379,7 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
 
 // ---------------------------------------------------------------------------
 // Orders 33 to 256: the same method over a workspace, one matrix per workgroup
-// in the serial parts.  The reduction works in place (from L2: n^2 complex
+// in the serial parts.  The reduction works in V's place (from L2: n^2 complex
 // values do not fit the LDS above n = 100) and leaves v_k in row k; QL runs on
 // the real tridiagonal with its rotations logged to memory; the rotations are
 // applied to the rows of a real Z, 64 rows per wavefront; the reflectors, last
@@ -390,13 +390,18 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
 // ---------------------------------------------------------------------------
 constexpr int kBigThreads = 1024, kBigMax = 256, kBigRounds = 3;
 
+// Vectors of eigenvalues closer than this times the largest are not those of
+// the Jacobi solver (a rounding of 1e-15 over the gap, against the 6e-8 of
+// complex64): such a matrix is solved by Jacobi.
+constexpr double kCloseGap = 1e-6;
+
 // A matrix's part of the workspace: jacobi_work_doubles' share, 4 n (n - 1)
 // doubles or more, holds the 3 n^2 + 9 n + 4 of these for n >= 33.
 struct BigWork {
   double2 *log, *delta;       // [n^2] rotations (c, s) of a round; [n] phases of Q's columns
   double *zt, *d, *e, *tau;   // Z transposed [col][row]; [n] each
   uint2* step;                // [4 n] of a round: l | m << 16, first rotation
-  int* state;                 // scale exponent, next eigenvalue, steps of the round
+  int* state;                 // scale exponent, next eigenvalue, steps of the round, eigenvalues too close
   __device__ BigWork(double* base, int n) {
     const int64_t n2 = (int64_t)n * n;
     log = reinterpret_cast<double2*>(base);
@@ -422,19 +427,21 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 }
 
 __global__ void __launch_bounds__(kBigThreads)
-    reduce_big_kernel(double2* __restrict__ H, int n, double* __restrict__ work, int64_t wstride) {
+    reduce_big_kernel(const double2* __restrict__ H, int n, double2* __restrict__ V, double* __restrict__ work,
+                      int64_t wstride) {
   __shared__ double2 sv[kBigMax], sw[kBigMax], part[kBigThreads];
   __shared__ double red[2][kBigThreads / 64];
   const int tid = threadIdx.x, W = (n + 63) / 64 * 64, G = kBigThreads / W;
   const int c = tid % W, g = tid / W;            // column; thread g takes the rows r = g modulo G
   const bool own = g < G && c < n;
-  double2* A = H + (int64_t)blockIdx.x * n * n;
+  const double2* h = H + (int64_t)blockIdx.x * n * n;
+  double2* A = V + (int64_t)blockIdx.x * n * n;
   const BigWork w(work + (int64_t)blockIdx.x * wstride, n);
 
   double big = 0.0;
   if (own)
     for (int r = g; r < n; r += G) {
-      const double2 x = A[(int64_t)r * n + c];
+      const double2 x = h[(int64_t)r * n + c];
       big = fmax(big, fmax(fabs(x.x), r == c ? 0.0 : fabs(x.y)));
     }
   big = group_max<64>(big);
@@ -446,10 +453,11 @@ __global__ void __launch_bounds__(kBigThreads)
   if (tid == 0) {
     w.state[0] = ex;
     w.state[1] = 0;
+    w.state[3] = 0;
   }
   if (own)
     for (int r = g; r < n; r += G) {
-      const double2 x = A[(int64_t)r * n + c];
+      const double2 x = h[(int64_t)r * n + c];
       A[(int64_t)r * n + c] = make_double2(x.x * scale, r == c ? 0.0 : x.y * scale);
     }
   __syncthreads();
@@ -665,16 +673,17 @@ __global__ void __launch_bounds__(64) rotate_big_kernel(int n, double* __restric
     for (int c = 0; c < n; ++c) w.zt[(int64_t)c * n + r] = z[c * 64];
 }
 
-// Column j of V = H_0 .. H_{n-2} diag(delta) z_j, its phase and its place
+// Column j of V = H_0 .. H_{n-2} diag(delta) z_j, its phase and its place, to
+// the workspace in place of the log (V still holds the reflectors)
 __global__ void __launch_bounds__(256)
-    back_big_kernel(const double2* __restrict__ H, int n, const double* __restrict__ work, int64_t wstride,
-                    double* __restrict__ eps, double2* __restrict__ V) {
+    back_big_kernel(const double2* __restrict__ V, int n, double* __restrict__ work, int64_t wstride,
+                    double* __restrict__ eps) {
   constexpr int NX = kBigMax / 64;
   const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= n) return;
   const int64_t b = blockIdx.y;
-  const BigWork w(const_cast<double*>(work) + b * wstride, n);
-  const double2* A = H + b * n * n;
+  const BigWork w(work + b * wstride, n);
+  const double2* A = V + b * n * n;
   double2 x[NX], v[NX];
 #pragma unroll
   for (int u = 0; u < NX; ++u) {
@@ -742,27 +751,41 @@ __global__ void __launch_bounds__(256)
   const double mine = w.d[j];
   int place = 0;
   bool order = true;
+  double top = 0.0, gap = HUGE_VAL;
   for (int i = lane; i < n; i += 64) {
     const double o = w.d[i];
     order = order && o == o;
     place += (o < mine) || (o == mine && i < j);
+    top = fmax(top, fabs(o));
+    if (i != j) gap = fmin(gap, fabs(o - mine));
   }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) place += __shfl_xor(place, off, 64);
+  if (-group_max<64>(-gap) <= kCloseGap * group_max<64>(top)) w.state[3] = 1;   // (of all columns, the same value)
   if (!__all(order)) place = j;                  // NaN eigenvalues (a matrix that is not finite) would share places
   if (lane == 0) eps[b * n + place] = ldexp(mine, w.state[0]);
 #pragma unroll
   for (int u = 0; u < NX; ++u) {
     const int r = lane + 64 * u;
     if (r < n)
-      V[(b * n + r) * n + place] = make_double2(x[u].x * fix.x - x[u].y * fix.y, x[u].x * fix.y + x[u].y * fix.x);
+      w.log[r * n + place] = make_double2(x[u].x * fix.x - x[u].y * fix.y, x[u].x * fix.y + x[u].y * fix.x);
   }
 }
 
+// V out of the workspace, and which matrices the Jacobi kernels leave out
+__global__ void __launch_bounds__(256)
+    store_big_kernel(int n, double* __restrict__ work, int64_t wstride, double2* __restrict__ V,
+                     int* __restrict__ state) {
+  const int64_t b = blockIdx.y, i = (int64_t)blockIdx.x * 256 + threadIdx.x, nn = (int64_t)n * n;
+  const BigWork w(work + b * wstride, n);
+  if (i < nn) V[b * nn + i] = w.log[i];
+  if (i == 0) state[3 * b] = w.state[3] ? 0 : kLeaveOut;
+}
+
 ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                       hipStream_t s) {
+                       int max_sweeps, hipStream_t s) {
   if (!work) {
-    set_error("tridiag_eigh: orders above 32 need a workspace");
+    set_error("tridiag_large_eigh: needs a workspace");
     return EPHW_EINVAL;
   }
   constexpr int64_t kChunk = 1024;               // that of jacobi_work_doubles
@@ -772,8 +795,8 @@ ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, 
   EPHW_HIP(hipFuncSetAttribute((const void*)rotate_big_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   for (int64_t b0 = 0; b0 < batch; b0 += chunk) {
     const unsigned nb = (unsigned)(batch - b0 < chunk ? batch - b0 : chunk);
-    double2* h = reinterpret_cast<double2*>(H) + b0 * n * n;
-    hipLaunchKernelGGL(reduce_big_kernel, dim3(nb), dim3(kBigThreads), 0, s, h, n, work, wstride);
+    double2 *h = reinterpret_cast<double2*>(H) + b0 * n * n, *v = reinterpret_cast<double2*>(V) + b0 * n * n;
+    hipLaunchKernelGGL(reduce_big_kernel, dim3(nb), dim3(kBigThreads), 0, s, h, n, v, work, wstride);
     EPHW_CHECK_LAUNCH();
     for (int round = 0; round < kBigRounds; ++round) {
       hipLaunchKernelGGL(ql_big_kernel, dim3(nb), dim3(64), 0, s, n, work, wstride, status, round + 1 == kBigRounds);
@@ -782,9 +805,14 @@ ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, 
                          round == 0);
       EPHW_CHECK_LAUNCH();
     }
-    hipLaunchKernelGGL(back_big_kernel, dim3((unsigned)ceil_div(n, 4), nb), dim3(256), 0, s, h, n, work, wstride,
-                       eps + b0 * n, reinterpret_cast<double2*>(V) + b0 * n * n);
+    hipLaunchKernelGGL(back_big_kernel, dim3((unsigned)ceil_div(n, 4), nb), dim3(256), 0, s, v, n, work, wstride,
+                       eps + b0 * n);
     EPHW_CHECK_LAUNCH();
+    hipLaunchKernelGGL(store_big_kernel, dim3((unsigned)ceil_div((int64_t)n * n, 256), nb), dim3(256), 0, s, n, work,
+                       wstride, v, jacobi_large_state(work, n, nb));
+    EPHW_CHECK_LAUNCH();
+    EPHW_TRY(jacobi_eigh_some(reinterpret_cast<double*>(h), nb, n, eps + b0 * n, reinterpret_cast<double*>(v), work,
+                              status, max_sweeps, s));
   }
   return EPHW_OK;
 }
@@ -816,20 +844,14 @@ ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint
 // 52 us; n = 11, 1024: 81 and 78, 4096: 104 and 82; n = 16, 1024: 117 and 138,
 // 4096: 290 and 149; n^3 x matrices is near 4 million where they meet.  From 17
 // to 32 this one is ahead at every count (n = 24: 449 and 259 us at 64 matrices).
-// From 33 to 63 few matrices are level (n = 33: 469 and 445 us, n = 48: 680 and
-// 750), 512 are not (n = 48: 2824 and 1371); n = 66, one matrix: 1362 and 1270,
-// n = 150: 9913 and 5409, n = 255, 64 matrices: 73 500 and 18 140.
 bool tridiag_better(int n, int64_t batch) {
-  if (n <= 16) return n > 6 && (int64_t)n * n * n * batch >= 4000000;
-  if (n <= 32 || n >= 64) return n <= kBigMax;
-  return batch >= 256;
+  return n > 16 ? n <= 32 : n > 6 && (int64_t)n * n * n * batch >= 4000000;
 }
 
-ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                         hipStream_t s) {
+ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s) {
   if (batch <= 0) return EPHW_OK;
-  if (n < 1 || n > kBigMax) {
-    set_error("tridiag_eigh: matrix order must be in [1, 256]");
+  if (n < 1 || n > 32) {
+    set_error("tridiag_eigh: matrix order must be in [1, 32]");
     return EPHW_EUNSUPPORTED;
   }
   if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
@@ -840,8 +862,29 @@ ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V
   if (n <= 12) return launch<12, 16>(H, batch, n, eps, V, status, s);
   if (n <= 16) return launch<16, 16>(H, batch, n, eps, V, status, s);
   if (n <= 24) return launch<24, 32>(H, batch, n, eps, V, status, s);
-  if (n <= 32) return launch<32, 32>(H, batch, n, eps, V, status, s);
-  return launch_big(H, batch, n, eps, V, work, status, s);
+  return launch<32, 32>(H, batch, n, eps, V, status, s);
+}
+
+// From 33 to 63 few matrices are level with Jacobi (n = 33: 469 by Jacobi and
+// 445 us here, n = 48: 680 and 750), 512 are not (n = 48: 2824 and 1371); n = 66,
+// one matrix: 1362 and 1270, n = 150: 9913 and 5409, n = 255, 64 matrices: 73 500
+// and 18 140.
+bool tridiag_large_better(int n, int64_t batch) {
+  return n > 32 && n <= kBigMax && (n >= 64 || batch >= 256);
+}
+
+ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                               int max_sweeps, hipStream_t s) {
+  if (batch <= 0) return EPHW_OK;
+  if (n <= 32 || n > kBigMax) {
+    set_error("tridiag_large_eigh: matrix order must be in [33, 256]");
+    return EPHW_EUNSUPPORTED;
+  }
+  if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
+    set_error("tridiag_large_eigh: matrices and eigenvectors must be 16-byte aligned complex128 arrays");
+    return EPHW_EINVAL;
+  }
+  return launch_big(H, batch, n, eps, V, work, status, max_sweeps, s);
 }
 
 }  // namespace ephw
