@@ -105,8 +105,9 @@ __global__ void __launch_bounds__((64 * TriShape<N, L>::waves))
   double big = 0.0;
 #pragma unroll
   for (int c = 0; c < N; ++c) {
-    a[c] = live && r < n && c < n ? h[r * n + c] : make_double2(0.0, 0.0);
-    if (c == r) a[c].y = 0.0;
+    // the matrix of jacobi.hip's small solves: the upper triangle and its conjugate
+    a[c] = live && r < n && c < n ? h[c < r ? c * n + r : r * n + c] : make_double2(0.0, 0.0);
+    if (c <= r) a[c].y = c == r ? 0.0 : -a[c].y;
     big = fmax(big, fmax(fabs(a[c].x), fabs(a[c].y)));
     q[c] = make_double2(c == r ? 1.0 : 0.0, 0.0);
   }
@@ -401,7 +402,7 @@ struct BigWork {
   double2 *log, *delta;       // [n^2] rotations (c, s) of a round; [n] phases of Q's columns
   double *zt, *d, *e, *tau;   // Z transposed [col][row]; [n] each
   uint2* step;                // [4 n] of a round: l | m << 16, first rotation
-  int* state;                 // scale exponent, next eigenvalue, steps of the round, eigenvalues too close
+  int* state;                 // scale exponent, next eigenvalue, steps of the round, whether Jacobi takes over
   __device__ BigWork(double* base, int n) {
     const int64_t n2 = (int64_t)n * n;
     log = reinterpret_cast<double2*>(base);
@@ -438,14 +439,21 @@ __global__ void __launch_bounds__(kBigThreads)
   double2* A = V + (int64_t)blockIdx.x * n * n;
   const BigWork w(work + (int64_t)blockIdx.x * wstride, n);
 
-  double big = 0.0;
+  // a matrix that is not Hermitian to 1e-14 of its norm is left to the Jacobi
+  // kernels, which do not converge on it
+  double big = 0.0, tot = 0.0, skew = 0.0;
   if (own)
     for (int r = g; r < n; r += G) {
-      const double2 x = h[(int64_t)r * n + c];
+      const double2 x = h[(int64_t)r * n + c], y = h[(int64_t)c * n + r];
       big = fmax(big, fmax(fabs(x.x), r == c ? 0.0 : fabs(x.y)));
+      tot += x.x * x.x + x.y * x.y;
+      skew += 0.25 * ((x.x - y.x) * (x.x - y.x) + (x.y + y.y) * (x.y + y.y));
     }
+  tot = block_sum(tot, red[0]);
+  __syncthreads();
+  skew = block_sum(skew, red[1]);
   big = group_max<64>(big);
-  if ((tid & 63) == 0) red[0][tid >> 6] = big;
+  if ((tid & 63) == 0) red[0][tid >> 6] = big;   // tot has been read
   __syncthreads();
   for (int i = 0; i < kBigThreads / 64; ++i) big = fmax(big, red[0][i]);
   const int ex = scale_exponent(big);
@@ -453,7 +461,7 @@ __global__ void __launch_bounds__(kBigThreads)
   if (tid == 0) {
     w.state[0] = ex;
     w.state[1] = 0;
-    w.state[3] = 0;
+    w.state[3] = skew > 1e-28 * tot ? 1 : 0;
   }
   if (own)
     for (int r = g; r < n; r += G) {
@@ -761,7 +769,7 @@ __global__ void __launch_bounds__(256)
   }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) place += __shfl_xor(place, off, 64);
-  if (-group_max<64>(-gap) <= kCloseGap * group_max<64>(top)) w.state[3] = 1;   // (of all columns, the same value)
+  if (-group_max<64>(-gap) <= kCloseGap * group_max<64>(top)) w.state[3] = 1;
   if (!__all(order)) place = j;                  // NaN eigenvalues (a matrix that is not finite) would share places
   if (lane == 0) eps[b * n + place] = ldexp(mine, w.state[0]);
 #pragma unroll
