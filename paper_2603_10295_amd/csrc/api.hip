@@ -823,7 +823,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
       // Jacobi: FP32 outputs stop the k+q sweeps at an off-diagonal norm of 1e-10 of the
       // total (eigenvalues then exact to ~1e-20 relative, eigenvectors to ~1e-10,
       // far below the complex64 rounding they are cast to); FP64 at 1e-14
-      if (r.any_rounding && tridiag_better(nw, (nq < qb ? nq : qb) * nk))   // for all batches of the call
+      if (r.any_rounding && tridiag_better(nw))
         EPHW_TRY(tridiag_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, s->ctx->status, st));
       else
         EPHW_TRY(jacobi_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, s->ctx->max_sweeps,

@@ -34,7 +34,7 @@ ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* 
 // rounding over the gaps, in degenerate blocks within a unitary mixing.  H is
 // overwritten.  The sweep limit bounds the QL steps per eigenvalue.
 // tridiag_better: the rule for taking it.
-bool tridiag_better(int n, int64_t batch);
+bool tridiag_better(int n);
 ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s);
 // Orders 33 to 256 (and jacobi_eigh's workspace): matrices with eigenvalues
 // closer than 1e-6 of the largest are solved by jacobi_eigh's kernels, so that

@@ -846,15 +846,16 @@ ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint
 
 }  // namespace
 
+// By the order alone: states of degenerate bands are the solver's own choice, and
+// must not depend on how the points are divided over calls, q batches or ranks.
 // Up to order 6 the two are level (n = 3: 82 us by Jacobi and 99 here at 131 072
-// matrices, n = 6: 280 and 261).  From 7 to 16 a call that leaves the chip idle
-// is Jacobi's, whose rounds are the shorter chain: n = 8, 4096 matrices 54 and
-// 52 us; n = 11, 1024: 81 and 78, 4096: 104 and 82; n = 16, 1024: 117 and 138,
-// 4096: 290 and 149; n^3 x matrices is near 4 million where they meet.  From 17
-// to 32 this one is ahead at every count (n = 24: 449 and 259 us at 64 matrices).
-bool tridiag_better(int n, int64_t batch) {
-  return n > 16 ? n <= 32 : n > 6 && (int64_t)n * n * n * batch >= 4000000;
-}
+// matrices, n = 6: 280 and 261).  From 7 on this one is ahead where there are
+// thousands of matrices (4096 of n = 8: 54 and 50 us, n = 11: 108 and 77, n = 16:
+// 291 and 142, n = 24: 1731 and 369); 64 matrices are level up to order 12 (n = 11:
+// 77 and 73), up to 30 us behind from 13 to 17 (n = 14: 93 and 115, n = 17: 126
+// and 158), where the Jacobi rounds are the shorter chain, and ahead again at 24
+// (457 and 266).
+bool tridiag_better(int n) { return n > 6 && n <= 32; }
 
 ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s) {
   if (batch <= 0) return EPHW_OK;
