@@ -785,8 +785,9 @@ using Small = SmallTable<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16>;
 // a sweep of rounds on A and logs their parameters, and the rows of V, each
 // independent of the others, replay the log of the sweep before on as many
 // wavefronts as there are rows to share out, in LDS, on the CUs the first
-// workgroups leave idle.  One launch per sweep holds both (two logs in turn),
-// up to the sweep limit; after convergence the launches return at once.
+// workgroups leave idle.  One launch per sweep holds both (two logs in turn);
+// after convergence the launches return at once.  Sweeps past kLargeSweeps (eight
+// to twelve are usual) follow each other in one last launch, whatever the limit.
 //
 // Per round J_i^H A J_j touches only the 2x2 block (pair i, pair j), so a
 // thread loads a block's four elements, applies the column and then the row
@@ -801,6 +802,7 @@ using Small = SmallTable<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16>;
 // ---------------------------------------------------------------------------
 constexpr int kLargeThreads = 1024;
 constexpr int kReplayRows = 2;      // rows of V per wavefront
+constexpr int kLargeSweeps = 16;    // launches of one sweep each
 
 struct LargeRot {
   double c, s, er, ei;
@@ -992,6 +994,22 @@ __global__ void __launch_bounds__(kLargeThreads)
     jacobi_replay(V, n, log, state, sweep - 1, (b - nb) / parts, (b - nb) % parts, replay_rows);
 }
 
+// Sweep number `last` is on A and in the log: its replay, then sweep after sweep
+// until the matrix has converged or the limit is reached, a workgroup per matrix.
+__global__ void __launch_bounds__(kLargeThreads)
+    jacobi_tail_kernel(double2* H, double2* V, int n, int parts, LargeRot* log, int* state, const uint32_t* status,
+                       int last) {
+  extern __shared__ double2 replay_rows[];
+  const int b = blockIdx.x, limit = sweep_limit(status);
+  for (int sweep = last;; ++sweep) {
+    for (int part = 0; part < parts; ++part) jacobi_replay(V, n, log, state, sweep, b, part, replay_rows);
+    __syncthreads();
+    if (state[3 * b] != 0 || sweep + 1 >= limit) return;   // the same for every thread
+    jacobi_sweep(H, n, log, state, status, sweep + 1, b, false);
+    __syncthreads();
+  }
+}
+
 // Sort ascending, fix each column's phase: eps from the diagonal of A, the
 // columns of V permuted and scaled in place, a row at a time.
 __global__ void __launch_bounds__(kLargeThreads)
@@ -1047,12 +1065,19 @@ ephw_status launch_large(double2* h, int64_t nb, int n, double* eps, double2* v,
   const size_t lds = (size_t)(kLargeThreads / 64) * kReplayRows * n * sizeof(double2);
   const int parts = (int)ceil_div(n, (kLargeThreads / 64) * kReplayRows);
   EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_sweep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_tail_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   LargeRot* log = reinterpret_cast<LargeRot*>(work);
   int* state = jacobi_large_state(work, n, nb);
-  for (int sweep = 0; sweep <= (max_sweeps > 0 ? max_sweeps : 1); ++sweep) {
+  const int last = max_sweeps < 1 ? 1 : max_sweeps < kLargeSweeps ? max_sweeps : kLargeSweeps;
+  for (int sweep = 0; sweep <= last; ++sweep) {
     const int64_t grid = nb + (sweep > 0 ? nb * parts : 0);
     hipLaunchKernelGGL(jacobi_sweep_kernel, dim3((unsigned)grid), dim3(kLargeThreads), lds, s, h, v, n, (int)nb, parts,
                        log, state, status, sweep, some);
+    EPHW_CHECK_LAUNCH();
+  }
+  if (max_sweeps > last) {
+    hipLaunchKernelGGL(jacobi_tail_kernel, dim3((unsigned)nb), dim3(kLargeThreads), lds, s, h, v, n, parts, log, state,
+                       status, last);
     EPHW_CHECK_LAUNCH();
   }
   hipLaunchKernelGGL(jacobi_finish_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, eps, v, state, status,

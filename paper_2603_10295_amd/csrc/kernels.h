@@ -18,7 +18,7 @@ int64_t jacobi_work_doubles(int n, int64_t batch);
 // off_tol2: convergence when (off-diagonal norm / total norm)^2 <= off_tol2
 // (not below 1e-28, the FP64 default; n <= 32 only, larger orders keep 1e-28)
 // H is overwritten where n > 32.  max_sweeps: the sweep limit the status words
-// hold, from which the host counts the launches of the large solves.
+// hold; where it is small it bounds the launches of the large solves.
 ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
                         int max_sweeps, hipStream_t s, double off_tol2 = 1e-28);
 
