@@ -837,10 +837,12 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
   EPHW_TRY(ws_need(s, WS_LOSS, (size_t)kt * qb * rot_tiles * 8));
   EPHW_TRY(ws_need(s, WS_UBAR, (size_t)qb * nm * nm * cs));
   const int chunks_u = splitk_chunks(nw2, 16, 256);
-  // Re per launch of the ubar products: all of them within 512 MB of partials
+  // partials of the ubar products, in the T buffer (free after the k loop) for as
+  // many Re per launch as it holds; one Re at a time where it holds none
   const int64_t ubar_each = qb * chunks_u * nm * nm * (int64_t)cs;
-  const int64_t ubar_group = std::max<int64_t>(1, std::min<int64_t>(ne, ((int64_t)512 << 20) / ubar_each));
-  EPHW_TRY(ws_need(s, WS_SPLIT, (size_t)(ubar_group * ubar_each)));
+  const int64_t ubar_group = std::max<int64_t>(1, std::min<int64_t>(ne, (int64_t)wsz / ubar_each));
+  const bool ubar_in_t = ubar_each <= (int64_t)wsz;
+  if (!ubar_in_t) EPHW_TRY(ws_need(s, WS_SPLIT, (size_t)ubar_each));
   // the per-pair Vbar GEMMs (Nw x Nw outputs, K = Nm Nw) split K until a unit
   // has about 1024 tiles
   const int64_t pair_out_tiles = cgemm_tiles(kind, nw, nw);
@@ -855,6 +857,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
   char* Gnubar = static_cast<char*>(wsp(s, WS_GNUBAR));
   char* W = static_cast<char*>(wsp(s, WS_W));
   char* Tm = static_cast<char*>(wsp(s, WS_T));
+  char* ubar_part = ubar_in_t ? Tm : static_cast<char*>(wsp(s, WS_SPLIT));
   char* Yb = static_cast<char*>(wsp(s, WS_YBAR));
   char* Z = static_cast<char*>(wsp(s, WS_Z));
   char* Wb = static_cast<char*>(wsp(s, WS_WBAR));
@@ -1085,7 +1088,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
       ub.strideB = E;
       ub.strideB1 = nb * E;
       ub.strideB2 = ub.K;
-      ub.C = wsp(s, WS_SPLIT);
+      ub.C = ubar_part;
       ub.ldc = nm;
       ub.strideC = eg * chunks_u * nm * nm;
       ub.strideC1 = chunks_u * nm * nm;
@@ -1094,11 +1097,11 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
       const int64_t total = nb * nm * nm;
       if (kind == 0)
         hipLaunchKernelGGL(ubar_reduce_kernel<double>, dim3(grid1(total, 256)), dim3(256), 0, st,
-                           static_cast<const double*>(wsp(s, WS_SPLIT)), nb, eg, chunks_u, nm * nm,
+                           reinterpret_cast<const double*>(ubar_part), nb, eg, chunks_u, nm * nm,
                            reinterpret_cast<double*>(ubar), e0 > 0 ? 1 : 0);
       else
         hipLaunchKernelGGL(ubar_reduce_kernel<float>, dim3(grid1(total, 256)), dim3(256), 0, st,
-                           static_cast<const float*>(wsp(s, WS_SPLIT)), nb, eg, chunks_u, nm * nm,
+                           reinterpret_cast<const float*>(ubar_part), nb, eg, chunks_u, nm * nm,
                            reinterpret_cast<float*>(ubar), e0 > 0 ? 1 : 0);
       EPHW_CHECK_LAUNCH();
     }
