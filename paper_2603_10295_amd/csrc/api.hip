@@ -572,7 +572,7 @@ ephw_status ephw_kset_create(ephw_system* s, const double* k, int64_t nk, int32_
     if ((e = phase_matrix(0, ks->k, nk, s->r_h, s->w_h, s->nh, ks->pkh, st)) != EPHW_OK)
       return fail(e);
   }
-  if (kind == 1 && nk >= kPackMinPoints && s->nw <= 32 && s->pack_scale > 0.f && cgemm_packable(nk, 128, s->ne) &&
+  if (prec == EPHW_FP32 && nk >= kPackMinPoints && s->nw <= 32 && s->pack_scale > 0.f && cgemm_packable(nk, 128, s->ne) &&
       alloc(&ks->pkp, (size_t)packed_bytes(nk, s->ne)) == EPHW_OK) {   // without memory for it: the set works unpacked
     Stage sg_(s, EPHW_STAGE_PHASE, st);
     if ((e = pack_phases(ks->k, nk, s->r_e, s->w_e, s->ne, s->pack_scale, ks->pkp, st)) != EPHW_OK) return fail(e);

@@ -68,3 +68,18 @@ def test_partials_one_re_at_a_time():
     ks.close()
     h.close()
     ctx.close()
+
+
+def test_compensated_sets_hold_one_copy_of_their_phases():
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(4, 1, synth.box((9, 9, 9)), synth.box((1, 1, 1)), [4, 44], g_dtype=np.complex64)
+    ctx, h = open_system(s)
+    k = dev(np.random.default_rng(1).random((600, 3)))
+    ks = ephw.KSet(h, k, ephw.FP32_COMP)
+    held = ctx.memory()[0]
+    ks.close()
+    held -= ctx.memory()[0]
+    assert held <= 600 * (24 + s.ne * 8 + len(s.r_h) * 16 + 4 * 8 + 16 * 24) + 6 * 256
+    h.close()
+    ctx.close()
