@@ -572,16 +572,18 @@ ephw_status ephw_kset_create(ephw_system* s, const double* k, int64_t nk, int32_
     if ((e = phase_matrix(0, ks->k, nk, s->r_h, s->w_h, s->nh, ks->pkh, st)) != EPHW_OK)
       return fail(e);
   }
-  if (prec == EPHW_FP32 && nk >= kPackMinPoints && s->nw <= 32 && s->pack_scale > 0.f && cgemm_packable(nk, 128, s->ne) &&
-      alloc(&ks->pkp, (size_t)packed_bytes(nk, s->ne)) == EPHW_OK) {   // without memory for it: the set works unpacked
-    Stage sg_(s, EPHW_STAGE_PHASE, st);
-    if ((e = pack_phases(ks->k, nk, s->r_e, s->w_e, s->ne, s->pack_scale, ks->pkp, st)) != EPHW_OK) return fail(e);
-  }
   if ((e = interp_eigh(s, ks->pkh, nk, s->nh, s->h_r, s->nw, ks->eps, ks->v64, st)) != EPHW_OK)
     return fail(e);
   {
     Stage sg_(s, EPHW_STAGE_OTHER, st);
     if ((e = cast_complex(kind, ks->v64, ks->vt, nk * nw2, st)) != EPHW_OK) return fail(e);
+  }
+  // a packed copy of the phases for the calls that take one, last and only
+  // without a memory cap: a call packs them itself where the set holds none
+  if (prec == EPHW_FP32 && nk >= kPackMinPoints && s->nw <= 32 && s->pack_scale > 0.f && s->mem->limit == 0 &&
+      cgemm_packable(nk, 128, s->ne) && alloc(&ks->pkp, (size_t)packed_bytes(nk, s->ne)) == EPHW_OK) {
+    Stage sg_(s, EPHW_STAGE_PHASE, st);
+    if ((e = pack_phases(ks->k, nk, s->r_e, s->w_e, s->ne, s->pack_scale, ks->pkp, st)) != EPHW_OK) return fail(e);
   }
   *out = ks;
   return EPHW_OK;
@@ -620,6 +622,7 @@ struct InterpWs {
   void *pq = nullptr, *u = nullptr, *g = nullptr, *gnu = nullptr, *w = nullptr, *vkq = nullptr;
   double *lam = nullptr, *e = nullptr, *pqc = nullptr, *hk = nullptr, *jwork = nullptr, *pqh = nullptr;
   double *bq = nullptr, *hkq = nullptr, *ekq = nullptr, *vkq64 = nullptr, *loss = nullptr;
+  void* pkp = nullptr;                             // packed phases of the set, where it holds none
   void* gchunk = nullptr;                          // rotated g of a batch for the linewidth (unfused)
   double *om = nullptr, *lwp = nullptr;            // omega [nq][nm]; fused linewidth partials
   size_t bytes = 0;
@@ -633,6 +636,7 @@ struct InterpReq {
   bool need_g = false, need_kq_eig = false;
   bool any_rounding = false; // of the phase sums (see GemmParams)
   bool packed = false;       // the Re sum on packed operands
+  bool phases = false;       // its phases packed by the call (the set holds none)
   bool fused = false;        // band rotations in the Re-sum GEMM's epilogue (no W buffer)
   bool lw = false;           // linewidth reduction of the rotated g (no g output)
   LwParams lwp;              // its kernel parameters, from the arguments below
@@ -647,19 +651,29 @@ struct InterpReq {
 bool interp_fusable(const ephw_system* s, const InterpReq& r) {
   if (r.prec != EPHW_FP32 || (r.flags & EPHW_OUT_WANNIER) || !r.need_g) return false;
   const int64_t E = (int64_t)s->nm * s->nw * s->nw, tail = r.nq % r.qb;
-  // behind the faster product of free rounding the epilogues on VALU are most
-  // of the kernel (Nw = 4, K = 250: 1070 us fused, 540 us with W stored and
-  // the rotations in a pass of their own)
-  if (r.any_rounding && s->ne >= kSplitMinK && !(s->nw == 8 && s->nm % 2 == 0)) return false;
   return cgemm_band_fusable(1, r.nk, r.qb * E, s->nw, s->ne, r.qb * E) &&
          (tail == 0 || cgemm_band_fusable(1, r.nk, tail * E, s->nw, s->ne, tail * E));
 }
 
-// Whether the call's Re sums run on packed operands: the set has its packed
-// phases and both the full and the last batch fit.
-bool interp_packable(const ephw_system* s, const ephw_kset* ks, const InterpReq& r) {
+// The epilogue that runs behind products of free rounding (the others run
+// behind the FP32 instructions).
+bool fuses_behind_any(const ephw_system* s) { return s->nw == 8 && s->nm % 2 == 0; }
+
+// The forms of a call's Re sums, and the buffers they need beside each other:
+//   kFast      packed operands; W stored and rotated in a pass of its own where
+//              the fused epilogue would run on VALU, which is most of the kernel
+//              behind the faster product (Nw = 4, K = 250: 1070 us fused, 540 so)
+//   kUnpacked  the same without the packed operands
+//   kPlain     W stored only where no epilogue takes it: the least memory
+enum InterpForm { kFast, kUnpacked, kPlain };
+
+void interp_form(const ephw_system* s, const ephw_kset* ks, InterpForm form, InterpReq* r) {
   const int64_t E = (int64_t)s->nm * s->nw * s->nw;
-  return r.any_rounding && r.need_g && ks->pkp && r.prec == EPHW_FP32 && cgemm_packable(r.nk, r.qb * E, s->ne);
+  r->fused = interp_fusable(s, *r) &&
+             (form == kPlain || !r->any_rounding || s->ne < kSplitMinK || fuses_behind_any(s));
+  r->packed = form == kFast && r->any_rounding && r->need_g && r->prec == EPHW_FP32 && r->nk >= kPackMinPoints &&
+              s->pack_scale > 0.f && cgemm_packable(r->nk, r->qb * E, s->ne);
+  r->phases = r->packed && !ks->pkp;
 }
 
 InterpWs interp_layout(const ephw_system* s, const InterpReq& r, char* base) {
@@ -689,6 +703,7 @@ InterpWs interp_layout(const ephw_system* s, const InterpReq& r, char* base) {
     const size_t gb = (size_t)qb * s->ne * E * cs;
     const size_t pb = r.packed ? (size_t)packed_bytes(qb * E, s->ne) + (size_t)qb * E * 4 : 0;
     w.g = take(gb > pb ? gb : pb);
+    if (r.phases) w.pkp = take((size_t)packed_bytes(nk, s->ne));
     w.gnu = take((size_t)qb * s->ne * E * cs);
     if (!r.fused) w.w = take((size_t)nk * qb * E * cs);
   }
@@ -796,6 +811,10 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     Stage sg_(s, EPHW_STAGE_PHASE, st, stages);
     EPHW_TRY(phase_matrix(0, q, nq, s->r_h, nullptr, s->nh, w.pqh, st));
   }
+  if (r.phases) {
+    Stage sg_(s, EPHW_STAGE_PHASE, st, stages);
+    EPHW_TRY(pack_phases(ks->k, nk, s->r_e, s->w_e, s->ne, s->pack_scale, w.pkp, st));
+  }
 
   for (int64_t q0 = 0; q0 < nq; q0 += qb) {
     const int32_t nb = (int32_t)((nq - q0) < qb ? (nq - q0) : qb);
@@ -868,7 +887,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     re.K = s->ne;
     re.A = ks->pk;
     re.compensated = comp;
-    re.any_rounding = r.any_rounding;
+    re.any_rounding = r.any_rounding && (!r.fused || fuses_behind_any(s));
     if (r.packed) {
       float* inv = reinterpret_cast<float*>(static_cast<char*>(w.g) + packed_bytes(re.N, re.K));
       {
@@ -876,7 +895,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
         EPHW_TRY(pack_columns(w.gnu, re.K, re.N, re.N, w.g, inv, st));
       }
       re.packed.on = true;
-      re.packed.A = ks->pkp;
+      re.packed.A = r.phases ? w.pkp : ks->pkp;
       re.packed.lda = packed_ld(nk);
       re.packed.inv_a = 1.f / s->pack_scale;
       re.packed.B = w.g;
@@ -965,6 +984,31 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
   return EPHW_OK;
 }
 
+// The form and q batch of a call and its workspace.  Under a memory cap the
+// faster forms may take what the plain form would (by a smaller batch, down to
+// half) or the workspace already has, never more: whatever fits beside a plain
+// call still fits.  Without a cap the plain form is the second try.
+ephw_status interp_reserve(ephw_kset* ks, InterpReq* r) {
+  ephw_system* s = ks->sys;
+  const int32_t qb = pick_q_batch(s, ks->nk, r->nq, prec_kind(r->prec));
+  auto bytes = [&](InterpForm form, int32_t batch) {
+    r->qb = batch;
+    interp_form(s, ks, form, r);
+    return interp_layout(s, *r, nullptr).bytes;
+  };
+  const size_t plain = bytes(kPlain, qb);
+  if (s->mem->limit > 0) {
+    const size_t room = std::max(plain, s->ws[WS_ARENA].bytes);
+    for (InterpForm form : {kFast, kUnpacked})
+      for (int32_t b = qb; b >= (qb + 1) / 2; --b)
+        if (bytes(form, b) <= room) return ws_need(s, WS_ARENA, interp_layout(s, *r, nullptr).bytes);
+  } else {
+    const ephw_status e = ws_need(s, WS_ARENA, bytes(kFast, qb));
+    if (e != EPHW_ENOMEM) return e;
+  }
+  return ws_need(s, WS_ARENA, bytes(kPlain, qb));
+}
+
 // Device address of `scratch` on the current device, looked up once per device.
 ephw_status scratch_address(int device, char** out) {
   static std::mutex mu;
@@ -1003,11 +1047,7 @@ ephw_status ephw_interpolate(ephw_kset* ks, const double* q, int64_t nq, const i
   if (s->nw > 32)
     return interpolate_large(ks, q, nq, kq_index, q_offset, flags, g_out, band_sum, loss, loss_seed, eps_kq, omega,
                              as_stream(stream));
-  r.qb = pick_q_batch(s, ks->nk, nq, prec_kind(prec));
-  r.fused = interp_fusable(s, r);
-  r.packed = interp_packable(s, ks, r);
-  const size_t need = interp_layout(s, r, nullptr).bytes;
-  EPHW_TRY(ws_need(s, WS_ARENA, need));
+  EPHW_TRY(interp_reserve(ks, &r));
   const InterpWs w = interp_layout(s, r, static_cast<char*>(wsp(s, WS_ARENA)));
   return interpolate_small(ks, q, kq_index, q_offset, r, g_out, band_sum, loss, loss_seed, eps_kq, omega, w, true,
                            as_stream(stream));
@@ -1044,7 +1084,7 @@ ephw_status ephw_interpolate_linewidth(ephw_kset* ks, const double* q, int64_t n
   r.nq_total = nq_total;
   r.gamma = gamma;
   r.qb = pick_q_batch(s, ks->nk, nq, prec_kind(ks->prec));
-  r.fused = interp_fusable(s, r);
+  interp_form(s, ks, kPlain, &r);
   const size_t need = interp_layout(s, r, nullptr).bytes;
   EPHW_TRY(ws_need(s, WS_ARENA, need));
   const InterpWs w = interp_layout(s, r, static_cast<char*>(wsp(s, WS_ARENA)));
@@ -1066,23 +1106,19 @@ ephw_status ephw_interpolate_noalloc(ephw_kset* ks, const double* q, int64_t nq,
   }
   // the largest q batch (up to the one ephw_interpolate would take) whose
   // buffers fit the scratch; the per-call buffers grow with nq, not with it
-  int32_t qb = pick_q_batch(s, ks->nk, nq, prec_kind(prec));
-  for (;;) {
-    r.qb = qb;
-    r.fused = interp_fusable(s, r);
-    r.packed = interp_packable(s, ks, r);
-    if (interp_layout(s, r, nullptr).bytes <= kScratchBytes) break;
-    if (qb == 1 && r.packed) {   // the packed operand's padding alone may pass the scratch
-      r.packed = false;
-      if (interp_layout(s, r, nullptr).bytes <= kScratchBytes) break;
+  const int32_t qb = pick_q_batch(s, ks->nk, nq, prec_kind(prec));
+  auto fits = [&](InterpForm form) {
+    for (r.qb = qb;; r.qb = r.qb / 2) {
+      interp_form(s, ks, form, &r);
+      if (interp_layout(s, r, nullptr).bytes <= kScratchBytes) return true;
+      if (r.qb == 1) return false;
     }
-    if (qb == 1) {
-      set_error("ephw_interpolate_noalloc: the call needs " + std::to_string(interp_layout(s, r, nullptr).bytes) +
-                " bytes of scratch at one q per batch, more than the " + std::to_string(kScratchBytes) +
-                " bytes the library holds");
-      return EPHW_ENOMEM;
-    }
-    qb = qb / 2 > 0 ? qb / 2 : 1;
+  };
+  if (!fits(kFast) && !fits(kUnpacked) && !fits(kPlain)) {
+    set_error("ephw_interpolate_noalloc: the call needs " + std::to_string(interp_layout(s, r, nullptr).bytes) +
+              " bytes of scratch at one q per batch, more than the " + std::to_string(kScratchBytes) +
+              " bytes the library holds");
+    return EPHW_ENOMEM;
   }
   char* base = nullptr;
   EPHW_TRY(scratch_address(s->ctx->device, &base));

@@ -184,7 +184,7 @@ struct ephw_kset {
   void* block = nullptr;    // holds k, pk, pkh, eps, v64 and vt
   double* k = nullptr;      // [nk][3]
   void* pk = nullptr;       // T [nk][ne]
-  void* pkp = nullptr;      // packed copy of pk (FP32 sets of kPackMinPoints points or more), or NULL
+  void* pkp = nullptr;      // packed copy of pk (some FP32 sets of kPackMinPoints points or more), or NULL
   double* pkh = nullptr;    // c128 [nk][nh]
   double* eps = nullptr;    // [nk][nw]
   double* v64 = nullptr;    // c128 [nk][nw][nw]

@@ -70,6 +70,77 @@ def test_partials_one_re_at_a_time():
     ctx.close()
 
 
+@pytest.mark.parametrize("nw,na,nk", [(4, 4, 180000), (8, 1, 180000), (4, 4, 60000), (8, 2, 60000)])
+def test_noalloc_where_the_stored_sums_pass_the_scratch(nw, na, nk):
+    """g alone in FP32: one q's unrotated sums are 276 MB where W would be stored
+    (180 000 points), and 92 or 184 MB beside 31 MB of packed phases."""
+    import torch
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(nw, na, synth.box((4, 4, 4)), synth.box((2, 1, 1)), [nw, 42], g_dtype=np.complex64)
+    ctx, h = open_system(s)
+    k = dev(np.random.default_rng(nk).random((nk, 3)))
+    q = dev(np.zeros((2, 3)) + 0.25)
+    kqi = torch.arange(nk, dtype=torch.int32, device="cuda:0").flip(0).expand(2, nk).contiguous()
+    ks = ephw.KSet(h, k, ephw.FP32)
+    a, b = (torch.empty((2, nk, s.nm, nw, nw), dtype=torch.complex64, device="cuda:0") for _ in range(2))
+    ephw.interpolate_noalloc(ks, q, kq_index=kqi, g_out=a)
+    ephw.interpolate(ks, q, kq_index=kqi, g_out=b)
+    ctx.check()
+    assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max())
+    ks.close()
+    h.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("nw,na,nk,nq,cap", [
+    (8, 2, 700, 6, "call"),      # packed, 65 Re padded to 80
+    (8, 2, 700, 40, "call"),
+    (4, 2, 700, 6, "call"),      # W stored
+    (8, 1, 300, 6, "call"),
+    (8, 2, 700, 40, "before"),   # the cap is there when the set is made
+    (4, 2, 700, 40, "before"),
+    (5, 2, 700, 40, "before"),   # W is stored in every form
+])
+def test_interpolate_within_the_plain_forms_memory(nw, na, nk, nq, cap):
+    """g alone in FP32 within what the plain forms of its sums take: g(Re,q)
+    twice, and W only where no epilogue rotates it."""
+    import torch
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(nw, na, synth.box((13, 5, 1)), synth.box((2, 1, 1)), [nw, 43], g_dtype=np.complex64)
+    k, q = (dev(np.random.default_rng(n).random((n, 3))) for n in (nk, nq))
+    kqi = torch.zeros((nq, nk), dtype=torch.int32, device="cuda:0")
+    E, fused = s.nm * nw * nw, nw in (4, 8)
+    plain = 2 * nq * s.ne * E * 8 + (0 if fused else nk * nq * E * 8)
+    # q-side arrays (phases, D(q), its modes) and the rounding up of every array
+    small = nq * (s.np_ * 8 + len(s.r_c) * 16 + s.nm * 8 + s.nm ** 2 * (16 + 16 + 8)) + 16 * 256
+    kset = nk * (24 + s.ne * 8 + len(s.r_h) * 16 + nw * 8 + nw * nw * (16 + 8)) + 6 * 256
+    out = torch.empty((3, nq, nk, s.nm, nw, nw), dtype=torch.complex64, device="cuda:0")
+    ctx, h = open_system(s)
+    base = ctx.memory()[0]
+    eig = nk * nw * nw * 16                        # H(k) of the set's bands
+    if cap == "before":
+        ctx.set_limits(max_device_bytes=base + kset + eig + plain + small)
+    ks = ephw.KSet(h, k, ephw.FP32)
+    if cap == "call":
+        ephw.interpolate(ks, q, kq_index=kqi, g_out=out[0])
+        h.trim()
+        ctx.set_limits(max_device_bytes=ctx.memory()[0] + plain + small)
+    for i in (1, 2):                               # the second call finds the first one's workspace
+        ephw.interpolate(ks, q, kq_index=kqi, g_out=out[i])
+    ctx.check()
+    ctx.set_limits()
+    h.trim()
+    ephw.interpolate(ks, q, kq_index=kqi, g_out=out[0])
+    ctx.check()
+    top = float(out[0].abs().max())
+    assert float((out[1] - out[0]).abs().max()) <= 1e-5 * top and torch.equal(out[1], out[2])
+    ks.close()
+    h.close()
+    ctx.close()
+
+
 def test_compensated_sets_hold_one_copy_of_their_phases():
     from gpu_run import dev
     from paper_2603_10295_amd import ephw
