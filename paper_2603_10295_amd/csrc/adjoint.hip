@@ -472,17 +472,17 @@ namespace {
 // The k tile is the M of the Re GEMM (for small Ne a short-K, store-bound
 // GEMM whose 128-row tiles want many k) and every k tile re-reads g(Re,q);
 // a larger q batch at the same pair budget would shorten the k tile, which
-// measured slower on the ribbon than the Eq. (9) GEMM it speeds up.
-void unit_shape(const ephw_system* s, int64_t nq, int64_t nk, int64_t E, size_t cs, int nbuf, bool forward,
+// measured slower on the ribbon than the Eq. (9) GEMM it speeds up.  wide: the
+// forward's two g(Re,q)-sized buffers may take 20 GB.
+void unit_shape(const ephw_system* s, int64_t nq, int64_t nk, int64_t E, size_t cs, int nbuf, bool wide,
                 int64_t* qb_out, int64_t* kt_out) {
   int64_t qb = s->q_batch;
   if (qb <= 0) {
     qb = (int64_t)(8.0e9 / (4.0 * (double)s->ne * E * cs));
     qb = std::max<int64_t>(1, std::min<int64_t>(qb, 8));
-    // the forward's two buffers may take 20 GB, one read of g(Re,Rp) for 8 q,
-    // while every k point still fits the pair budget
+    // one read of g(Re,Rp) for 8 q, while every k point still fits the pair budget
     const int64_t qw = std::min<int64_t>(8, (int64_t)(20.0e9 / (2.0 * (double)s->ne * E * cs)));
-    if (forward && qw > qb && (double)nbuf * cs * std::min(qw, nq) * E * nk <= 48.0e9) qb = qw;
+    if (wide && qw > qb && (double)nbuf * cs * std::min(qw, nq) * E * nk <= 48.0e9) qb = qw;
   }
   qb = std::min(qb, nq);
   int64_t kt = (int64_t)(48.0e9 / ((double)nbuf * cs * qb * E));
@@ -535,8 +535,25 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
   const int kind = prec_kind(ks->prec);
   const size_t cs = csize(kind);
   const int64_t nw = s->nw, nm = s->nm, nw2 = nw * nw, E = nm * nw2, nk = ks->nk, ne = s->ne, np = s->np;
-  int64_t qb, kt;
-  unit_shape(s, nq, nk, E, cs, 2, true, &qb, &kt);
+  const bool need_g = (flags & (EPHW_OUT_G | EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) != 0;
+  // the wider batch only without a memory cap, and where there is room for it
+  int64_t qb, kt, qn, kn;
+  unit_shape(s, nq, nk, E, cs, 2, false, &qn, &kn);
+  unit_shape(s, nq, nk, E, cs, 2, s->mem->limit == 0, &qb, &kt);
+  if (need_g && qb > qn) {
+    const size_t gsz = (size_t)qb * ne * E * cs;
+    ephw_status e = ws_need(s, WS_G, gsz);
+    if (e == EPHW_OK) e = ws_need(s, WS_GNU, gsz);
+    if (e == EPHW_OK) e = ws_need(s, WS_W, (size_t)kt * qb * E * cs);
+    if (e == EPHW_OK) e = ws_need(s, WS_T, (size_t)kt * qb * E * cs);
+    if (e == EPHW_ENOMEM) {
+      EPHW_TRY(ephw_system_trim(s));
+      qb = qn;
+      kt = kn;
+    } else if (e != EPHW_OK) {
+      return e;
+    }
+  }
   // see GemmParams
   const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   // q side
@@ -572,7 +589,6 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
   EPHW_TRY(mode_vectors(kind, static_cast<const double*>(wsp(s, WS_E)), nq, (int)nm, s->ism, wsp(s, WS_U), st));
   const bool rot = (flags & (EPHW_OUT_G | EPHW_OUT_LOSS)) != 0;
-  const bool need_g = (flags & (EPHW_OUT_G | EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) != 0;
   const size_t gsz = (size_t)qb * ne * E * cs, wsz = (size_t)kt * qb * E * cs;
   const int64_t rot_tiles = cgemm_tiles(kind, nm * nw, nw);  // per pair
   if (need_g) {

@@ -154,3 +154,32 @@ def test_compensated_sets_hold_one_copy_of_their_phases():
     assert held <= 600 * (24 + s.ne * 8 + len(s.r_h) * 16 + 4 * 8 + 16 * 24) + 6 * 256
     h.close()
     ctx.close()
+
+
+def test_wide_forward_under_a_cap():
+    """40 bands, 30 modes, 1331 Re: g(Re,q) of one q is 511 MB.  Without a cap
+    eight q run at a time, under one the three that fit 8 GB with the gradient's
+    buffers."""
+    import torch
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(40, 10, synth.box((11, 11, 11)), synth.box((1, 1, 1)), [40, 45], g_dtype=np.complex64,
+                          with_g=False)
+    ctx = ephw.Context(0)
+    h = ephw.System(ctx, nw=40, na=10, r_e=s.r_e, r_p=s.r_p, r_h=s.r_h, r_c=s.r_c, h_r=s.h_r, c_r=s.c_r, mass=s.mass,
+                    g=None, g_dtype=ephw.C64)
+    h.set_g(torch.randn((1, 1331, 30, 40, 40), dtype=torch.complex64, device="cuda:0"))
+    k, kqi = synth.uniform_grid((8, 1, 1)), synth.grid_index_of_sum((8, 1, 1))
+    ks = ephw.KSet(h, dev(k), ephw.FP32)
+    out = torch.empty((2, 8, 8, 30, 40, 40), dtype=torch.complex64, device="cuda:0")
+    h.trim()
+    ctx.set_limits(max_device_bytes=ctx.memory()[0] + 2 * 3 * 1331 * 48000 * 8 + (256 << 20))
+    ephw.interpolate(ks, dev(k), kq_index=dev(kqi), g_out=out[0])
+    ctx.check()
+    ctx.set_limits()
+    ephw.interpolate(ks, dev(k), kq_index=dev(kqi), g_out=out[1])
+    ctx.check()
+    assert float((out[1] - out[0]).abs().max()) <= 1e-6 * float(out[1].abs().max())
+    ks.close()
+    h.close()
+    ctx.close()
