@@ -352,8 +352,10 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
   // kPackMinPoints rows repay.  By k the columns are those of every g(Rp) (once
   // per call, or group by group for every chunk where they pass 4 GB) and then
   // those of a chunk's G', each for its own k's pairs; by q those of a batch's
-  // G_nu.  Without memory for them the call runs unpacked.  (1000 k, 1000 Rp of
-  // 384 columns, K = 1000: the Re sums 7.2 + 1.8 ms packed, 14.8 split.)
+  // G_nu.  Without memory for them the call runs unpacked, so also under a memory
+  // cap where they would take more than that does (or the workspace has).  (1000
+  // k, 1000 Rp of 384 columns, K = 1000: the Re sums 7.2 + 1.8 ms packed, 14.8
+  // split.)
   const bool any_rounding = kind == 0 || (flags & (EPHW_OUT_BAND_SUM | EPHW_OUT_LOSS)) == 0;
   const float scale2 = by_k ? s->pack_scale_p : s->pack_scale;
   pl.points = by_k ? nq : ks->nk;
@@ -367,10 +369,14 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
     pl.pack2 = scale2 > 0.f && npairs / pl.na >= kPackMinPoints && npairs >= pl.points &&
                cgemm_grouped_packable(pl.points, chunk * E, pl.depth);
   }
-  ephw_status got = ws_need(s, WS_PAIRSET, pair_layout(s, kind, pl, nullptr).bytes);
-  if (got == EPHW_ENOMEM && (pl.pack1 || pl.pack2)) {
-    pl.pack1 = pl.pack2 = false;
-    got = ws_need(s, WS_PAIRSET, pair_layout(s, kind, pl, nullptr).bytes);
+  PairPlan unpacked = pl;
+  unpacked.pack1 = unpacked.pack2 = false;
+  const size_t plain = pair_layout(s, kind, unpacked, nullptr).bytes, need = pair_layout(s, kind, pl, nullptr).bytes;
+  ephw_status got = EPHW_ENOMEM;
+  if (s->mem->limit == 0 || need <= std::max(plain, s->ws[WS_PAIRSET].bytes)) got = ws_need(s, WS_PAIRSET, need);
+  if (got == EPHW_ENOMEM) {
+    pl = unpacked;
+    got = ws_need(s, WS_PAIRSET, plain);
   }
   EPHW_TRY(got);
   const PairWs w = pair_layout(s, kind, pl, static_cast<char*>(wsp(s, WS_PAIRSET)));

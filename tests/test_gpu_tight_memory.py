@@ -183,3 +183,36 @@ def test_wide_forward_under_a_cap():
     ks.close()
     h.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("order,nk,nq", [("by_k", 560, 20), ("by_k", 560, 700), ("by_q", 700, 5)])
+def test_pairs_under_a_cap_keep_the_plain_workspace(order, nk, nq):
+    """A packed pair list leaves no more behind under a cap than the plain sums
+    (those of a call with band sums), so that the next call finds its room."""
+    import torch
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(4, 1, synth.box((4, 17, 1)), synth.box((13, 5, 1)), [4, 46], g_dtype=np.complex64)
+    ctx, h = open_system(s)
+    ctx.set_limits(max_device_bytes=64 << 30)
+    rng = np.random.default_rng(2)
+    ks = ephw.KSet(h, dev(rng.random((nk, 3))), ephw.FP32)
+    q, n = dev(rng.random((nq, 3))), nk * nq
+    major, minor = (nk, nq) if order == "by_k" else (nq, nk)
+    args = (q, ephw.PAIRS_BY_K if order == "by_k" else ephw.PAIRS_BY_Q, minor * np.arange(major + 1),
+            torch.arange(n, dtype=torch.int32, device="cuda:0") % minor, torch.zeros(n, dtype=torch.int32, device="cuda:0"))
+    g = torch.empty((2, n, 3, 4, 4), dtype=torch.complex64, device="cuda:0")
+    t = torch.empty((n, 3), dtype=torch.float64, device="cuda:0")
+    h.trim()
+    base = ctx.memory()[0]
+    ephw.interpolate_pairs(ks, *args, flags=ephw.OUT_G | ephw.OUT_BAND_SUM, g_out=g[0], band_sum=t)
+    ctx.check()
+    plain = ctx.memory()[0] - base
+    h.trim()
+    ephw.interpolate_pairs(ks, *args, flags=ephw.OUT_G, g_out=g[1])
+    ctx.check()
+    assert ctx.memory()[0] - base <= plain
+    assert float((g[1] - g[0]).abs().max()) <= 1e-5 * float(g[0].abs().max())
+    ks.close()
+    h.close()
+    ctx.close()
