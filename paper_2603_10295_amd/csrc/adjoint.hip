@@ -1248,7 +1248,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
   const size_t gsz = (size_t)qb * ne * E * cs, wsz = (size_t)kt * qb * E * cs;
   EPHW_TRY(ws_need(s, WS_GBAR, gsz));
   EPHW_TRY(ws_need(s, WS_GNUBAR, gsz));
-  EPHW_TRY(ws_need(s, WS_T, wsz));
+  if (!small) EPHW_TRY(ws_need(s, WS_T, wsz));   // the band-rotation kernels keep T' in LDS
   EPHW_TRY(ws_need(s, WS_WBAR, wsz));
   EPHW_TRY(ws_need(s, WS_OFF, (size_t)kt * qb * 8));
   char* Gbar = static_cast<char*>(wsp(s, WS_GBAR));

@@ -216,3 +216,30 @@ def test_pairs_under_a_cap_keep_the_plain_workspace(order, nk, nq):
     ks.close()
     h.close()
     ctx.close()
+
+
+def test_coarse_transform_takes_one_pair_buffer():
+    """Up to 32 bands in one k tile the rotations need the rotated pairs alone,
+    beside g(Re,q) twice and the small arrays."""
+    import torch
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(8, 2, synth.box((8, 8, 8)), synth.box((2, 2, 2)), [8, 47], g_dtype=np.complex64)
+    ctx, h = open_system(s)
+    k = synth.uniform_grid((8, 8, 8))
+    q = synth.uniform_grid((2, 2, 2))
+    n = np.rint(8 * k).astype(int)
+    t = (n[None] + np.rint(8 * q).astype(int)[:, None]) % 8
+    kqi = dev((t[..., 0] * 64 + t[..., 1] * 8 + t[..., 2]).astype(np.int32))
+    ks = ephw.KSet(h, dev(k), ephw.FP32)
+    gb = torch.empty((8, 512, 6, 8, 8), dtype=torch.complex64, device="cuda:0")
+    out = torch.empty(s.g.shape, dtype=torch.complex64, device="cuda:0")
+    h.trim()
+    base = ctx.memory()[0]
+    ephw.wannier_transform(ks, dev(q), kqi, gb.normal_(), out)
+    ctx.check()
+    pairs = 8 * 512 * 384 * 8
+    assert ctx.memory()[0] - base <= 2 * pairs + pairs + 512 * 512 * 8 + 512 * 64 * 8 + (1 << 18)
+    ks.close()
+    h.close()
+    ctx.close()
