@@ -208,7 +208,7 @@ PairWs pair_layout(const ephw_system* s, int kind, const PairPlan& pl, char* bas
   w.probs = reinterpret_cast<GroupProblem*>(take((size_t)pl.na * sizeof(GroupProblem)));
   w.pair_idx = reinterpret_cast<int32_t*>(take((size_t)pl.npairs * 4));
   if (!pl.by_k || pl.pack1) w.qa = reinterpret_cast<double*>(take((size_t)pl.na * 24));
-  w.pq = take((size_t)pl.nqp * s->np * cs);
+  if (!pl.by_k || !pl.pack2) w.pq = take((size_t)pl.nqp * s->np * cs);
   w.pqc = reinterpret_cast<double*>(take((size_t)pl.nqp * s->nc * 16));
   w.lam = reinterpret_cast<double*>(take((size_t)pl.nqp * nm * 8));
   w.e = reinterpret_cast<double*>(take((size_t)pl.nqp * nm * nm * 16));
