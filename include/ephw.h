@@ -25,7 +25,8 @@
  *     u_{kappa alpha, nu}(q) = e_{kappa alpha, nu}(q) / sqrt(M_kappa) (mode
  *     index kappa alpha = 3 kappa + alpha); omega = sqrt(|lambda|).
  *   - Eigenvalues are ascending; each eigenvector column is scaled so that its
- *     largest-magnitude component is real and positive.
+ *     largest-magnitude component is real and positive (above order 32 the first
+ *     of those within 5e-8 of the largest).
  *
  * Memory
  *   - ephw_system_load copies the Wannier-space tensors from HOST memory into
@@ -79,7 +80,8 @@ typedef int32_t ephw_status;
                                which also returns band sums or the loss.  So do
                                its bands at interpolated k+q, solved by
                                tridiagonalisation, and their states also by a
-                               unitary mixing within degenerate blocks */
+                               unitary mixing within degenerate blocks, or a phase
+                               where the largest components are equally large */
 #define EPHW_FP32_COMP   2  /* compensated FP32: as EPHW_FP32, but each phase sum
                                accumulates in K blocks of 32 (fresh FP32 MFMA
                                accumulators per block, block sums added in FP32;

@@ -74,6 +74,12 @@ __host__ __device__ __forceinline__ int ascending_place(At at, int n, int i) {
   return order ? place : i;
 }
 
+// Orders above 32: the component of an eigenvector that is made real positive is
+// the first whose squared magnitude is at least kTied times the largest.  Atoms
+// that a symmetry maps on each other tie, and the last bits, in which the solvers
+// differ, would choose between them.
+constexpr double kTied = 1.0 - 1e-7;
+
 // ---------------------------------------------------------------------------
 // phonon-limited linewidth weights (the downstream reduction of stored or
 // freshly rotated matrix elements): parameters and occupations

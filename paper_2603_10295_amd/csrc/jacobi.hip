@@ -1029,13 +1029,14 @@ __global__ void __launch_bounds__(kLargeThreads)
     const int src = perm[c];
     eo[c] = A[src * n + src].x;
     double best = -1.0, br = 1.0, bi = 0.0;
+    for (int r = 0; r < n; ++r) best = fmax(best, norm2(vb[r * n + src]));
     for (int r = 0; r < n; ++r) {
-      const double vr = vb[r * n + src].x, vi = vb[r * n + src].y;
-      const double m = vr * vr + vi * vi;
-      if (m > best) {
-        best = m;
-        br = vr;
-        bi = vi;
+      const double2 v = vb[r * n + src];
+      if (norm2(v) >= kTied * best) {
+        best = norm2(v);
+        br = v.x;
+        bi = v.y;
+        break;
       }
     }
     const double mag = sqrt(best);

@@ -730,30 +730,29 @@ __global__ void __launch_bounds__(256)
       x[u].y = fma(-y[u].x, s.y, fma(-y[u].y, s.x, x[u].y));
     }
   }
-  // the largest entry (the first of equals)
-  double best = -1.0;
-  int at = 0;
+  // the first entry that is as large as any (see kTied)
+  double best = 0.0;
+#pragma unroll
+  for (int u = 0; u < NX; ++u) best = fmax(best, x[u].x * x[u].x + x[u].y * x[u].y);
+  best = group_max<64>(best);
+  int at = n;
   double2 bv = make_double2(1.0, 0.0);
 #pragma unroll
-  for (int u = 0; u < NX; ++u) {
-    const double m2 = x[u].x * x[u].x + x[u].y * x[u].y;
-    if (lane + 64 * u < n && m2 > best) {
-      best = m2;
+  for (int u = NX - 1; u >= 0; --u)
+    if (lane + 64 * u < n && x[u].x * x[u].x + x[u].y * x[u].y >= kTied * best) {
       at = lane + 64 * u;
       bv = x[u];
     }
-  }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    const double ob = __shfl_xor(best, off, 64), ox = __shfl_xor(bv.x, off, 64), oy = __shfl_xor(bv.y, off, 64);
+    const double ox = __shfl_xor(bv.x, off, 64), oy = __shfl_xor(bv.y, off, 64);
     const int oa = __shfl_xor(at, off, 64);
-    if (ob > best || (ob == best && oa < at)) {
-      best = ob;
+    if (oa < at) {
       at = oa;
       bv = make_double2(ox, oy);
     }
   }
-  const double mag = sqrt(best);
+  const double mag = sqrt(bv.x * bv.x + bv.y * bv.y);
   const double2 fix = mag > 0.0 ? make_double2(bv.x / mag, -bv.y / mag) : make_double2(1.0, 0.0);
   // ascending order (ties by index)
   const double mine = w.d[j];

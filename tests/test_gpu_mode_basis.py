@@ -13,13 +13,19 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-def degenerate_system(nw, na, prec, groups=3):
-    """D(q) = F(q) M with every eigenvalue of M repeated `groups` times"""
+def degenerate_system(nw, na, prec, groups=3, mirror=False):
+    """D(q) = F(q) M with every eigenvalue of M repeated `groups` times, or
+    (mirror) none repeated, but every mode as large on one half of the atoms as on
+    the other"""
     s = synth.make_system(nw, na, synth.box((4, 1, 1)), synth.box((2, 2, 1)), [nw, na],
                           g_dtype=np.complex128 if prec == 0 else np.complex64)
     rng = np.random.default_rng(na)
     qm = np.linalg.qr(rng.standard_normal((s.nm, s.nm)))[0]
-    m = (qm * np.repeat(1.0 + np.arange(-(-s.nm // groups)), groups)[:s.nm]) @ qm.T
+    if mirror:
+        a, b = (x + x.T for x in rng.standard_normal((2, s.nm // 2, s.nm // 2)))
+        m = np.block([[a, b], [b, a]])
+    else:
+        m = (qm * np.repeat(1.0 + np.arange(-(-s.nm // groups)), groups)[:s.nm]) @ qm.T
     paired = (s.r_c[None] == -s.r_c[:, None]).all(-1).any(1)
     f = np.exp(-(s.r_c ** 2).sum(1)) * paired
     return dataclasses.replace(s, c_r=f[:, None, None] * (0.5 * (m + m.T)), mass=np.full(na, 2.0))
@@ -37,7 +43,6 @@ def reference(run, h, s, ks, q, kqi):
     vec = torch.empty((4, s.nw, s.nw), dtype=torch.complex128, device="cuda:0")
     ks.bands(None, vec)
     v, (lam, _, e) = vec.cpu().numpy(), run.phonons(h, q)
-    assert np.abs(np.diff(lam, axis=-1)).min() < 1e-12 * lam.max()
     u = e / np.sqrt(np.repeat(s.mass, 3))[:, None]
     k = np.array([[i / 4, 0, 0] for i in range(4)])
     w = oracle.phases(q, s.r_p) @ s.g.astype(np.complex128).reshape(len(s.r_p), -1)
@@ -73,6 +78,29 @@ def test_modes_are_those_of_phonons(how, prec, nw, na, nq):
     ref = reference(run, h, s, ks, q, kqi)
     # sums of at most 16 terms and rotations of at most nm and nw, a few roundings each
     tol = 1e-12 if prec == 0 else 1e-5
+    assert np.abs(g.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
+    ks.close()
+    h.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("nw,na,nq", [(4, 6, 5), (3, 12, 260), (2, 22, 5), (33, 22, 3)])
+def test_modes_with_equal_components(prec, nw, na, nq):
+    """Modes even or odd under a mirror: no solver's last bits may choose the
+    component that fixes the phase."""
+    import torch
+    from gpu_run import Runner, cplx_dtype, dev
+    from paper_2603_10295_amd import ephw
+    run, s = Runner(), degenerate_system(nw, na, prec, mirror=True)
+    k, q, kqi = grid(nq)
+    h = run.system(s)
+    ks = ephw.KSet(h, dev(k), prec)
+    g = torch.empty((nq, 4, s.nm, nw, nw), dtype=cplx_dtype(prec), device="cuda:0")
+    ephw.interpolate(ks, dev(q), kq_index=dev(kqi), g_out=g)
+    run.ctx.check()
+    ref = reference(run, h, s, ks, q, kqi)
+    # the modes' own error is a rounding over the gaps, here at least 1e-5 of the norm
+    tol = 1e-9 if prec == 0 else 1e-5
     assert np.abs(g.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
     ks.close()
     h.close()
