@@ -581,9 +581,9 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
     double *hk = static_cast<double*>(wsp(s, WS_HK)), *lam = static_cast<double*>(wsp(s, WS_LAM));
     double *e = static_cast<double*>(wsp(s, WS_E)), *work = jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr;
     if (kind != 0 && any_rounding && tridiag_large_better((int)nm, nq))   // see interp_eigh_ws
-      EPHW_TRY(tridiag_large_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, s->ctx->max_sweeps, st));
+      EPHW_TRY(tridiag_large_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, st));
     else
-      EPHW_TRY(jacobi_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, s->ctx->max_sweeps, st));
+      EPHW_TRY(jacobi_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, st));
   }
   if (omega) EPHW_TRY(abs_sqrt(static_cast<const double*>(wsp(s, WS_LAM)), omega, nq * nm, st));
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
@@ -813,7 +813,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
     EPHW_TRY(jacobi_eigh(static_cast<double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
                          static_cast<double*>(wsp(s, WS_E)), jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr,
-                         s->ctx->status, s->ctx->max_sweeps, st));
+                         s->ctx->status, st));
   }
   EPHW_TRY(ws_need(s, WS_U, (size_t)nq * nm * nm * cs));
   EPHW_TRY(mode_vectors(kind, static_cast<const double*>(wsp(s, WS_E)), nq, (int)nm, s->ism, wsp(s, WS_U), st));
@@ -1230,7 +1230,7 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
     EPHW_TRY(jacobi_eigh(static_cast<double*>(wsp(s, WS_HK)), nq, (int)nm, static_cast<double*>(wsp(s, WS_LAM)),
                          static_cast<double*>(wsp(s, WS_E)), jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr,
-                         s->ctx->status, s->ctx->max_sweeps, st));
+                         s->ctx->status, st));
   }
   EPHW_TRY(ws_need(s, WS_UINV, (size_t)nq * nm * nm * cs));
   {

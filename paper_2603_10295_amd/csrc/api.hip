@@ -34,8 +34,8 @@ ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64
   p.ldc = d2;
   EPHW_TRY(cgemm(0, p, st));
   if (c64 && tridiag_large_better(dim, n))
-    return tridiag_large_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, s->ctx->max_sweeps, st);
-  return jacobi_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, s->ctx->max_sweeps, st);
+    return tridiag_large_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, st);
+  return jacobi_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, st);
 }
 
 }  // namespace ephw
@@ -127,7 +127,6 @@ ephw_status ephw_ctx_set_limits(ephw_ctx* ctx, int64_t max_device_bytes, int32_t
   const uint32_t sweeps = (uint32_t)max_sweeps;
   EPHW_HIP(hipMemcpy(ctx->status + 1, &sweeps, sizeof(sweeps), hipMemcpyHostToDevice));
   ctx->mem->limit = max_device_bytes;
-  ctx->max_sweeps = max_sweeps;
   return EPHW_OK;
 }
 
@@ -845,8 +844,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
       if (r.any_rounding && tridiag_better(nw))
         EPHW_TRY(tridiag_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, s->ctx->status, st));
       else
-        EPHW_TRY(jacobi_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, s->ctx->max_sweeps,
-                             st, kind == 0 ? 1e-28 : 1e-20));
+        EPHW_TRY(jacobi_eigh(w.hkq, (int64_t)nb * nk, nw, ekq, w.vkq64, w.jwork, s->ctx->status, st, kind == 0 ? 1e-28 : 1e-20));
       if (kind != 0) EPHW_TRY(cast_complex(kind, w.vkq64, w.vkq, (int64_t)nb * nk * nw2, st));
       ekq_b = ekq;
     } else if ((eps_kq || r.lw) && kq_index) {

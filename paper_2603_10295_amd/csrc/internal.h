@@ -106,7 +106,6 @@ struct ephw_ctx {
   // device words: [0] status bits raised by kernels, [1] sweep limit of the
   // Jacobi eigensolves (read by the kernels at run time)
   uint32_t* status = nullptr;
-  int max_sweeps = kDefaultSweeps;   // the second word, for the host
   // shared with every object made on the context, so that objects freed
   // after the context (in any order) still release their bytes safely
   std::shared_ptr<MemBudget> mem = std::make_shared<MemBudget>();

@@ -787,7 +787,9 @@ using Small = SmallTable<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16>;
 // wavefronts as there are rows to share out, in LDS, on the CUs the first
 // workgroups leave idle.  One launch per sweep holds both (two logs in turn);
 // after convergence the launches return at once.  Sweeps past kLargeSweeps (eight
-// to twelve are usual) follow each other in one last launch, whatever the limit.
+// to twelve are usual) follow each other in one last launch.  The kernels read the
+// limit: the launches of a call, which may be captured in a graph, are the same
+// whatever it is.
 //
 // Per round J_i^H A J_j touches only the 2x2 block (pair i, pair j), so a
 // thread loads a block's four elements, applies the column and then the row
@@ -1062,25 +1064,22 @@ inline int64_t log_doubles(int n) { return (int64_t)4 * 2 * (n + (n & 1) - 1) * 
 
 // nb <= kLargeChunk matrices
 ephw_status launch_large(double2* h, int64_t nb, int n, double* eps, double2* v, double* work, uint32_t* status,
-                         int max_sweeps, bool some, hipStream_t s) {
+                         bool some, hipStream_t s) {
   const size_t lds = (size_t)(kLargeThreads / 64) * kReplayRows * n * sizeof(double2);
   const int parts = (int)ceil_div(n, (kLargeThreads / 64) * kReplayRows);
   EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_sweep_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   EPHW_HIP(hipFuncSetAttribute((const void*)jacobi_tail_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   LargeRot* log = reinterpret_cast<LargeRot*>(work);
   int* state = jacobi_large_state(work, n, nb);
-  const int last = max_sweeps < 1 ? 1 : max_sweeps < kLargeSweeps ? max_sweeps : kLargeSweeps;
-  for (int sweep = 0; sweep <= last; ++sweep) {
+  for (int sweep = 0; sweep <= kLargeSweeps; ++sweep) {
     const int64_t grid = nb + (sweep > 0 ? nb * parts : 0);
     hipLaunchKernelGGL(jacobi_sweep_kernel, dim3((unsigned)grid), dim3(kLargeThreads), lds, s, h, v, n, (int)nb, parts,
                        log, state, status, sweep, some);
     EPHW_CHECK_LAUNCH();
   }
-  if (max_sweeps > last) {
-    hipLaunchKernelGGL(jacobi_tail_kernel, dim3((unsigned)nb), dim3(kLargeThreads), lds, s, h, v, n, parts, log, state,
-                       status, last);
-    EPHW_CHECK_LAUNCH();
-  }
+  hipLaunchKernelGGL(jacobi_tail_kernel, dim3((unsigned)nb), dim3(kLargeThreads), lds, s, h, v, n, parts, log, state,
+                     status, kLargeSweeps);
+  EPHW_CHECK_LAUNCH();
   hipLaunchKernelGGL(jacobi_finish_kernel, dim3((unsigned)nb), dim3(kLargeThreads), 0, s, h, n, eps, v, state, status,
                      some);
   EPHW_CHECK_LAUNCH();
@@ -1092,13 +1091,13 @@ ephw_status launch_large(double2* h, int64_t nb, int n, double* eps, double2* v,
 int* jacobi_large_state(double* work, int n, int64_t nb) { return reinterpret_cast<int*>(work + log_doubles(n) * nb); }
 
 ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* V, double* work, uint32_t* status,
-                             int max_sweeps, hipStream_t s) {
+                             hipStream_t s) {
   if (n <= kSmallN || n > 256 || nb < 1 || nb > kLargeChunk || !work) {
     set_error("jacobi_eigh_some: a chunk of matrices of order 33 to 256 and their workspace");
     return EPHW_EINVAL;
   }
   return launch_large(reinterpret_cast<double2*>(H), nb, n, eps, reinterpret_cast<double2*>(V), work, status,
-                      max_sweeps, true, s);
+                      true, s);
 }
 
 int64_t jacobi_work_doubles(int n, int64_t batch) {
@@ -1127,7 +1126,7 @@ ephw_status jacobi_eigh_grouped(const EighJob* d_jobs, int njobs, int64_t total,
 }
 
 ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                        int max_sweeps, hipStream_t s, double off_tol2) {
+                        hipStream_t s, double off_tol2) {
   if (batch <= 0) return EPHW_OK;
   if (!(off_tol2 > 0.0) || off_tol2 < kOffTol2) off_tol2 = kOffTol2;
   if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
@@ -1157,7 +1156,7 @@ ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V,
   for (int64_t b0 = 0; b0 < batch; b0 += kLargeChunk) {
     const int64_t nb = (batch - b0) < kLargeChunk ? (batch - b0) : kLargeChunk;
     EPHW_TRY(launch_large(reinterpret_cast<double2*>(H) + b0 * n * n, nb, n, eps + b0 * n,
-                          reinterpret_cast<double2*>(V) + b0 * n * n, work, status, max_sweeps, false, s));
+                          reinterpret_cast<double2*>(V) + b0 * n * n, work, status, false, s));
   }
   return EPHW_OK;
 }

@@ -17,17 +17,16 @@ ephw_status phase_matrix(int prec, const double* pts, int64_t n, const int32_t* 
 int64_t jacobi_work_doubles(int n, int64_t batch);
 // off_tol2: convergence when (off-diagonal norm / total norm)^2 <= off_tol2
 // (not below 1e-28, the FP64 default; n <= 32 only, larger orders keep 1e-28)
-// H is overwritten where n > 32.  max_sweeps: the sweep limit the status words
-// hold; where it is small it bounds the launches of the large solves.
+// H is overwritten where n > 32.
 ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                        int max_sweeps, hipStream_t s, double off_tol2 = 1e-28);
+                        hipStream_t s, double off_tol2 = 1e-28);
 
 // Orders above 32, at most 1024 matrices, some of them left out: those whose
 // state (3 ints a matrix in the workspace, here) holds kLeaveOut keep their eps and V.
 constexpr int kLeaveOut = 2;
 int* jacobi_large_state(double* work, int n, int64_t nb);
 ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* V, double* work, uint32_t* status,
-                             int max_sweeps, hipStream_t s);
+                             hipStream_t s);
 
 // The same eigenproblem by tridiagonalisation and QL (tridiag.hip), several
 // times faster, for orders up to 32: eigenvectors agree with jacobi_eigh's to
@@ -41,7 +40,7 @@ ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V
 // the vectors of every matrix agree with its to complex64 rounding.
 bool tridiag_large_better(int n, int64_t batch);
 ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                               int max_sweeps, hipStream_t s);
+                               hipStream_t s);
 
 // many small (n <= 32) eigensolves of different orders in one launch;
 // matrix m of the launch belongs to the job with the largest block_base <= m

@@ -790,7 +790,7 @@ __global__ void __launch_bounds__(256)
 }
 
 ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                       int max_sweeps, hipStream_t s) {
+                       hipStream_t s) {
   if (!work) {
     set_error("tridiag_large_eigh: needs a workspace");
     return EPHW_EINVAL;
@@ -819,7 +819,7 @@ ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, 
                        wstride, v, jacobi_large_state(work, n, nb));
     EPHW_CHECK_LAUNCH();
     EPHW_TRY(jacobi_eigh_some(reinterpret_cast<double*>(h), nb, n, eps + b0 * n, reinterpret_cast<double*>(v), work,
-                              status, max_sweeps, s));
+                              status, s));
   }
   return EPHW_OK;
 }
@@ -882,7 +882,7 @@ bool tridiag_large_better(int n, int64_t batch) {
 }
 
 ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                               int max_sweeps, hipStream_t s) {
+                               hipStream_t s) {
   if (batch <= 0) return EPHW_OK;
   if (n <= 32 || n > kBigMax) {
     set_error("tridiag_large_eigh: matrix order must be in [33, 256]");
@@ -892,7 +892,7 @@ ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, dou
     set_error("tridiag_large_eigh: matrices and eigenvectors must be 16-byte aligned complex128 arrays");
     return EPHW_EINVAL;
   }
-  return launch_big(H, batch, n, eps, V, work, status, max_sweeps, s);
+  return launch_big(H, batch, n, eps, V, work, status, s);
 }
 
 }  // namespace ephw

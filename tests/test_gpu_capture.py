@@ -46,3 +46,39 @@ def test_replays(prec, nw, na, nk, capped):
     ks.close()
     h.close()
     ctx.close()
+
+
+def test_a_limit_raised_after_the_capture_counts():
+    import torch
+    from gpu_run import dev
+    from paper_2603_10295_amd import ephw
+    s = synth.make_system(4, 22, synth.box((2, 2, 1)), synth.box((2, 2, 1)), [4, 51], g_dtype=np.complex64)
+    ctx = ephw.Context(0)
+    h = ephw.System.from_synth(ctx, s)
+    ks = ephw.KSet(h, dev(np.random.default_rng(1).random((5, 3))), 1)
+    q = dev(np.random.default_rng(2).random((3, 3)))
+    out, ref = (torch.empty((3, 5, 66, 4, 4), dtype=torch.complex64, device="cuda:0") for _ in range(2))
+    t = torch.empty((3, 5, 66), dtype=torch.float64, device="cuda:0")
+
+    def call(g):
+        ephw.interpolate_noalloc(ks, q, flags=ephw.OUT_G | ephw.OUT_BAND_SUM, g_out=g, band_sum=t)
+    call(ref)
+    ctx.check()
+    ctx.set_limits(max_sweeps=3)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out)
+    ctx.set_limits(max_sweeps=40)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        ctx.check()
+        assert torch.equal(out, ref)
+    ctx.set_limits(max_sweeps=3)
+    graph.replay()
+    with pytest.raises(ephw.EphwError) as e:
+        ctx.check()
+    assert e.value.status == ephw.ENOCONV
+    ks.close()
+    h.close()
+    ctx.close()
