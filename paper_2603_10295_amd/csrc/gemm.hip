@@ -1796,9 +1796,13 @@ ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream) {
       (prec == 0 || (p.ldb % 2 == 0 && p.strideB % 2 == 0 && p.strideB1 % 2 == 0 && p.strideB2 % 2 == 0 &&
                      !p.offB && reinterpret_cast<uintptr_t>(p.B) % 16 == 0))) {
     // FP64: the 16-row tile's matrix work, padding included, takes less time than
-    // reading B, where a thread per column waits for its operands (M = 16, K = 125,
-    // N = 48000: 29 us against 61)
-    if (prec == 0 && p.any_rounding)
+    // reading B, where a thread per column waits for its operands (K = 125, M = 16,
+    // N = 48000: 29 us against 61; M = 10, N = 65 664: 40 and 62, N = 393 216: 184
+    // and 206).  With up to eight rows, and up to four more so, that thread has few
+    // sums to wait for, and reads B faster once there are columns enough to fill the
+    // chip (M = 4: N = 23 328 19 and 23, 33 024 27 and 24, 65 664 40 and 26; M = 8:
+    // 49 152 29 and 32, 65 664 40 and 37, 131 328 63 and 52).
+    if (prec == 0 && p.any_rounding && (p.M > 8 || p.N < (p.M > 4 ? 65536 : 32768)))
       return p.transA ? launch<double, 16, 128, 16, 1, 4, true, false, 0, 2>(p, stream)
                       : launch<double, 16, 128, 16, 1, 4, false, false, 0, 2>(p, stream);
     return prec == 0 ? dispatch_skinny<double>(p, stream) : dispatch_skinny<float>(p, stream);
