@@ -1189,8 +1189,16 @@ ephw_status ephw_wannier_transform(ephw_kset* ks, const double* q, int64_t nq, c
   // up to 32 bands with every k in one tile: the band-rotation kernels, and up to
   // 24 modes the mode kernel (products of 48 x 8 outputs and K = 8 per pair, 6 x
   // 64 and K = 6 per Re, are mostly padding on GEMM tiles: 340 and 170 us at 512
-  // k x 64 q, 90 and 41 us here)
-  const bool small = nw <= 32 && kt == nk && qb * nk <= 0x7fffffff, small_modes = small && nm <= 24;
+  // k x 64 q, 90 and 41 us here).  From 9 bands on a wavefront takes a pair and its
+  // modes one after the other, so there must be pairs enough: with 24 modes or more
+  // than 16 bands few of them leave the chip idle where GEMM tiles share out the
+  // modes (whole transforms, us, this and GEMM: 32 bands, 12 modes, FP32 8 pairs 183
+  // and 125, 128: 210 and 189, 576: 306 and 474; FP64 576: 627 and 606, 4096: 4954
+  // and 5717; 16 bands, 24 modes, FP64 128: 526 and 475, 576: 699 and 691; 16
+  // bands, 3 modes, 8: 57 and 63).
+  const int64_t enough = nw > 16 ? (kind == 0 ? 1024 : 512) : nw > 8 && nm > 12 ? 512 : 0;
+  const bool small = nw <= 32 && kt == nk && qb * nk <= 0x7fffffff && qb * nk >= enough;
+  const bool small_modes = small && nm <= 24;
   // phases as Eq. (6) writes them (no lattice-vector weights); the q ones
   // carry 1/(Ne Np)
   EPHW_TRY(ws_need(s, WS_CPK, (size_t)nk * ne * cs));
