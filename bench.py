@@ -9,7 +9,8 @@ eigensolves, the Rp phase GEMM (Eq. 9), mode rotation, the Re phase GEMM
 (Eq. 10), band rotations, storing every g_{mn nu}(k,q) (complex64) into a
 q-chunk output buffer.  Inputs are resident in HBM before timing starts.
 
-Reported: g(k,q) elements/s of the FP32-MFMA path (the value), the same
+Reported: g(k,q) elements/s of the FP32 path (the value; its phase sums run on
+the 16-bit matrix cores with FP32 values split), the same
 workload on the FP64 path and the speedup, the error of both against the
 CPU oracle on a q sample, per-stage times from HIP events, the roofline of
 the dominant kernel, and the oracle's own throughput on a bounded sample.
@@ -826,7 +827,7 @@ def main(argv=None):
         err32 = block_error(g32, ref)
         log(f"FP32 vs oracle: normwise {err32[0]:.2e}, max blockwise {err32[1]:.2e}, scaled {err32[2]:.2e}")
 
-    # ---- compensated FP32: K-blocked accumulation in the phase GEMMs ------
+    # ---- compensated FP32: partial sums folded in the phase GEMMs ---------
     comp = None
     if not args.no_comp:
         del p32.out
@@ -835,8 +836,8 @@ def main(argv=None):
         tc, stc = timed(pc, args.comp_steps, 1 if args.warmup else 0, profile=True)
         comp = {"value": cnt.elems / tc, "ms_per_step": tc * 1e3,
                 "re_gemm_ms_per_step": round(stc["re_gemm"][0] / args.comp_steps, 3),
-                "note": "both phase GEMMs accumulate in K blocks of 32 (fresh FP32 MFMA accumulators per "
-                        "block, block sums added in FP32); g stored, band rotations unfused"}
+                "note": "both phase GEMMs on the BF16 matrix cores (FP32 values in three parts), fresh FP32 "
+                        "accumulators every 16 k, partial sums added in FP32; g stored, band rotations unfused"}
         log(f"compensated FP32: {tc * 1e3:.1f} ms/step")
         if cpu is not None:
             e = block_error(pc.sample(qs_idx), ref)

@@ -75,7 +75,8 @@ typedef int32_t ephw_status;
 #define EPHW_FP32        1  /* complex64 GEMMs on FP32 MFMA, g stored c64.  A call
                                that returns g alone may run its phase sums on the
                                16-bit matrix cores with every value split in two
-                               or three parts (error against FP64 no larger): its
+                               or three parts (error against FP64 no larger, for
+                               values above 1e-31; smaller ones lose parts): its
                                g then differs in rounding from that of a call
                                which also returns band sums or the loss.  So do
                                its bands at interpolated k+q, solved by

@@ -661,7 +661,9 @@ bool fuses_behind_any(const ephw_system* s) { return s->nw == 8 && s->nm % 2 == 
 // The forms of a call's Re sums, and the buffers they need beside each other:
 //   kFast      packed operands; W stored and rotated in a pass of its own where
 //              the fused epilogue would run on VALU, which is most of the kernel
-//              behind the faster product (Nw = 4, K = 250: 1070 us fused, 540 so)
+//              behind the faster product (g of 4000 k x 100 q, us, fused and
+//              stored: Nw = 4, Nm = 6, K = 64 483 and 414, 250 875 and 573; Nw = 8,
+//              Nm = 9, K = 64 2590 and 2134, 250 4744 and 2992; 64 x 8 likewise)
 //   kUnpacked  the same without the packed operands
 //   kPlain     W stored only where no epilogue takes it: the least memory
 enum InterpForm { kFast, kUnpacked, kPlain };

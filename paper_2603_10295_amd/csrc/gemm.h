@@ -122,8 +122,10 @@ struct GemmParams {
   // against 64 bits no larger; FP64: on tiles that sum in another order.  Set
   // for FP64 results, and for FP32 ones where only complex64 values are
   // returned.  Sums returned in double precision (band sums, losses,
-  // linewidths, gradients) keep the FP32 instructions and with them their
-  // digits beyond FP32's, and so do the eigenproblems they depend on.
+  // linewidths, gradients) keep the FP32 instructions, and the eigenproblems
+  // they depend on their solver, so that their values do not move by more than
+  // 1e-9; they are no more accurate for it (against 64 bits their errors are
+  // some 1e-7 either way).
   bool any_rounding = false;
   int64_t n1 = 1, n2 = 1;
   int64_t strideA1 = 0, strideA2 = 0, strideB1 = 0, strideB2 = 0, strideC1 = 0, strideC2 = 0;
@@ -149,7 +151,8 @@ int64_t cgemm_tiles(int prec, int64_t M, int64_t N);
 // 32-bit byte offsets)
 bool cgemm_packable(int64_t M, int64_t N, int64_t K);
 
-// prec: 0 = complex128 on FP64 MFMA, 1 = complex64 on FP32 MFMA
+// prec: 0 = complex128 on FP64 MFMA, 1 = complex64 on FP32 MFMA, or on the 16-bit
+// ones with split values (any_rounding, packed)
 ephw_status cgemm(int prec, const GemmParams& p, hipStream_t stream);
 
 // Many independent GEMMs C = A B (row-major, no transposes) in one persistent

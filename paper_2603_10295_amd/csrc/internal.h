@@ -74,9 +74,11 @@ inline ephw_status upload(X** dst, const X* src, size_t count, int64_t* owner_by
   return EPHW_OK;
 }
 
-// k points from which an FP32 set's Re sums run on packed operands: packing the
-// other operand costs about 24 bytes of traffic per value, the faster product
-// saves about 2e-14 s per value and k point, which breaks even near 270 points
+// k points from which an FP32 set's Re sums run on packed operands.  The split and
+// the packed form are level at 256 points (64 q, us: Nw = 8, K = 1000 491 and 467,
+// Nw = 11, K = 324 592 and 580, Nw = 16, K = 216 748 and 752) and the packed one is
+// ahead by 0.80 to 0.94 at 384 (686 and 563, 742 and 688, 975 and 917); below 512
+// the difference is not taken for a second copy of a set's phases
 constexpr int64_t kPackMinPoints = 512;
 
 inline int prec_kind(int32_t prec) { return prec == EPHW_FP64 ? 0 : 1; }

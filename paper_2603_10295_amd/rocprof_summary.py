@@ -42,10 +42,11 @@ def short_name(name: str) -> str:
 
 
 def source_digest() -> str:
-    """Hash of the GEMM source: the traffic figures hold only for this kernel."""
+    """Hash of the GEMM sources: the traffic figures hold only for these kernels."""
     h = hashlib.sha256()
-    with open(os.path.join(HERE, "csrc", "gemm.hip"), "rb") as f:
-        h.update(f.read())
+    for name in ("gemm.hip", "gemm_split.h"):
+        with open(os.path.join(HERE, "csrc", name), "rb") as f:
+            h.update(f.read())
     return h.hexdigest()[:16]
 
 
