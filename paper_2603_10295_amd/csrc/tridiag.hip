@@ -18,9 +18,9 @@
 // in LDS, then a thread per row of Q applies the log to its row in registers.
 // (With all lanes of a group computing the recurrence alike, in one kernel with
 // the reduction, the recurrence was most of the time.)
-// 131 072 matrices (us, reduction + QL, Jacobi): n = 8: 104 + 246, 753; n = 11:
-// 334 + 539, 2363; n = 16: 677 + 1285, 7431.  32 768 of n = 24: 939 + 1091,
-// 11 583; of n = 32: 1782 + 2849, 33 633.  The QL of a few matrices is its chain
+// 131 072 matrices (us, reduction + QL, Jacobi): n = 8: 103 + 242, 761; n = 11:
+// 333 + 535, 2347; n = 16: 667 + 1277, 7325.  32 768 of n = 24: 929 + 1082,
+// 11 454; of n = 32: 1734 + 2814, 33 783.  The QL of a few matrices is its chain
 // alone (n = 16: 105 us).
 #include "kernels.h"
 
@@ -386,8 +386,9 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
 // applied to the rows of a real Z, 64 rows per wavefront; the reflectors, last
 // first, take the columns of Z back, a wavefront per column.  Bound by the QL
 // chain (about 0.85 n^2 rotations in a row) and the reduction's n steps of five
-// barriers.  8 matrices of n = 150: reduction 1.27 ms,
-// QL 2.84, rotations 1.23, back 0.12; Jacobi 9.9.
+// barriers.  8 matrices of n = 150: reduction 1.19 ms,
+// QL 2.90, rotations 1.25, back 0.12, launches that find nothing left to the
+// Jacobi kernels 0.08; Jacobi 9.9.
 // ---------------------------------------------------------------------------
 constexpr int kBigThreads = 1024, kBigMax = 256, kBigRounds = 3;
 

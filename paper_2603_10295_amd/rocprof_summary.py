@@ -90,7 +90,7 @@ def traffic(fetch_db: str, write_db: str, copy_bytes: int, command: str = "") ->
     cf, cw = copy_value(fg), copy_value(wg)
     ff = kib / cf if cf else None
     fw = kib / cw if cw else None
-    out = [f"# HBM traffic per dispatch from rocprofv3 counters (gemm.hip digest {source_digest()})",
+    out = [f"# HBM traffic per dispatch from rocprofv3 counters (GEMM source digest {source_digest()})",
            f"# command: {command}" if command else "# command: (not recorded)",
            f"# calibration: device copy of {copy_bytes} bytes read FETCH_SIZE={cf} KiB, WRITE_SIZE={cw} KiB",
            f"# scale factors: fetch x{ff:.4f}, write x{fw:.4f}" if ff and fw else "# scale factors: unavailable",
