@@ -853,12 +853,27 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
   EPHW_TRY(ws_need(s, WS_LOSS, (size_t)kt * qb * rot_tiles * 8));
   EPHW_TRY(ws_need(s, WS_UBAR, (size_t)qb * nm * nm * cs));
   const int chunks_u = splitk_chunks(nw2, 16, 256);
-  // partials of the ubar products, in the T buffer (free after the k loop) for as
-  // many Re per launch as it holds; one Re at a time where it holds none
+  // partials of the ubar products: in G_nu's buffer or T's, free by then, for as
+  // many Re per launch as the larger holds (nearly all but for Nw^2 far below Nm).
+  // Where that is less than an eighth of them and no memory cap is set, in up to
+  // 512 MB of their own (Nw = 1, Nm = 24, 27 Re: 408 us with a launch per Re, 215)
   const int64_t ubar_each = qb * chunks_u * nm * nm * (int64_t)cs;
-  const int64_t ubar_group = std::max<int64_t>(1, std::min<int64_t>(ne, (int64_t)wsz / ubar_each));
-  const bool ubar_in_t = ubar_each <= (int64_t)wsz;
-  if (!ubar_in_t) EPHW_TRY(ws_need(s, WS_SPLIT, (size_t)ubar_each));
+  int64_t ubar_group = std::min<int64_t>(ne, (int64_t)std::max(gsz, wsz) / ubar_each);
+  bool ubar_own = false;
+  if (ubar_group < ne && 8 * ubar_group < ne && s->mem->limit == 0) {
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(ne, ((int64_t)512 << 20) / ubar_each));
+    const ephw_status got = ws_need(s, WS_SPLIT, (size_t)(want * ubar_each));
+    if (got != EPHW_OK && got != EPHW_ENOMEM) return got;
+    if (got == EPHW_OK) {
+      ubar_own = true;
+      ubar_group = want;
+    }
+  }
+  if (ubar_group < 1) {
+    EPHW_TRY(ws_need(s, WS_SPLIT, (size_t)ubar_each));
+    ubar_own = true;
+    ubar_group = 1;
+  }
   // the per-pair Vbar GEMMs (Nw x Nw outputs, K = Nm Nw) split K until a unit
   // has about 1024 tiles
   const int64_t pair_out_tiles = cgemm_tiles(kind, nw, nw);
@@ -873,7 +888,7 @@ ephw_status ephw_loss_backward(ephw_kset* ks, const double* q, int64_t nq, const
   char* Gnubar = static_cast<char*>(wsp(s, WS_GNUBAR));
   char* W = static_cast<char*>(wsp(s, WS_W));
   char* Tm = static_cast<char*>(wsp(s, WS_T));
-  char* ubar_part = ubar_in_t ? Tm : static_cast<char*>(wsp(s, WS_SPLIT));
+  char* ubar_part = ubar_own ? static_cast<char*>(wsp(s, WS_SPLIT)) : gsz >= wsz ? Gnu : Tm;
   char* Yb = static_cast<char*>(wsp(s, WS_YBAR));
   char* Z = static_cast<char*>(wsp(s, WS_Z));
   char* Wb = static_cast<char*>(wsp(s, WS_WBAR));

@@ -45,17 +45,20 @@ def test_loss_backward_takes_no_more_for_its_partials(prec, nw, na, nk):
     ctx.close()
 
 
-def test_partials_one_re_at_a_time():
-    """The form of a unit whose other buffers hold no partial: 24 modes, 4 bands,
-    one k.  Modes and bands are not degenerate."""
+@pytest.mark.parametrize("nw,capped", [(4, False), (1, False), (1, True)])
+def test_partials_in_groups(nw, capped):
+    """Partials of 24 modes in the free buffers, four Re of six at a time; of one
+    band, where these hold none, in their own, and one Re at a time under a cap."""
     import oracle.adjoint
     import torch
     from gpu_run import dev
     from paper_2603_10295_amd import ephw
-    s = synth.make_system(4, 8, synth.box((3, 2, 1)), synth.box((2, 2, 1)), [4, 41])
+    s = synth.make_system(nw, 8, synth.box((3, 2, 1)), synth.box((2, 2, 1)), [4, 41])
     k = np.zeros((1, 3))
     ref = oracle.adjoint.loss_and_grads(s, k, k, 11)
     ctx, h = open_system(s)
+    if capped:
+        ctx.set_limits(max_device_bytes=1 << 30)
     ks = ephw.KSet(h, dev(k), 0)
     dg = torch.zeros(s.g.shape, dtype=torch.complex128, device="cuda:0")
     dk, dq = torch.zeros((1, 3), dtype=torch.float64, device="cuda:0"), torch.zeros((1, 3), dtype=torch.float64, device="cuda:0")
