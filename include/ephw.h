@@ -25,7 +25,7 @@
  *     u_{kappa alpha, nu}(q) = e_{kappa alpha, nu}(q) / sqrt(M_kappa) (mode
  *     index kappa alpha = 3 kappa + alpha); omega = sqrt(|lambda|).
  *   - Eigenvalues are ascending; each eigenvector column is scaled so that its
- *     largest-magnitude component is real and positive (above order 32 the first
+ *     largest-magnitude component is real and positive (above order 16 the first
  *     of those within 5e-8 of the largest).
  *
  * Memory
@@ -192,7 +192,7 @@ ephw_status ephw_bands(ephw_system* sys, const double* k, int64_t nk, double* ep
      evecs [nq][nm][nm] c128 eigenvectors e (columns), or NULL  (u = e/sqrt(M)),
            16-byte aligned (EPHW_EINVAL otherwise)
    The modes nu of every other call are these, also within degenerate blocks
-   (to complex64 rounding where g is complex64). */
+   (to 1e-10, and to complex64 rounding where g is complex64). */
 ephw_status ephw_phonons(ephw_system* sys, const double* q, int64_t nq, double* lam,
                          double* omega, void* evecs, void* stream);
 

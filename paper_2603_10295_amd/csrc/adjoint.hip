@@ -580,8 +580,9 @@ ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const 
     if (jw > 0) EPHW_TRY(ws_need(s, WS_JWORK, (size_t)jw * 8));
     double *hk = static_cast<double*>(wsp(s, WS_HK)), *lam = static_cast<double*>(wsp(s, WS_LAM));
     double *e = static_cast<double*>(wsp(s, WS_E)), *work = jw > 0 ? static_cast<double*>(wsp(s, WS_JWORK)) : nullptr;
-    if (kind != 0 && any_rounding && tridiag_large_better((int)nm, nq))   // see interp_eigh_ws
-      EPHW_TRY(tridiag_large_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, st));
+    const double close = close_modes(kind, any_rounding);
+    if (close > 0.0 && tridiag_modes_better((int)nm, nq))
+      EPHW_TRY(tridiag_modes_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, close, st));
     else
       EPHW_TRY(jacobi_eigh(hk, nq, (int)nm, lam, e, work, s->ctx->status, st));
   }

@@ -19,7 +19,7 @@ void set_error(const std::string& msg) { g_last_error = msg; }
 
 ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64_t nr, const double* mats, int dim,
                            double* out_eps, double* out_v, double* hk, double* jwork, bool stages, hipStream_t st,
-                           bool c64) {
+                           double close) {
   const int64_t d2 = (int64_t)dim * dim;
   Stage sg_(s, EPHW_STAGE_EIG, st, stages);
   GemmParams p;
@@ -33,8 +33,8 @@ ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64
   p.C = hk;
   p.ldc = d2;
   EPHW_TRY(cgemm(0, p, st));
-  if (c64 && tridiag_large_better(dim, n))
-    return tridiag_large_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, st);
+  if (close > 0.0 && tridiag_modes_better(dim, n))
+    return tridiag_modes_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, close, st);
   return jacobi_eigh(hk, n, dim, out_eps, out_v, jwork, s->ctx->status, st);
 }
 
@@ -798,7 +798,7 @@ ephw_status interpolate_small(ephw_kset* ks, const double* q, const int32_t* kq_
     EPHW_TRY(phase_matrix(0, q, nq, s->r_c, s->w_c, s->nc, w.pqc, st));
   }
   EPHW_TRY(interp_eigh_ws(s, w.pqc, nq, s->nc, s->c_scaled, nm, w.lam, w.e, w.hk, w.jwork, stages, st,
-                          kind != 0 && r.any_rounding));
+                          close_modes(kind, r.any_rounding)));
   {
     Stage sg_(s, EPHW_STAGE_OTHER, st, stages);
     if (omega) EPHW_TRY(abs_sqrt(w.lam, omega, nq * nm, st));

@@ -74,7 +74,7 @@ __host__ __device__ __forceinline__ int ascending_place(At at, int n, int i) {
   return order ? place : i;
 }
 
-// Orders above 32: the component of an eigenvector that is made real positive is
+// Orders above 16: the component of an eigenvector that is made real positive is
 // the first whose squared magnitude is at least kTied times the largest.  Atoms
 // that a symmetry maps on each other tie, and the last bits, in which the solvers
 // differ, would choose between them.

@@ -87,13 +87,18 @@ inline size_t csize(int kind) { return kind == 0 ? 16 : 8; }
 // FP64 interpolation + eigensolve: out_eps [n][dim], out_v c128 [n][dim][dim]
 // from A = phases [n][nr] (c128) and B = R-space matrices [nr][dim*dim] (c128),
 // with caller-given buffers: hk [n][dim][dim] c128 and, for dim > 32, jwork of
-// jacobi_work_doubles(dim, n) doubles.  c64: the vectors are used rounded to
-// complex64 only.  The mode vectors of D(q) are the same basis in every call,
-// also inside degenerate blocks: a loss, its gradient, band sums per mode and
-// the modes of ephw_phonons belong together.
+// jacobi_work_doubles(dim, n) doubles.  close: see tridiag_modes_eigh, 0 for the
+// Jacobi solver alone
 ephw_status interp_eigh_ws(ephw_system* s, const double* phase, int64_t n, int64_t nr, const double* mats, int dim,
                            double* out_eps, double* out_v, double* hk, double* jwork, bool stages, hipStream_t st,
-                           bool c64 = false);
+                           double close = 0.0);
+
+// The mode vectors of D(q) are the same basis in every call, also inside
+// degenerate blocks: a loss, its gradient, band sums per mode and the modes of
+// ephw_phonons belong together.  Calls whose rounding is free may take the
+// tridiagonal solver where its vectors are those of Jacobi to what they are used
+// for: a rounding of some 1e-15 over the gap, below complex64's 6e-8, or 1e-10.
+inline double close_modes(int kind, bool any_rounding) { return !any_rounding ? 0.0 : kind == 0 ? 1e-4 : 1e-6; }
 
 ephw_status interpolate_large(ephw_kset* ks, const double* q, int64_t nq, const int32_t* kq_index, int64_t q_offset,
                               uint32_t flags, void* g_out, double* band_sum, double* loss, uint64_t loss_seed,

@@ -383,6 +383,14 @@ __device__ __forceinline__ void jacobi_small_body(const double* __restrict__ H, 
         bv = v;
       }
     }
+    for (int r = 0; n > 16 && r < n; ++r) {
+      const double2 v = V[r * N2 + src];
+      if (norm2(v) >= kTied * best) {
+        best = norm2(v);
+        bv = v;
+        break;
+      }
+    }
     const double mag = sqrt(best);
     fix[lane] = mag > 0.0 ? make_double2(bv.x / mag, -bv.y / mag) : make_double2(1.0, 0.0);
   }
@@ -664,7 +672,7 @@ __device__ __forceinline__ void jacobi_small_body_pos(JobAt job_at, uint32_t* st
 template <int NP>
 __global__ void __launch_bounds__(64 * kSmallPerBlock)
     jacobi_small_kernel(const double* __restrict__ H, int64_t batch, int n, double* __restrict__ eps,
-                        double* __restrict__ V, uint32_t* status, double tol2) {
+                        double* __restrict__ V, uint32_t* status, double tol2, bool some) {
   extern __shared__ double2 jlds[];
   using L = SmallLayout<NP>;
   constexpr int M = solves_per_wave<NP>();
@@ -688,6 +696,7 @@ __global__ void __launch_bounds__(64 * kSmallPerBlock)
     };
     jacobi_small_body_pos<NP>(job_at, status, tol2, jlds + (wave * M + g * P::S) * L::slice_elems, lane % P::LPM);
   } else {
+    if (some && H[2 * m0 * n * n + 1] != 1.0) return;   // see jacobi_eigh_some
     jacobi_small_body<NP>(H, n, eps, V, status, tol2, m0, jlds + wave * L::slice_elems, lane, ent, pqt);
   }
 }
@@ -737,7 +746,7 @@ __global__ void __launch_bounds__(64 * kSmallPerBlock)
   }
 }
 
-using SmallKernel = void (*)(const double*, int64_t, int, double*, double*, uint32_t*, double);
+using SmallKernel = void (*)(const double*, int64_t, int, double*, double*, uint32_t*, double, bool);
 using GroupedKernel = void (*)(const EighJob*, int, int64_t, uint32_t*);
 
 template <int... NPs>
@@ -1062,6 +1071,20 @@ constexpr int64_t kLargeChunk = 1024;  // matrices per large-n launch (bounds th
 // doubles of one matrix's two logs: n2 - 1 rounds of n / 2 rotations each
 inline int64_t log_doubles(int n) { return (int64_t)4 * 2 * (n + (n & 1) - 1) * large_pairs(n); }
 
+ephw_status launch_small(const double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status,
+                         double off_tol2, bool some, hipStream_t s) {
+  const int np = (n + 1) / 2, waves = Small::per_block(np), per = waves * Small::per_wave(np);
+  const int64_t max_per_launch = (int64_t)0x7fffffff * per;
+  for (int64_t b0 = 0; b0 < batch; b0 += max_per_launch) {
+    const int64_t nb = (batch - b0) < max_per_launch ? (batch - b0) : max_per_launch;
+    const int64_t grid = (nb + per - 1) / per;
+    hipLaunchKernelGGL(Small::small(np), dim3((unsigned)grid), dim3(64 * waves), Small::bytes(np), s,
+                       H + 2 * b0 * n * n, nb, n, eps + b0 * n, V + 2 * b0 * n * n, status, off_tol2, some);
+    EPHW_CHECK_LAUNCH();
+  }
+  return EPHW_OK;
+}
+
 // nb <= kLargeChunk matrices
 ephw_status launch_large(double2* h, int64_t nb, int n, double* eps, double2* v, double* work, uint32_t* status,
                          bool some, hipStream_t s) {
@@ -1088,17 +1111,18 @@ ephw_status launch_large(double2* h, int64_t nb, int n, double* eps, double2* v,
 
 }  // namespace
 
-int* jacobi_large_state(double* work, int n, int64_t nb) { return reinterpret_cast<int*>(work + log_doubles(n) * nb); }
-
 ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* V, double* work, uint32_t* status,
                              hipStream_t s) {
-  if (n <= kSmallN || n > 256 || nb < 1 || nb > kLargeChunk || !work) {
-    set_error("jacobi_eigh_some: a chunk of matrices of order 33 to 256 and their workspace");
+  // (of the small solves, those with several matrices to a wavefront take them all)
+  if (n <= 16 || n > 256 || nb < 1 || (n > kSmallN && (nb > kLargeChunk || !work))) {
+    set_error("jacobi_eigh_some: matrices of order 17 to 256, above 32 a chunk of them and their workspace");
     return EPHW_EINVAL;
   }
-  return launch_large(reinterpret_cast<double2*>(H), nb, n, eps, reinterpret_cast<double2*>(V), work, status,
-                      true, s);
+  if (n <= kSmallN) return launch_small(H, nb, n, eps, V, status, kOffTol2, true, s);
+  return launch_large(reinterpret_cast<double2*>(H), nb, n, eps, reinterpret_cast<double2*>(V), work, status, true, s);
 }
+
+int* jacobi_large_state(double* work, int n, int64_t nb) { return reinterpret_cast<int*>(work + log_doubles(n) * nb); }
 
 int64_t jacobi_work_doubles(int n, int64_t batch) {
   if (n <= kSmallN) return 0;
@@ -1137,18 +1161,7 @@ ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V,
     set_error("jacobi_eigh: matrix order must be in [1, 256]");
     return EPHW_EUNSUPPORTED;
   }
-  if (n <= kSmallN) {
-    const int np = (n + 1) / 2, waves = Small::per_block(np), per = waves * Small::per_wave(np);
-    const int64_t max_per_launch = (int64_t)0x7fffffff * per;
-    for (int64_t b0 = 0; b0 < batch; b0 += max_per_launch) {
-      const int64_t nb = (batch - b0) < max_per_launch ? (batch - b0) : max_per_launch;
-      const int64_t grid = (nb + per - 1) / per;
-      hipLaunchKernelGGL(Small::small(np), dim3((unsigned)grid), dim3(64 * waves), Small::bytes(np), s,
-                         H + 2 * b0 * n * n, nb, n, eps + b0 * n, V + 2 * b0 * n * n, status, off_tol2);
-      EPHW_CHECK_LAUNCH();
-    }
-    return EPHW_OK;
-  }
+  if (n <= kSmallN) return launch_small(H, batch, n, eps, V, status, off_tol2, false, s);
   if (!work) {
     set_error("jacobi_eigh: large matrices need a workspace");
     return EPHW_EINVAL;

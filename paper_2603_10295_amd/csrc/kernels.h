@@ -21,8 +21,10 @@ int64_t jacobi_work_doubles(int n, int64_t batch);
 ephw_status jacobi_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
                         hipStream_t s, double off_tol2 = 1e-28);
 
-// Orders above 32, at most 1024 matrices, some of them left out: those whose
-// state (3 ints a matrix in the workspace, here) holds kLeaveOut keep their eps and V.
+// Some of the matrices only, the others keep their eps and V.  Up to order 32:
+// those whose first entry has an imaginary part of 1 (the solves do not read it).
+// Above, at most 1024 of them: those whose state (3 ints a matrix in the
+// workspace, here) does not hold kLeaveOut.
 constexpr int kLeaveOut = 2;
 int* jacobi_large_state(double* work, int n, int64_t nb);
 ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* V, double* work, uint32_t* status,
@@ -35,12 +37,12 @@ ephw_status jacobi_eigh_some(double* H, int64_t nb, int n, double* eps, double* 
 // tridiag_better: the rule for taking it.
 bool tridiag_better(int n);
 ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s);
-// Orders 33 to 256 (and jacobi_eigh's workspace): matrices with eigenvalues
-// closer than 1e-6 of the largest are solved by jacobi_eigh's kernels, so that
-// the vectors of every matrix agree with its to complex64 rounding.
-bool tridiag_large_better(int n, int64_t batch);
-ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                               hipStream_t s);
+// Orders 17 to 256 (work: jacobi_eigh's) for the modes, whose vectors are to be
+// jacobi_eigh's: matrices with eigenvalues closer than `close` of the largest are
+// solved by its kernels, those of the others agree to a rounding over the gap.
+bool tridiag_modes_better(int n, int64_t batch);
+ephw_status tridiag_modes_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                               double close, hipStream_t s);
 
 // many small (n <= 32) eigensolves of different orders in one launch;
 // matrix m of the launch belongs to the job with the largest block_base <= m

@@ -445,7 +445,8 @@ ephw_status ephw_interpolate_pairs(ephw_kset* ks, const double* q, int64_t nq, i
     if (!by_k || !pl.pack2) EPHW_TRY(phase_matrix(kind, qp, pl.nqp, s->r_p, s->w_p, s->np, w.pq, st));
     EPHW_TRY(phase_matrix(0, qp, pl.nqp, s->r_c, s->w_c, s->nc, w.pqc, st));
   }
-  EPHW_TRY(interp_eigh_ws(s, w.pqc, pl.nqp, s->nc, s->c_scaled, nm, w.lam, w.e, w.hk, w.jwork, true, st));
+  EPHW_TRY(interp_eigh_ws(s, w.pqc, pl.nqp, s->nc, s->c_scaled, nm, w.lam, w.e, w.hk, w.jwork, true, st,
+                          close_modes(kind, kind == 0)));
   {
     Stage sg_(s, EPHW_STAGE_OTHER, st);
     EPHW_TRY(mode_vectors(kind, w.e, pl.nqp, nm, s->ism, w.u, st));

@@ -84,9 +84,18 @@ __device__ __forceinline__ bool negligible(double e, double d0, double d1) {
   return fabs(e) <= fmax(2.220446049250313e-16 * (fabs(d0) + fabs(d1)), 1e-140);
 }
 
-// H -> d in eps, |e| and the scale's exponent in the first n + 1 doubles of H's
-// own matrix, Q in V
-template <int N, int L>
+// Where |e| and the scale's exponent stay between the kernels, in doubles of the
+// matrix in H: the first n + 1 of it, or (KEEP: the Jacobi kernels may take the
+// matrix) the imaginary parts of its diagonal, which no solver reads; |e| of the
+// last index is not used
+template <bool KEEP>
+struct EdgeSlots {
+  static __device__ __forceinline__ int e(int n, int i) { return KEEP ? 2 * i * (n + 1) + 1 : i; }
+  static __device__ __forceinline__ int exponent(int n) { return KEEP ? e(n, n - 1) : n; }
+};
+
+// H -> d in eps, |e| and the scale's exponent in H (EdgeSlots), Q in V
+template <int N, int L, bool KEEP>
 __global__ void __launch_bounds__((64 * TriShape<N, L>::waves))
     reduce_kernel(double2* __restrict__ H, int64_t batch, int n, double* __restrict__ eps, double2* __restrict__ V) {
   using S = TriShape<N, L>;
@@ -195,9 +204,10 @@ __global__ void __launch_bounds__((64 * TriShape<N, L>::waves))
   }
   wave_sync();
   if (!live || r >= n) return;
+  using Edge = EdgeSlots<KEEP>;
   eps[b * n + r] = dr;
-  off[r] = er;
-  if (r == 0) off[n] = (double)ex;               // n = 1: the matrix has two doubles
+  if (!KEEP || r + 1 < n) off[Edge::e(n, r)] = er;
+  if (r == 0) off[Edge::exponent(n)] = (double)ex;   // n = 1: the matrix has two doubles
   double2* out = V + (b * n + r) * n;
 #pragma unroll
   for (int c = 0; c < N; ++c) {
@@ -207,11 +217,12 @@ __global__ void __launch_bounds__((64 * TriShape<N, L>::waves))
 }
 
 // (d, e, Q) -> eigenvalues ascending (ties by index) and their vectors, each
-// with its largest entry real positive
-template <int N>
+// with its largest entry real positive.  KEEP: the imaginary part of H's first
+// entry becomes 1 where eigenvalues are closer than `close` of the largest, else 0
+template <int N, bool KEEP>
 __global__ void __launch_bounds__((QlShape<N>::M * N))
-    ql_kernel(const double2* __restrict__ H, int64_t batch, int n, double* __restrict__ eps, double2* __restrict__ V,
-              uint32_t* status) {
+    ql_kernel(double2* __restrict__ H, int64_t batch, int n, double* __restrict__ eps, double2* __restrict__ V,
+              uint32_t* status, double close) {
   using S = QlShape<N>;
   constexpr int M = S::M, T = S::T, CB = S::CB;
   __shared__ double2 shared[S::shared];
@@ -220,6 +231,8 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
   __shared__ uint32_t steps[M * T];              // l | m << 16 of each logged step
   __shared__ int rank[M * N];
   __shared__ double2 fix[M * CB];
+  __shared__ int near[M];
+  using Edge = EdgeSlots<KEEP>;
   const int tid = threadIdx.x;
   const int r = tid % n, mt = tid / n;           // row, matrix of the workgroup
   const int64_t b0 = (int64_t)blockIdx.x * M, b = b0 + mt;
@@ -227,7 +240,8 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
   double2 z[N];
   if (live) {
     sd[r * M + mt] = eps[b * n + r];
-    se[r * M + mt] = reinterpret_cast<const double*>(H + b * n * n)[r];
+    se[r * M + mt] = reinterpret_cast<const double*>(H + b * n * n)[Edge::e(n, r)];
+    if (KEEP && r == 0) near[mt] = 0;
     const double2* in = V + (b * n + r) * n;
 #pragma unroll
     for (int c = 0; c < N; ++c) z[c] = c < n ? in[c] : make_double2(0.0, 0.0);
@@ -340,8 +354,17 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
   if (live) {
     const int place = ascending_place([&](int j) { return sd[j * M + mt]; }, n, r);
     rank[mt * N + r] = place;
-    const double* tail = reinterpret_cast<const double*>(H + b * n * n);
-    eps[b * n + place] = ldexp(sd[r * M + mt], (int)tail[n]);
+    const double* edge = reinterpret_cast<const double*>(H + b * n * n);
+    eps[b * n + place] = ldexp(sd[r * M + mt], (int)edge[Edge::exponent(n)]);
+    if constexpr (KEEP) {
+      double top = 0.0, gap = HUGE_VAL;
+      for (int j = 0; j < n; ++j) {
+        const double o = sd[j * M + mt];
+        top = fmax(top, fabs(o));
+        if (j != r) gap = fmin(gap, fabs(o - sd[r * M + mt]));
+      }
+      if (gap <= close * top) near[mt] = 1;      // every lane that writes, the same value
+    }
   }
   // phases, CB columns at a time: rows to LDS, a thread per column
 #pragma unroll
@@ -363,6 +386,16 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
           bv = x;
         }
       }
+      if constexpr (N > 16)
+        for (int j = 0; j < n; ++j) {
+          const double2 x = shared[(tid / CB * N + j) * CB + tid % CB];
+          const double m2 = x.x * x.x + x.y * x.y;
+          if (m2 >= kTied * best) {
+            best = m2;
+            bv = x;
+            break;
+          }
+        }
       const double mag = sqrt(best);
       fix[tid] = mag > 0.0 ? make_double2(bv.x / mag, -bv.y / mag) : make_double2(1.0, 0.0);
     }
@@ -376,6 +409,7 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
       }
     }
   }
+  if (KEEP && live && r == 0) H[b * n * n].y = near[mt] ? 1.0 : 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -391,11 +425,6 @@ __global__ void __launch_bounds__((QlShape<N>::M * N))
 // Jacobi kernels 0.08; Jacobi 9.9.
 // ---------------------------------------------------------------------------
 constexpr int kBigThreads = 1024, kBigMax = 256, kBigRounds = 3;
-
-// Vectors of eigenvalues closer than this times the largest are not those of
-// the Jacobi solver (a rounding of 1e-15 over the gap, against the 6e-8 of
-// complex64): such a matrix is solved by Jacobi.
-constexpr double kCloseGap = 1e-6;
 
 // A matrix's part of the workspace: jacobi_work_doubles' share, 4 n (n - 1)
 // doubles or more, holds the 3 n^2 + 9 n + 4 of these for n >= 33.
@@ -686,7 +715,7 @@ __global__ void __launch_bounds__(64) rotate_big_kernel(int n, double* __restric
 // the workspace in place of the log (V still holds the reflectors)
 __global__ void __launch_bounds__(256)
     back_big_kernel(const double2* __restrict__ V, int n, double* __restrict__ work, int64_t wstride,
-                    double* __restrict__ eps) {
+                    double* __restrict__ eps, double close) {
   constexpr int NX = kBigMax / 64;
   const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= n) return;
@@ -769,7 +798,7 @@ __global__ void __launch_bounds__(256)
   }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) place += __shfl_xor(place, off, 64);
-  if (-group_max<64>(-gap) <= kCloseGap * group_max<64>(top)) w.state[3] = 1;
+  if (-group_max<64>(-gap) <= close * group_max<64>(top)) w.state[3] = 1;
   if (!__all(order)) place = j;                  // NaN eigenvalues (a matrix that is not finite) would share places
   if (lane == 0) eps[b * n + place] = ldexp(mine, w.state[0]);
 #pragma unroll
@@ -791,9 +820,9 @@ __global__ void __launch_bounds__(256)
 }
 
 ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                       hipStream_t s) {
+                       double close, hipStream_t s) {
   if (!work) {
-    set_error("tridiag_large_eigh: needs a workspace");
+    set_error("tridiag_modes_eigh: orders above 32 need a workspace");
     return EPHW_EINVAL;
   }
   constexpr int64_t kChunk = 1024;               // that of jacobi_work_doubles
@@ -814,7 +843,7 @@ ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, 
       EPHW_CHECK_LAUNCH();
     }
     hipLaunchKernelGGL(back_big_kernel, dim3((unsigned)ceil_div(n, 4), nb), dim3(256), 0, s, v, n, work, wstride,
-                       eps + b0 * n);
+                       eps + b0 * n, close);
     EPHW_CHECK_LAUNCH();
     hipLaunchKernelGGL(store_big_kernel, dim3((unsigned)ceil_div((int64_t)n * n, 256), nb), dim3(256), 0, s, n, work,
                        wstride, v, jacobi_large_state(work, n, nb));
@@ -825,8 +854,9 @@ ephw_status launch_big(double* H, int64_t batch, int n, double* eps, double* V, 
   return EPHW_OK;
 }
 
-template <int N, int L>
-ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s) {
+template <int N, int L, bool KEEP = false>
+ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint32_t* status, hipStream_t s,
+                   double close = 0.0) {
   using S = TriShape<N, L>;
   const int64_t grid = ceil_div(batch, (int64_t)S::waves * S::G), gridq = ceil_div(batch, QlShape<N>::M);
   if (grid > 0x7fffffff || gridq > 0x7fffffff) {
@@ -835,11 +865,11 @@ ephw_status launch(double* H, int64_t batch, int n, double* eps, double* V, uint
   }
   // every column's phase needs a thread as well as every row
   const int rows = QlShape<N>::M * (n > QlShape<N>::CB ? n : QlShape<N>::CB);
-  hipLaunchKernelGGL((reduce_kernel<N, L>), dim3((unsigned)grid), dim3(64 * S::waves), 0, s,
+  hipLaunchKernelGGL((reduce_kernel<N, L, KEEP>), dim3((unsigned)grid), dim3(64 * S::waves), 0, s,
                      reinterpret_cast<double2*>(H), batch, n, eps, reinterpret_cast<double2*>(V));
   EPHW_CHECK_LAUNCH();
-  hipLaunchKernelGGL((ql_kernel<N>), dim3((unsigned)gridq), dim3((unsigned)((rows + 63) / 64 * 64)), 0, s,
-                     reinterpret_cast<const double2*>(H), batch, n, eps, reinterpret_cast<double2*>(V), status);
+  hipLaunchKernelGGL((ql_kernel<N, KEEP>), dim3((unsigned)gridq), dim3((unsigned)((rows + 63) / 64 * 64)), 0, s,
+                     reinterpret_cast<double2*>(H), batch, n, eps, reinterpret_cast<double2*>(V), status, close);
   EPHW_CHECK_LAUNCH();
   return EPHW_OK;
 }
@@ -874,26 +904,35 @@ ephw_status tridiag_eigh(double* H, int64_t batch, int n, double* eps, double* V
   return launch<32, 32>(H, batch, n, eps, V, status, s);
 }
 
-// From 33 to 63 few matrices are level with Jacobi (n = 33: 469 by Jacobi and
-// 445 us here, n = 48: 680 and 750), 512 are not (n = 48: 2824 and 1371); n = 66,
-// one matrix: 1362 and 1270, n = 150: 9913 and 5409, n = 255, 64 matrices: 73 500
-// and 18 140.
-bool tridiag_large_better(int n, int64_t batch) {
-  return n > 32 && n <= kBigMax && (n >= 64 || batch >= 256);
+// Up to 22 the Jacobi rounds of few matrices are the shorter chain (whole calls,
+// n = 18, 64 matrices: 155 by Jacobi and 227 us here; 2048: 392 and 404, 4096: 751
+// and 684; n = 21, 64: 230 and 272, 2048: 560 and 476; n = 24, one: 460 and 260).
+// From 33 to 63 few
+// matrices are level (n = 33: 469 by Jacobi and 445 us here, n = 48: 680 and 750),
+// 512 are not (n = 48: 2824 and 1371); n = 66, one matrix: 1362 and 1270, n = 150:
+// 9913 and 5409, n = 255, 64 matrices: 73 500 and 18 140.
+bool tridiag_modes_better(int n, int64_t batch) {
+  if (n <= 32) return n > 22 || (n > 16 && batch >= 2048);
+  return n <= kBigMax && (n >= 64 || batch >= 256);
 }
 
-ephw_status tridiag_large_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
-                               hipStream_t s) {
+ephw_status tridiag_modes_eigh(double* H, int64_t batch, int n, double* eps, double* V, double* work, uint32_t* status,
+                               double close, hipStream_t s) {
   if (batch <= 0) return EPHW_OK;
-  if (n <= 32 || n > kBigMax) {
-    set_error("tridiag_large_eigh: matrix order must be in [33, 256]");
+  if (n <= 16 || n > kBigMax) {
+    set_error("tridiag_modes_eigh: matrix order must be in [17, 256]");
     return EPHW_EUNSUPPORTED;
   }
   if ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(V)) & 15) {
-    set_error("tridiag_large_eigh: matrices and eigenvectors must be 16-byte aligned complex128 arrays");
+    set_error("tridiag_modes_eigh: matrices and eigenvectors must be 16-byte aligned complex128 arrays");
     return EPHW_EINVAL;
   }
-  return launch_big(H, batch, n, eps, V, work, status, s);
+  if (n > 32) return launch_big(H, batch, n, eps, V, work, status, close, s);
+  if (n <= 24)
+    EPHW_TRY((launch<24, 32, true>(H, batch, n, eps, V, status, s, close)));
+  else
+    EPHW_TRY((launch<32, 32, true>(H, batch, n, eps, V, status, s, close)));
+  return jacobi_eigh_some(H, batch, n, eps, V, nullptr, status, s);
 }
 
 }  // namespace ephw

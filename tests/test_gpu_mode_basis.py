@@ -55,7 +55,7 @@ def reference(run, h, s, ks, q, kqi):
 # every call that takes the sizes: pair lists and the static scratch have up to 32
 # bands, pair lists no compensated sets
 FORMS = [(how, prec, nw, na, nq)
-         for nw, na, nq in [(4, 2, 9), (4, 6, 5), (3, 10, 5), (3, 12, 260), (2, 22, 5), (33, 22, 3)]
+         for nw, na, nq in [(4, 2, 9), (4, 6, 5), (1, 6, 2100), (4, 8, 5), (3, 10, 5), (3, 12, 260), (2, 22, 5), (33, 22, 3)]
          for prec in (0, 1, 2) for how in ("interpolate", "noalloc", "with_loss", "pairs")
          if not (nw > 32 and how in ("noalloc", "pairs")) and not (prec == 2 and how == "pairs")]
 
@@ -88,7 +88,7 @@ def test_modes_are_those_of_phonons(how, prec, nw, na, nq):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("nw,na,nq", [(4, 6, 5), (3, 12, 260), (2, 22, 5), (33, 22, 3)])
+@pytest.mark.parametrize("nw,na,nq", [(4, 6, 5), (1, 6, 2100), (4, 8, 5), (3, 10, 5), (3, 12, 260), (2, 22, 5), (33, 22, 3)])
 def test_modes_with_equal_components(prec, nw, na, nq):
     """Modes even or odd under a mirror: no solver's last bits may choose the
     component that fixes the phase."""
@@ -110,7 +110,7 @@ def test_modes_with_equal_components(prec, nw, na, nq):
     h.close()
 
 
-@pytest.mark.parametrize("nw,na", [(4, 6), (3, 9), (33, 22)])
+@pytest.mark.parametrize("nw,na", [(4, 6), (4, 8), (3, 9), (33, 22)])
 def test_loss_and_gradient_belong_together(nw, na):
     """FP64: L is quadratic in g, so central differences of the loss of
     ephw_interpolate along any direction equal the gradient's product with it."""
